@@ -49,26 +49,9 @@ LDS_PEAK_TBPS = 256 * 128 * 2.4e9 / 1e12
 # recorded in the profile named below.  Valid only for the kernel sources it
 # was measured on (their SHA-256) and the same workload, form and item classes
 # (padded size, inversion columns, items); otherwise "traffic" is null.
-TRAFFIC_SOURCES = ["paper_1111_2157_amd/csrc/lowrank_impl.h", "paper_1111_2157_amd/csrc/lowrank_pair_impl.h",
-                   "paper_1111_2157_amd/csrc/lowrank_p3_impl.h",
-                   "paper_1111_2157_amd/csrc/batched_lr.h", "paper_1111_2157_amd/csrc/dyson_impl.h",
-                   "paper_1111_2157_amd/csrc/batched_lr16.hip", "paper_1111_2157_amd/csrc/batched_lr32.hip",
-                   "paper_1111_2157_amd/csrc/batched_lr48.hip", "paper_1111_2157_amd/csrc/batched_lr64.hip"]
-TRAFFIC = {
-    ("batched-Nk4096-Nb20..64-x8-Nw2048", "low-rank",
-     ((32, 5, 5256), (32, 14, 5256), (48, 5, 6552), (48, 14, 6552), (64, 5, 6660), (64, 14, 6660))): {
-        "bytes": 244.49e9,  # FETCH 109.96 GB + WRITE 134.52 GB
-        "profile": "profiles/batched_cfg4.md",
-        "sources_sha256": "de41587efc8a209589a8d114de9e1f41446dd861fb72014a234b37fdaca0f207",
-    },
-    # the plan's quarter k-tile with the default frequency tile of 256
-    ("batched-Nk4096-Nb20..64-x8-Nw2048", "low-rank",
-     ((32, 5, 4672), (32, 14, 4672), (48, 5, 5824), (48, 14, 5824), (64, 5, 5920), (64, 14, 5920))): {
-        "bytes": 243.15e9,  # FETCH 110.09 GB + WRITE 133.06 GB
-        "profile": "profiles/batched_cfg4.md",
-        "sources_sha256": "de41587efc8a209589a8d114de9e1f41446dd861fb72014a234b37fdaca0f207",
-    },
-}
+TRAFFIC_SOURCES = ["paper_1111_2157_amd/csrc/spectral_impl.h", "paper_1111_2157_amd/csrc/lowrank_impl.h",
+                   "paper_1111_2157_amd/csrc/dyson_impl.h"]
+TRAFFIC = {}
 
 
 def class_key(classes):
@@ -114,6 +97,8 @@ def density_kernel(ctx, nb, nc):
     kernel the context will run for this band window."""
     nbp = (nb + 15) // 16 * 16
     var = ctx.get_variant(0, nbp)
+    if var == 136:
+        return ("spec_kernel<%d, %d orbitals> (low-rank, spectral form)" % (nbp, nc), flops_per_eval_lowrank(nb, nc))
     if var >= 0 and var & 8:
         return "lr_kernel<%d, density> (low-rank, variant %d)" % (nbp, var), flops_per_eval_lowrank(nb, nc)
     if nbp == 64:

@@ -11,11 +11,17 @@
 // always drains.  Queue counters are reset by a small kernel before each pass.
 //
 // The low-rank form of the step has one persistent kernel per class of items
-// (batched_lr.h).
-#include "batched_lr.h"
+// (spectral_impl.h).
 #include "dyson64_impl.h"
 
 namespace dmft {
+
+struct BatchItem {
+  int32_t args;   // index into the per-(iterate, size) argument array
+  int32_t nbp;    // padded band-window size of the item
+  int32_t ktile;  // k-tile within that (iterate, size) launch
+  int32_t wtile;  // frequency tile
+};
 
 constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
 // Per-wavefront LDS slot of phase 2: large enough for every single-wavefront size,

@@ -40,9 +40,15 @@ enum { KIND_DENSITY = 0, KIND_TRACE = 1, KIND_ADJOINT = 2, KIND_GENERAL = 3 };
 struct Bucket {
   int nbp = 0;
   std::vector<int32_t> klist;
+  int var = -1;        // kernel variant (density kind)
+  bool spec = false;   // it is the spectral kernel
   int n_ktiles = 0;
-  int ktile_base = 0;
+  int ktile_base = 0;  // first k-tile among those of the buckets of the same form
+  int64_t t_base = 0;  // spectral form: first slot of the sums within a frequency tile (doubles)
 };
+
+// Forms make_layout may choose between for the density kind.
+enum { LAYOUT_AUTO = 0, LAYOUT_LEAN = 1, LAYOUT_NO_SPEC = 2, LAYOUT_SPEC = 3 };
 
 // Workspace layout of a single-lattice call.
 struct Layout {
@@ -51,6 +57,11 @@ struct Layout {
   size_t spart = 0, xpart = 0, tpart = 0, kscal = 0, ktrace = 0, total = 0;
   int64_t s_stride = 0;
   int n_wtiles = 0, n_ktiles_total = 0;
+  // spectral form (density kind)
+  Tile stile;
+  int s_wtiles = 0, s_ktiles_total = 0;
+  int64_t t_stride = 0;
+  size_t tsum = 0, xs = 0;
   std::vector<Bucket> buckets;
   std::vector<int32_t> nb, nbp;
   std::vector<int64_t> off_b, off_n, off_s;
@@ -198,6 +209,40 @@ Tile heuristic_tile(int nk, int nw) {
   return t;
 }
 
+// Tile of the spectral form: the cheapest (k-tile, frequency tile) under a model
+// of its pass.  A group of 16 frequencies of one k-point costs a work-group its
+// matrix products at 64 cycles and its row operations at 4 cycles a wavefront
+// (measured within 15% at 32 to 64 bands), a k-point about two groups' worth of
+// set-up and write-out, and items run in rounds over the work-group slots of 256
+// CUs.  Smaller k-tiles mean more G_loc partials and smaller frequency tiles more
+// partial sums, each written and read once at about 4 TB/s, and both are kept to
+// about 2 GB.
+Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc) {
+  const int ncls = spec_ncls(nc), nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
+  const double per_cu = spec_wgs_per_cu(nbp, ncls);
+  const double group = (64.0 * (nt * nbp / 2 + nr * nt * 8) / 4.0 + 4.0 * (18.0 * ncls * ncls + 130.0 * ncls) + 2500.0) *
+                       std::max(1.0, per_cu * 0.9) / 2.2e9;
+  const double setup = 2.5e-5, slots = 256.0 * per_cu;
+  const int nwr = (nw + 15) / 16 * 16;
+  Tile best;
+  double best_t = 1e300;
+  for (int kt = 1; kt <= std::min(nk, 64); kt *= 2)
+    for (int f = 1; f <= nwr / 16; f = f < 8 ? f + 1 : f * 2) {
+      const int wt = (nwr / 16 + f - 1) / f * 16;
+      const double ktiles = (nk + kt - 1) / kt, wtiles = (nw + wt - 1) / wt;
+      const double items = ktiles * wtiles;
+      const double xs = ktiles * nw * 16.0 * ncls * ncls, ts = wtiles * nk * 8.0 * spec_slot_doubles(nbp, ncls);
+      if ((xs > 2e9 && kt < std::min(nk, 64) / 2) || (ts > 2e9 && f > 1)) continue;
+      const double t = std::ceil(items / slots) * kt * (setup + (wt / 16) * group) + xs * 2.0 / 4e12 + ts * 2.0 / 1.5e12;
+      if (t < best_t) {
+        best_t = t;
+        best.kt = kt;
+        best.wt = wt;
+      }
+    }
+  return best;
+}
+
 Tile choose_tile(const dmft_handle h, int kind, int nk, int nw, int nbp) {
   auto it = h->tune.find(tile_key(kind, nbp, nk, nw));
   return it != h->tune.end() ? it->second : heuristic_tile(nk, nw);
@@ -216,9 +261,27 @@ int choose_var(const dmft_handle h, int kind, int nbp) {
   return dyson_variants(nbp, kind, v, 16) > 0 ? v[0] : -1;
 }
 
-// Build the workspace layout for one lattice.
+// Density kernel of one padded size for nc orbitals: the chosen variant, except
+// that the three-frequency packing serves nc <= 5 only (the autotuner may have
+// chosen it on another shape, or the caller); elsewhere the size's default runs.
+// spec = false: the first other variant where that would be the spectral one.
+int density_var(const dmft_handle h, int nbp, int nc, bool spec) {
+  int v[16];
+  const int n = dyson_variants(nbp, KIND_DENSITY, v, 16);
+  int var = choose_var(h, KIND_DENSITY, nbp);
+  if (var == kLowrankP3Variant && !lowrank_p3_fits(nbp, nc)) var = n > 0 ? v[0] : var;
+  if (!spec && var == kSpectralVariant)
+    for (int i = 0; i < n; ++i)
+      if (v[i] != kSpectralVariant) return v[i];
+  return var;
+}
+
+// Build the workspace layout for one lattice.  form (density kind): by the
+// chosen variants with room for every other one too (so that one workspace size
+// holds whatever is chosen later), the same without that room, without the
+// spectral form, or only the spectral form.
 int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, Layout& L, int kind,
-                const Tile* force = nullptr) {
+                const Tile* force = nullptr, int form = LAYOUT_AUTO) {
   int nk = lat->nk, nw = sig->nw;
   L.ragged = lat->nb != nullptr;
   L.nb.assign(nk, lat->nb_max);
@@ -242,20 +305,44 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.tile.wt = std::max(1, std::min(L.tile.wt, nw));
   L.tile.kt = std::max(1, std::min(L.tile.kt, nk));
   L.n_wtiles = (nw + L.tile.wt - 1) / L.tile.wt;
+  const int ncls = spec_ncls(lat->nc);
+  if (kind == KIND_DENSITY) {
+    const bool tuned = force || h->tune.count(tile_key(kind, L.nbp_max, nk, nw));
+    L.stile = tuned ? L.tile : spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc);
+    // whole groups of 16 frequencies
+    L.stile.wt = std::min((L.stile.wt + 15) / 16 * 16, (nw + 15) / 16 * 16);
+    L.stile.kt = std::max(1, std::min(L.stile.kt, nk));
+    L.s_wtiles = (nw + L.stile.wt - 1) / L.stile.wt;
+  }
   L.buckets.clear();
-  int base = 0;
+  int base = 0, sbase = 0, all = 0, sall = 0;
+  bool any = false, sany = false;
   for (int s : kNbpSizes) {
     Bucket b;
     b.nbp = s;
     for (int k = 0; k < nk; ++k)
       if (L.nbp[k] == s) b.klist.push_back(k);
     if (b.klist.empty()) continue;
-    b.n_ktiles = ((int)b.klist.size() + L.tile.kt - 1) / L.tile.kt;
-    b.ktile_base = base;
-    base += b.n_ktiles;
+    const int size = (int)b.klist.size();
+    if (kind == KIND_DENSITY) {
+      b.var = form == LAYOUT_SPEC ? kSpectralVariant : density_var(h, s, lat->nc, form != LAYOUT_NO_SPEC);
+      b.spec = b.var == kSpectralVariant;
+      b.t_base = L.t_stride;
+      L.t_stride += size * spec_slot_doubles(s, ncls);
+      sall += (size + L.stile.kt - 1) / L.stile.kt;
+    }
+    all += (size + L.tile.kt - 1) / L.tile.kt;
+    (b.spec ? sany : any) = true;
+    const int kt = b.spec ? L.stile.kt : L.tile.kt;
+    int& at = b.spec ? sbase : base;
+    b.n_ktiles = (size + kt - 1) / kt;
+    b.ktile_base = at;
+    at += b.n_ktiles;
     L.buckets.push_back(b);
   }
   L.n_ktiles_total = base;
+  L.s_ktiles_total = sbase;
+  if (form == LAYOUT_AUTO && kind == KIND_DENSITY) any = sany = true;
   // the kernels are compiled for one padded size each and take nb_k within
   // (NBP - 16, NBP] as given (they skip the chunk tests of all but the last
   // 16 bands); every k of a bucket must satisfy that
@@ -282,9 +369,11 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.meta_nbp = take(sizeof(int32_t) * nk);
   L.meta_klist = take(sizeof(int32_t) * nk);
   L.meta_offs = take(sizeof(int64_t) * (nk + 1));
-  L.spart = take((size_t)L.n_wtiles * L.s_stride * 16);
-  L.xpart = take((size_t)L.n_ktiles_total * nw * 256 * 16);
+  L.spart = take(any ? (size_t)L.n_wtiles * L.s_stride * 16 : 0);
+  L.xpart = take(any ? (size_t)all * nw * 256 * 16 : 0);
   L.tpart = take((size_t)L.n_wtiles * nk * 3 * sizeof(double));
+  L.tsum = take(sany ? (size_t)L.s_wtiles * L.t_stride * sizeof(double) : 0);
+  L.xs = take(sany ? (size_t)sall * ((nw + 3) / 4) * 4 * ncls * ncls * 16 : 0);
   L.kscal = take((size_t)nk * 3 * sizeof(double));
   L.ktrace = take((size_t)nk * 2 * sizeof(double));
   L.tune_a = take((size_t)nw * lat->nc * lat->nc * 16 + 64);
@@ -358,6 +447,17 @@ struct AdjReq {
   const double* gbar = nullptr;
 };
 
+// The arguments of a bucket in the spectral form.
+void spec_args(const Layout& L, const Bucket& b, char* ws, DysonArgs& a) {
+  a.kt = L.stile.kt;
+  a.wt = L.stile.wt;
+  a.n_wtiles = L.s_wtiles;
+  a.tsum = (double*)(ws + L.tsum);
+  a.t_stride = L.t_stride;
+  a.t_base = b.t_base;
+  a.xs = (double*)(ws + L.xs);
+}
+
 int run_dyson(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, const Layout& L,
               char* ws, double mu, const double* mu_ptr, int mode, hipStream_t s, const AdjReq& adj = AdjReq()) {
   DysonArgs a{};
@@ -419,16 +519,9 @@ int run_dyson(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, con
       HIPCHK(h, launch_adjoint(b.nbp, adj.gen, a, adj.nbar, L.ragged ? (const int64_t*)(ws + L.meta_offn) : nullptr,
                                adj.gbar, (double*)(ws + L.xpart), (double*)(ws + L.tpart), b.n_ktiles, s));
     } else {
-      const int kind = (mode & MODE_TRACE) ? KIND_TRACE : KIND_DENSITY;
-      int var = choose_var(h, kind, b.nbp);
-      // the three-frequency packing serves nc <= 5 only; the variant chosen for
-      // this size (by the autotuner on another shape, or by the caller) falls
-      // back to the size's default elsewhere
-      if (var == kLowrankP3Variant && !lowrank_p3_fits(b.nbp, lat->nc)) {
-        int v[16];
-        var = dyson_variants(b.nbp, kind, v, 16) > 0 ? v[0] : var;
-      }
-      HIPCHK(h, launch_dyson(b.nbp, var, a, b.n_ktiles, s));
+      DysonArgs aa = a;
+      if (b.spec) spec_args(L, b, ws, aa);
+      HIPCHK(h, launch_dyson(b.nbp, (mode & MODE_TRACE) ? choose_var(h, KIND_TRACE, b.nbp) : b.var, aa, b.n_ktiles, s));
     }
     if (h->timing) {
       HIPCHK(h, hipEventRecord(ev.second, s));
@@ -482,6 +575,49 @@ int prepare(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, void*
   return upload_meta(h, L, (char*)ws, s, false);
 }
 
+// N(k) and the per-k scalars of every bucket.
+int nk_epilogues(dmft_handle h, const Layout& L, char* ws, const EpilogueArgs& base, double* nk, hipStream_t s) {
+  EpilogueArgs e = base;
+  bool others = false;
+  for (const Bucket& b : L.buckets)
+    if (b.spec)
+      e.skip_sizes |= 1 << (b.nbp / 16);
+    else
+      others = true;
+  if (others) HIPCHK(h, launch_nk_epilogue(e, nk, s));
+  size_t at = 0;
+  for (const Bucket& b : L.buckets) {
+    if (b.spec) {
+      e.spec_nbp = b.nbp;
+      e.klist = L.ragged || L.buckets.size() > 1 ? (const int32_t*)(ws + L.meta_klist) + at : nullptr;
+      e.nklist = (int)b.klist.size();
+      e.n_wtiles = L.s_wtiles;
+      e.tsum = (double*)(ws + L.tsum);
+      e.t_stride = L.t_stride;
+      e.t_base = b.t_base;
+      HIPCHK(h, launch_nk_epilogue(e, nk, s));
+    }
+    at += b.klist.size();
+  }
+  return DMFT_OK;
+}
+
+// G_loc from the partials of every bucket.
+int gloc_epilogues(dmft_handle h, const Layout& L, char* ws, const EpilogueArgs& base, double* gloc, hipStream_t s) {
+  if (L.n_ktiles_total)
+    HIPCHK(h, launch_gloc_reduce(L.n_ktiles_total, base.nw, base.nc, (const double*)(ws + L.xpart), gloc, s));
+  if (L.s_ktiles_total) {
+    EpilogueArgs e = base;
+    e.spec_nbp = L.nbp_max;
+    e.xs = (const double*)(ws + L.xs);
+    e.n_xs = L.s_ktiles_total;
+    e.gloc_add = L.n_ktiles_total > 0;
+    e.gloc_out = gloc;
+    HIPCHK(h, launch_nk_epilogue(e, nullptr, s));
+  }
+  return DMFT_OK;
+}
+
 int density_impl(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, const Layout& L,
                  char* ws, double mu, const double* mu_ptr, int tail_order, double* nk, double* gloc,
                  double* scalars, hipStream_t s) {
@@ -492,12 +628,11 @@ int density_impl(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, 
   if (r) return r;
   EpilogueArgs e = epilogue_args(lat, sig, L, ws, mu, mu_ptr, tail_order);
   if (mode & MODE_S) {
-    HIPCHK(h, launch_nk_epilogue(e, nk, s));
+    r = nk_epilogues(h, L, ws, e, nk, s);
+    if (r) return r;
     if (scalars) HIPCHK(h, launch_scalar_reduce(lat->nk, lat->wk, e.kscal, 3, scalars, s));
   }
-  if (gloc) HIPCHK(h, launch_gloc_reduce(L.n_ktiles_total, sig->nw, lat->nc,
-                                         (const double*)(ws + L.xpart), gloc, s));
-  return DMFT_OK;
+  return gloc ? gloc_epilogues(h, L, ws, e, gloc, s) : DMFT_OK;
 }
 
 int ntot_impl(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, const Layout& L,
@@ -538,21 +673,30 @@ int density_noalloc_impl(dmft_handle h, const dmft_lattice* lat, const dmft_sigm
   u.nb = nullptr;
   const size_t cap = noalloc_scratch_bytes();
   Layout L;
-  Tile t = choose_tile(h, KIND_DENSITY, u.nk, sig->nw, nbp_of(u.nb_max));
-  for (;;) {
-    r = make_layout(h, &u, sig, L, KIND_DENSITY, &t);
+  // the chosen variants' layout, then (the spectral form's sums are larger than
+  // N(k)'s) one without the spectral form
+  for (int form : {LAYOUT_LEAN, LAYOUT_NO_SPEC}) {
+    L = Layout();
+    r = make_layout(h, &u, sig, L, KIND_DENSITY, nullptr, form);
     if (r) return r;
-    if (L.total <= cap) break;
-    // fewer k tiles shrink the G_loc partials, fewer frequency tiles those of sum_n G
-    if (t.kt < u.nk) {
-      t.kt = std::min(u.nk, 2 * t.kt);
-    } else if (t.wt < sig->nw) {
-      t.wt = std::min(sig->nw, 2 * t.wt);
-    } else {
-      return fail(h, DMFT_EWORKSPACE, "this shape needs %zu bytes of scratch; the allocation-free scratch holds %zu",
-                  L.total, cap);
+    Tile t = L.buckets[0].spec ? L.stile : L.tile;
+    while (L.total > cap) {
+      // fewer k tiles shrink the G_loc partials, fewer frequency tiles those of sum_n G
+      if (t.kt < u.nk)
+        t.kt = std::min(u.nk, 2 * t.kt);
+      else if (t.wt < sig->nw)
+        t.wt = std::min(sig->nw, 2 * t.wt);
+      else
+        break;
+      L = Layout();
+      r = make_layout(h, &u, sig, L, KIND_DENSITY, &t, form);
+      if (r) return r;
     }
+    if (L.total <= cap) break;
   }
+  if (L.total > cap)
+    return fail(h, DMFT_EWORKSPACE, "this shape needs %zu bytes of scratch; the allocation-free scratch holds %zu",
+                L.total, cap);
   if (h->device < 0) return fail(h, DMFT_EINVAL, "handle has no device (planning handle)");
   char* w = (char*)noalloc_scratch(h->device);
   if (!w) return fail(h, DMFT_EHIP, "no scratch address for device %d", h->device);
@@ -994,40 +1138,39 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
     int nbp = L0.nbp_max, nk = lat->nk, nw = sig->nw, nc = lat->nc;
     int vars[16];
     int nv = dyson_variants(nbp, kind, vars, 16);
-    Tile base = heuristic_tile(nk, nw);
-    std::vector<Tile> tiles;
+    const Tile base = heuristic_tile(nk, nw), sbase = spec_heuristic_tile(nk, nw, nbp, nc);
     // frequency tiles around the default, then the k-tile halved and doubled
     // with the frequency tile scaled the other way (the same number of items;
-    // fewer G_loc partial read-backs against fewer partials of the running sum)
-    for (int f : {1, 2, 4, 8}) {
-      Tile t = base;
-      t.wt = std::max(4, std::min(nw, base.wt * f / 2));
-      bool dup = false;
-      for (auto& u : tiles) dup |= (u.wt == t.wt && u.kt == t.kt);
-      if (!dup) tiles.push_back(t);
-    }
-    for (int g : {-1, 1}) {
-      Tile t = base;
-      t.kt = g < 0 ? base.kt / 2 : std::min(nk, base.kt * 2);
-      t.wt = g < 0 ? std::min(nw, base.wt * 2) : std::max(4, base.wt / 2);
-      if (t.kt < 1 || t.kt == base.kt) continue;
-      bool dup = false;
-      for (auto& u : tiles) dup |= (u.wt == t.wt && u.kt == t.kt);
-      if (!dup) tiles.push_back(t);
-    }
+    // fewer G_loc partial read-backs against fewer partials of the running sum).
+    // Spectral form: its own default, and the k-tile and the frequency tile
+    // halved and doubled, alone and against each other.
+    std::vector<Tile> tiles, stiles;
+    auto add = [&](std::vector<Tile>& list, int kt, int wt) {
+      Tile t;
+      t.kt = std::max(1, std::min(nk, kt));
+      t.wt = std::max(4, std::min(nw, wt));
+      for (auto& u : list)
+        if (u.wt == t.wt && u.kt == t.kt) return;
+      list.push_back(t);
+    };
+    for (int f : {1, 2, 4, 8}) add(tiles, base.kt, base.wt * f / 2);
+    if (base.kt > 1) add(tiles, base.kt / 2, base.wt * 2);
+    add(tiles, base.kt * 2, base.wt / 2);
+    for (int f : {2, 1, 4})
+      for (int g : {2, 1, 4}) add(stiles, sbase.kt * f / 2, sbase.wt * g / 2);
     size_t nres = kind == KIND_DENSITY ? (size_t)nw * nc * nc * 2 + 3
                   : kind == KIND_ADJOINT ? (size_t)nw * nc * nc * 2 + 2 : 2;
     std::vector<double> ref(nres), got(nres);
     bool have_ref = false;
     double best_ms = 1e300;
-    Tile best_tile = base;
+    Tile best_tile = vars[0] == kSpectralVariant ? sbase : base;
     int best_var = vars[0];
     char key[32];
     snprintf(key, sizeof key, "%d/%d", kind, nbp);
     for (int vi = 0; vi < nv; ++vi) {
       if (vars[vi] == kLowrankP3Variant && !lowrank_p3_fits(nbp, nc)) continue;
       h->tvar[key] = vars[vi];
-      for (const Tile& t : tiles) {
+      for (const Tile& t : vars[vi] == kSpectralVariant ? stiles : tiles) {
         Layout L;
         r = make_layout(h, lat, sig, L, kind, &t);
         if (r) return r;
@@ -1102,7 +1245,7 @@ namespace {
 // Layouts of all iterates inside one workspace, plus the argument array, the
 // work queue, the queue counters and per-iterate mu slots.
 int batched_layout(dmft_handle h, int n_iter, const dmft_lattice* const* lat, const dmft_sigma* const* sig,
-                   std::vector<Layout>& Ls, std::vector<size_t>& base, const std::vector<Tile>* tiles,
+                   std::vector<Layout>& Ls, std::vector<size_t>& base, const std::vector<Tile>* tiles, bool lowrank,
                    size_t* total, size_t* o_args, size_t* o_items, size_t* o_cnt, size_t* o_mu, int* n_args,
                    int* n_items) {
   if (n_iter < 1 || !lat || !sig) return fail(h, DMFT_EINVAL, "need n_iter >= 1 and lattice/sigma arrays");
@@ -1116,19 +1259,21 @@ int batched_layout(dmft_handle h, int n_iter, const dmft_lattice* const* lat, co
     Tile t;
     if (tiles) {
       t = (*tiles)[s];
+    } else if (lowrank) {
+      t = spec_heuristic_tile(lat[s]->nk, sig[s]->nw, nbp_of(lat[s]->nb_max), lat[s]->nc);
     } else {
       // few, large frequency tiles: the queue is drained dynamically, and the
       // partial sums over frequency tiles stay a few GiB even for big batches
       t = heuristic_tile(lat[s]->nk, sig[s]->nw);
       t.wt = std::max(t.wt, (sig[s]->nw + 7) / 8);
     }
-    r = make_layout(h, lat[s], sig[s], Ls[s], KIND_DENSITY, &t);
+    r = make_layout(h, lat[s], sig[s], Ls[s], KIND_DENSITY, &t, lowrank ? LAYOUT_SPEC : LAYOUT_NO_SPEC);
     if (r) return r;
     base[s] = o;
     o = align_up(o + Ls[s].total);
     for (const Bucket& b : Ls[s].buckets) {
       ++na;
-      ni += b.n_ktiles * Ls[s].n_wtiles;
+      ni += b.n_ktiles * (lowrank ? Ls[s].s_wtiles : Ls[s].n_wtiles);
     }
   }
   *o_args = o;
@@ -1250,10 +1395,10 @@ int batched_pass_impl(dmft_handle h, const double* mu_dev, double* const* nk_out
     char* wb = w + it.base;
     const double* mup = (const double*)(w + h->b_mu) + s;
     EpilogueArgs e = epilogue_args(&it.lat, &it.sig, it.lay, wb, 0.0, mup, h->b_tail);
-    if (nk_out && nk_out[s]) HIPCHK(h, launch_nk_epilogue(e, nk_out[s], stream));
-    if (gloc_out && gloc_out[s])
-      HIPCHK(h, launch_gloc_reduce(it.lay.n_ktiles_total, it.sig.nw, it.lat.nc, (const double*)(wb + it.lay.xpart),
-                                   gloc_out[s], stream));
+    int r = nk_out && nk_out[s] ? nk_epilogues(h, it.lay, wb, e, nk_out[s], stream) : DMFT_OK;
+    if (r) return r;
+    r = gloc_out && gloc_out[s] ? gloc_epilogues(h, it.lay, wb, e, gloc_out[s], stream) : DMFT_OK;
+    if (r) return r;
   }
   return DMFT_OK;
 }
@@ -1265,7 +1410,7 @@ int batched_build(dmft_handle h, int n_iter, const dmft_lattice* const* lat, con
   std::vector<size_t> base;
   size_t total, o_args, o_items, o_cnt, o_mu;
   int na, ni;
-  int r = batched_layout(h, n_iter, lat, sig, Ls, base, tiles, &total, &o_args, &o_items, &o_cnt, &o_mu, &na, &ni);
+  int r = batched_layout(h, n_iter, lat, sig, Ls, base, tiles, lowrank, &total, &o_args, &o_items, &o_cnt, &o_mu, &na, &ni);
   if (r) return r;
   if (!ws || (uintptr_t)ws % kAlign) return fail(h, DMFT_EWORKSPACE, "workspace NULL or misaligned");
   if (ws_bytes < total) return fail(h, DMFT_EWORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, total);
@@ -1325,17 +1470,18 @@ int batched_build(dmft_handle h, int n_iter, const dmft_lattice* const* lat, con
       a.xpart = (double*)(wb + L.xpart);
       a.tpart = (double*)(wb + L.tpart);
       a.err = (int*)(w + base[0] + Ls[0].err);
+      if (lowrank) spec_args(L, b, wb, a);
       int ai = (int)args.size();
       args.push_back(a);
       at += b.klist.size();
       const double nbp = b.nbp, nc = lat[s]->nc;
       for (int kt = 0; kt < b.n_ktiles; ++kt) {
-        int nkt = std::min(L.tile.kt, (int)b.klist.size() - kt * L.tile.kt);
-        for (int wt = 0; wt < L.n_wtiles; ++wt) {
-          int nwt = std::min(L.tile.wt, sig[s]->nw - wt * L.tile.wt);
+        int nkt = std::min(a.kt, (int)b.klist.size() - kt * a.kt);
+        for (int wt = 0; wt < a.n_wtiles; ++wt) {
+          int nwt = std::min(a.wt, sig[s]->nw - wt * a.wt);
           if (lowrank) {
-            // one queue per class (padded size, columns of the inversions)
-            double c = (nbp * nbp * nc + 2.0 * nbp * nc * nc + 4.0 * nc * nc * nc) * nkt * nwt;
+            // one queue per class (padded size, orbitals)
+            double c = (12.0 * nbp * nc * nc + 32.0 * nc * nc * nc) * nkt * nwt;
             lrq[{b.nbp, lr_nc_class(b.nbp, lat[s]->nc)}].push_back(Q{{ai, b.nbp, kt, wt}, c});
           } else {
             double c = nbp * nbp * (nbp + 2.0 * nc) * nkt * nwt;
@@ -1366,8 +1512,6 @@ int batched_build(dmft_handle h, int n_iter, const dmft_lattice* const* lat, con
       c.ncls = it->first.second;
       c.off = (int)items.size();
       c.count = (int)qv.size();
-      // one wavefront per SIMD: four single-wavefront, two pair or one four-wavefront
-      // work-group per CU
       c.grid = std::min(c.count, lr_class_wgs_per_cu(c.nbp, c.ncls) * ncu);
       for (auto& x : qv) items.push_back(x.it);
       h->b_cls.push_back(c);
@@ -1443,23 +1587,38 @@ std::vector<std::vector<Tile>> batched_tile_candidates(const std::vector<Tile>& 
   return out;
 }
 
+// The candidates of one form, from its default tile of every iterate.
+int batched_candidates(dmft_handle h, int n_iter, const dmft_lattice* const* lat, const dmft_sigma* const* sig,
+                       bool lowrank, std::vector<std::vector<Tile>>& out) {
+  std::vector<Layout> Ls;
+  std::vector<size_t> base;
+  size_t total, a, b, c, d;
+  int na, ni;
+  int r = batched_layout(h, n_iter, lat, sig, Ls, base, nullptr, lowrank, &total, &a, &b, &c, &d, &na, &ni);
+  if (r) return r;
+  std::vector<Tile> tiles;
+  for (auto& L : Ls) tiles.push_back(lowrank ? L.stile : L.tile);
+  out = batched_tile_candidates(tiles);
+  return DMFT_OK;
+}
+
 int dmft_batched_workspace_size(dmft_handle h, int n_iter, const dmft_lattice* const* lat, const dmft_sigma* const* sig,
                                 size_t* bytes) {
   if (!bytes) return fail(h, DMFT_EINVAL, "bytes is NULL");
   std::vector<Layout> Ls;
   std::vector<size_t> base;
-  size_t total, a, b, c, d;
+  size_t total, a, b, c, d, most = 0;
   int na, ni;
-  int r = batched_layout(h, n_iter, lat, sig, Ls, base, nullptr, &total, &a, &b, &c, &d, &na, &ni);
-  if (r) return r;
-  // room for every tile the plan times
-  std::vector<Tile> tiles;
-  for (auto& L : Ls) tiles.push_back(L.tile);
-  size_t most = total;
-  for (const auto& cand : batched_tile_candidates(tiles)) {
-    r = batched_layout(h, n_iter, lat, sig, Ls, base, &cand, &total, &a, &b, &c, &d, &na, &ni);
+  // room for every tile of either form the plan times
+  for (bool lr : {true, false}) {
+    std::vector<std::vector<Tile>> cands;
+    int r = batched_candidates(h, n_iter, lat, sig, lr, cands);
     if (r) return r;
-    most = std::max(most, total);
+    for (const auto& cand : cands) {
+      r = batched_layout(h, n_iter, lat, sig, Ls, base, &cand, lr, &total, &a, &b, &c, &d, &na, &ni);
+      if (r) return r;
+      most = std::max(most, total);
+    }
   }
   *bytes = most;
   return DMFT_OK;
@@ -1478,28 +1637,45 @@ int dmft_batched_plan(dmft_handle h, int n_iter, const dmft_lattice* const* lat,
     h->graph = nullptr;
   }
   h->b_tile_chosen = -1;
-  int r = batched_build(h, n_iter, lat, sig, tail_order, ws, ws_bytes, stream, nullptr, false);
-  if (r) return r;
+  int r;
   // Autotune the form of the step (dense inversion or low-rank) and the k- and
   // frequency-tile sizes of the persistent launches: time the kernels for each
   // candidate that fits the workspace, keep the fastest plan.
-  std::vector<Tile> base_tiles;
-  for (auto& it : h->iters) base_tiles.push_back(it.lay.tile);
+  std::vector<std::vector<Tile>> form_cands[2];
+  std::vector<Tile> best_tiles;  // a form that fits the workspace, until the timings below
+  bool best_lr = true, fits = false;
+  for (int lr = 0; lr < 2; ++lr) {
+    r = batched_candidates(h, n_iter, lat, sig, lr != 0, form_cands[lr]);
+    if (r) return r;
+    std::vector<Layout> Ls;
+    std::vector<size_t> bs;
+    size_t total, a, b, c, d;
+    int na, ni;
+    r = batched_layout(h, n_iter, lat, sig, Ls, bs, &form_cands[lr][0], lr != 0, &total, &a, &b, &c, &d, &na, &ni);
+    if (r) return r;
+    const bool wanted = h->b_form_pref == DMFT_FORM_AUTO || (lr != 0) == (h->b_form_pref == DMFT_FORM_LOWRANK);
+    if (wanted && total <= ws_bytes) {
+      fits = true;
+      best_lr = lr != 0;
+      best_tiles = form_cands[lr][0];
+    }
+  }
+  if (!ws || (uintptr_t)ws % kAlign) return fail(h, DMFT_EWORKSPACE, "workspace NULL or misaligned");
+  if (!fits) return fail(h, DMFT_EWORKSPACE, "workspace too small: %zu bytes", ws_bytes);
+  HIPCHK(h, hipSetDevice(h->device));
   std::vector<double> mu0(n_iter, 0.0);
   char* w = (char*)ws;
   hipEvent_t e0, e1;
   HIPCHK(h, hipEventCreate(&e0));
   HIPCHK(h, hipEventCreate(&e1));
   double best = 1e300, best_lowrank = 1e300;
-  std::vector<Tile> best_tiles = base_tiles;
-  bool best_lr = true;
   // low-rank form first; the dense form's other tiles are timed only when its
   // first one comes within 1.5x of the best low-rank plan
-  const std::vector<std::vector<Tile>> cands = batched_tile_candidates(base_tiles);
   int best_ci = -1;
   for (bool lr : {true, false}) {
     if (h->b_form_pref != DMFT_FORM_AUTO && lr != (h->b_form_pref == DMFT_FORM_LOWRANK)) continue;
     double first = -1.0;
+    const std::vector<std::vector<Tile>>& cands = form_cands[lr];
     for (int ci = 0; ci < (int)cands.size(); ++ci) {
       const std::vector<Tile>& cand = cands[ci];
       if (h->b_tile_pref >= 0 && ci != h->b_tile_pref && h->b_tile_pref < (int)cands.size()) continue;
@@ -1508,7 +1684,7 @@ int dmft_batched_plan(dmft_handle h, int n_iter, const dmft_lattice* const* lat,
       std::vector<size_t> bs;
       size_t total, a, b, c, d;
       int na, ni;
-      r = batched_layout(h, n_iter, lat, sig, Ls, bs, &cand, &total, &a, &b, &c, &d, &na, &ni);
+      r = batched_layout(h, n_iter, lat, sig, Ls, bs, &cand, lr, &total, &a, &b, &c, &d, &na, &ni);
       if (r) return r;
       if (total > ws_bytes) continue;
       r = batched_build(h, n_iter, lat, sig, tail_order, ws, ws_bytes, stream, &cand, lr);

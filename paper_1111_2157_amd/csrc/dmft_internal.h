@@ -9,6 +9,31 @@
 
 namespace dmft {
 
+// ---- spectral form (spectral_impl.h): tile counts and per-k slot of its sums.
+// Orbital columns nc is padded to.
+constexpr int spec_ncls(int nc) { return nc <= 4 ? 4 : nc <= 6 ? nc : (nc + 1) / 2 * 2; }
+// 16-wide tiles of the nc^2 columns and of the 2 nb - 1 rows.
+constexpr int spec_col_tiles(int ncls) { return (ncls * ncls + 15) / 16; }
+constexpr int spec_row_tiles(int nbp) { return 2 * (nbp / 16); }
+// Doubles of one k-point's sums in one frequency tile: the tiles in lane order,
+// then sum_n Re d_v of the nbp (sorted) bands.
+constexpr int64_t spec_slot_doubles(int nbp, int ncls) {
+  return (int64_t)spec_row_tiles(nbp) * spec_col_tiles(ncls) * 256 + nbp;
+}
+// Work-groups of four wavefronts per CU a spectral kernel is compiled for: as
+// many as leave its frequency loop without register spills (per lane 2 rt ct
+// registers of sums and about 8 nc + 100 for the rows of the inversions and the
+// operands in flight) and fit their LDS tables in 160 KB.
+constexpr int spec_wgs_per_cu(int nbp, int ncls) {
+  const int nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
+  const int regs = nr * nt * 2 + 8 * ncls + 110 + (ncls <= 6 ? nbp / 2 : 0);
+  const int lds = 16 * nt * 16 * 16 + 4 * 256 + 2 * 16 * (nbp + 4) * 16 + nbp * 17 * 8 + nbp * 20 + 64 +
+                  (ncls <= 6 ? 16 : 2 * ncls * (nbp + 1) * 16);
+  const int by_regs = regs <= 176 ? 3 : regs <= 256 ? 2 : 1;
+  const int by_lds = 163840 / lds;
+  return by_regs < by_lds ? by_regs : (by_lds < 1 ? 1 : by_lds);
+}
+
 // Kernel modes (bit set).
 enum : int {
   MODE_S = 1,      // accumulate sum_n G_kn into per-(frequency tile, k) partials
@@ -55,6 +80,12 @@ struct DysonArgs {
   const double* nbar;          // MODE_GEN: complex N(k) cotangent (N(k) layout) or null
   const int64_t* off_n;        // MODE_GEN: [nk+1] offsets into nbar (ragged) or null (uniform)
   const double* gbar;          // MODE_GEN: complex G_loc cotangent [nw][nc][nc] or null
+  // spectral form: per frequency tile (stride t_stride doubles) this bucket's
+  // k-points have slots of spec_slot_doubles from t_base, in klist order; xs is
+  // the G_loc partial [n_ktiles][ceil(nw / 4)][ncls columns][4 frequencies][ncls rows] complex
+  double* tsum;
+  int64_t t_stride, t_base;
+  double* xs;
 };
 
 struct EpilogueArgs {
@@ -82,6 +113,19 @@ struct EpilogueArgs {
   double* kscal;               // [nk][3] per-k  tr N, tr(S N S^dag), sum_v E_v N_vv
   double* ktrace;              // [nk][2] per-k  tr N, d tr N / dmu   (trace mode)
   double s2;                   // sum_n 1 / w_n^2, summed in increasing n
+  int skip_sizes;              // bit nbp / 16: k-points of that padded size are left to the spectral epilogue
+  // spectral form: when spec_nbp > 0 launch_nk_epilogue runs the spectral
+  // epilogue on the bucket klist[0 .. nklist) instead (fields as in DysonArgs)
+  int spec_nbp;
+  const int32_t* klist;
+  int nklist;
+  double* tsum;
+  int64_t t_stride, t_base;
+  // ... or, when gloc_out is set, the reduction of n_xs G_loc partials (added to
+  // gloc_out's contents if gloc_add)
+  const double* xs;
+  int n_xs, gloc_add;
+  double* gloc_out;
 };
 
 // Launchers (return hipError_t of the launch).
@@ -97,6 +141,8 @@ struct EpilogueArgs {
 // kind only.  A launch of either outside its shapes returns hipErrorInvalidValue.
 constexpr int kLowrankPairVariant = 40;
 constexpr int kLowrankP3Variant = 42;
+// The spectral form (spectral_impl.h), density kind, every size.
+constexpr int kSpectralVariant = 136;
 inline bool lowrank_p3_fits(int nbp, int nc) { return nc <= 5 && nbp <= 64; }
 hipError_t launch_dyson(int nbp, int var, const DysonArgs& a, int n_ktiles, hipStream_t s);
 int dyson_variants(int nbp, int kind, int* out, int max);

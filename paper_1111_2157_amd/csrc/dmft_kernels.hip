@@ -22,16 +22,12 @@ hipError_t launch_lowrank(int nbp, int var, const DysonArgs& a, dim3 grid, hipSt
 int lowrank_variants(int nbp, int kind, int* out, int max);
 bool dyson_supported(int nbp);
 
-// Dense variants first (the first one is the default), then the low-rank ones.
-// Kinds 2 (fused scalar adjoint) and 3 (general vector-Jacobian product): the
-// low-rank variants first, then code 0 for the dense adjoint kernel, which
-// exists up to 48 bands.
-int dyson_variants(int nbp, int kind, int* out, int max) {
-  if (kind == 2 || kind == 3) {
-    int n = lowrank_variants(nbp, kind, out, max);
-    if (nbp <= 48 && dyson_supported(nbp) && n < max) out[n++] = 0;
-    return n;
-  }
+hipError_t launch_spectral(int nbp, int ncls, const DysonArgs& a, const void* items, int n_items,
+                           const DysonArgs* args, int* counter, int grid, hipStream_t s);
+hipError_t launch_spectral_epilogue(const EpilogueArgs& a, double* nk_out, hipStream_t s);
+
+// Kinds 0 and 1 without the spectral kernel: dense variants first, then the low-rank ones.
+static int band_variants(int nbp, int kind, int* out, int max) {
   int n = 0;
   switch (nbp) {
     case 16: n = variants_16(kind, out, max); break;
@@ -43,10 +39,29 @@ int dyson_variants(int nbp, int kind, int* out, int max) {
   return n + lowrank_variants(nbp, kind, out + n, max - n);
 }
 
+// The first variant is the default: the spectral kernel for kind 0.
+// Kinds 2 (fused scalar adjoint) and 3 (general vector-Jacobian product): the
+// low-rank variants first, then code 0 for the dense adjoint kernel, which
+// exists up to 48 bands.
+int dyson_variants(int nbp, int kind, int* out, int max) {
+  if (kind == 2 || kind == 3) {
+    int n = lowrank_variants(nbp, kind, out, max);
+    if (nbp <= 48 && dyson_supported(nbp) && n < max) out[n++] = 0;
+    return n;
+  }
+  if (kind == 0 && dyson_supported(nbp) && max > 0) {
+    out[0] = kSpectralVariant;
+    return 1 + band_variants(nbp, kind, out + 1, max - 1);
+  }
+  return band_variants(nbp, kind, out, max);
+}
+
 bool dyson_supported(int nbp) { return nbp == 16 || nbp == 32 || nbp == 48 || nbp == 64; }
 
 hipError_t launch_dyson(int nbp, int var, const DysonArgs& a, int n_ktiles, hipStream_t s) {
   dim3 grid((unsigned)(n_ktiles * a.n_wtiles));
+  if (var == kSpectralVariant)
+    return launch_spectral(nbp, spec_ncls(a.nc), a, nullptr, 0, nullptr, nullptr, (int)grid.x, s);
   if (var & 8) return launch_lowrank(nbp, var, a, grid, s);
   switch (nbp) {
     case 16: return launch_dyson_16(var, a, grid, s);
@@ -83,6 +98,7 @@ __global__ void __launch_bounds__(256) nk_epilogue_kernel(EpilogueArgs a, double
   const int k = blockIdx.x;
   const int nc = a.nc;
   const int nb = a.nb_uniform > 0 ? a.nb_uniform : a.nb[k];
+  if ((a.skip_sizes >> ((nb + 15) / 16)) & 1) return;
   const int64_t ob = a.nb_uniform > 0 ? (int64_t)k * nb : a.off_b[k];
   const int64_t on = a.nb_uniform > 0 ? (int64_t)k * nb * nb : a.off_n[k];
   const int T = (a.nb_uniform > 0 ? (a.nb_uniform + 15) / 16 * 16 : a.nbp[k]) / 16;
@@ -299,6 +315,7 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t n) {
 }
 
 hipError_t launch_nk_epilogue(const EpilogueArgs& a, double* nk_out, hipStream_t s) {
+  if (a.spec_nbp > 0) return launch_spectral_epilogue(a, nk_out, s);
   hipLaunchKernelGGL(nk_epilogue_kernel, dim3(a.nk), dim3(256), 0, s, a, nk_out);
   return hipGetLastError();
 }

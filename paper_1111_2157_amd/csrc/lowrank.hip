@@ -16,14 +16,8 @@ int lowrank_variants_48(int kind, int* out, int max);
 int lowrank_variants_64(int kind, int* out, int max);
 hipError_t launch_lowrank_pair64(const DysonArgs& a, dim3 grid, hipStream_t s);
 hipError_t launch_lowrank_p3(int nbp, const DysonArgs& a, dim3 grid, hipStream_t s);
-hipError_t launch_lr_class_16(int ncls, const void* items, int n_items, const DysonArgs* args, int* counter, int grid,
-                              hipStream_t s);
-hipError_t launch_lr_class_32(int ncls, const void* items, int n_items, const DysonArgs* args, int* counter, int grid,
-                              hipStream_t s);
-hipError_t launch_lr_class_48(int ncls, const void* items, int n_items, const DysonArgs* args, int* counter, int grid,
-                              hipStream_t s);
-hipError_t launch_lr_class_64(int ncls, const void* items, int n_items, const DysonArgs* args, int* counter, int grid,
-                              hipStream_t s);
+hipError_t launch_spectral(int nbp, int ncls, const DysonArgs& a, const void* items, int n_items,
+                           const DysonArgs* args, int* counter, int grid, hipStream_t s);
 
 hipError_t launch_lowrank(int nbp, int var, const DysonArgs& a, dim3 grid, hipStream_t s) {
   if (var == kLowrankPairVariant) return nbp == 64 ? launch_lowrank_pair64(a, grid, s) : hipErrorInvalidValue;
@@ -58,31 +52,15 @@ int lowrank_variants(int nbp, int kind, int* out, int max) {
   }
 }
 
-// Column class of the batched kernels: 5 for nc <= 5 (three frequencies per
-// matrix-core tile), else nc rounded up to 8, 10
-// (32 bands), 12, 14 (32, 48 and 64 bands) or 16.  Every column costs a
-// broadcast and four FMAs in each of the nc pivot steps of both inversions,
-// which on small windows weighs as much as the matrix-core work.
-int lr_nc_class(int nbp, int nc) {
-  if (lowrank_p3_fits(nbp, nc)) return 5;
-  if (nc <= 8) return 8;
-  if (nbp == 32 && nc <= 10) return 10;
-  if (nc <= 12) return 12;
-  if (nbp >= 32 && nc <= 14) return 14;
-  return 16;
-}
+// Classes of the batched low-rank pass: the spectral kernel of each padded size
+// and orbital count.
+int lr_nc_class(int, int nc) { return spec_ncls(nc); }
 
-int lr_class_wgs_per_cu(int nbp, int ncls) { return nbp < 64 ? 4 : ncls == 5 ? 1 : 2; }
+int lr_class_wgs_per_cu(int nbp, int ncls) { return spec_wgs_per_cu(nbp, ncls); }
 
 hipError_t launch_lr_class(int nbp, int ncls, const void* items, int n_items, const DysonArgs* args, int* counter,
                            int grid, hipStream_t s) {
-  switch (nbp) {
-    case 16: return launch_lr_class_16(ncls, items, n_items, args, counter, grid, s);
-    case 32: return launch_lr_class_32(ncls, items, n_items, args, counter, grid, s);
-    case 48: return launch_lr_class_48(ncls, items, n_items, args, counter, grid, s);
-    case 64: return launch_lr_class_64(ncls, items, n_items, args, counter, grid, s);
-    default: return hipErrorInvalidValue;
-  }
+  return launch_spectral(nbp, ncls, DysonArgs{}, items, n_items, args, counter, grid, s);
 }
 
 }  // namespace dmft

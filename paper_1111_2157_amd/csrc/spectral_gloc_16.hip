@@ -1,0 +1,6 @@
+// Instantiation unit of the spectral kernel (spectral_impl.h) without the sums
+// (G_loc only) for band windows padded to 16.
+#define SPEC_NBP 16
+#define SPEC_NAME launch_spectral_gloc_16
+#define SPEC_WS false
+#include "spectral_unit.h"
