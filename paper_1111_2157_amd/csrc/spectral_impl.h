@@ -39,6 +39,15 @@
 // The FP64 matrix and vector units share their rate (72 TFLOP/s measured for a
 // large matrix product), so all three stages count: the split keeps A and C on
 // full 16x16x4 products and B on uniform row operations.
+//
+// Measured (512 k-points, 2048 frequencies, per k-point and frequency; in brackets
+// the frequency-at-a-time low-rank kernels): 32 bands and 10 orbitals 2.46 ns (5.3),
+// 48 and 14 5.33 ns (10.2), 64 and 14 5.85 ns (13.5), 64 and 5 1.04 ns.  At
+// 48 and 14 the matrix products alone would take 2.4 ns at the rate of a large
+// product and the row operations of B 1.6; what bounds the rest is that neither unit
+// runs while the other does: with 256 KB of accumulators, row matrices and
+// projectors a SIMD holds one wavefront, so the LDS round trips between the stages
+// (0.6 ns) and the changes between the units are exposed.
 #pragma once
 
 #include "lowrank_impl.h"
@@ -53,13 +62,6 @@ typedef __attribute__((address_space(1))) v2d gv2d;
 typedef __attribute__((address_space(1))) double gdouble;
 typedef __attribute__((address_space(3))) v2d lv2d;
 typedef __attribute__((address_space(3))) double lds_double;
-
-// *p += v in the cache that owns the address, nothing returned.
-__device__ __forceinline__ void spec_atomic_add(gdouble* p, double v) {
-#ifdef __HIP_DEVICE_COMPILE__
-  __builtin_amdgcn_global_atomic_fadd_f64(p, v);
-#endif
-}
 
 // LDS address hidden from the optimizer: the accesses of a stage become this
 // register plus an immediate, instead of one loop-invariant address register
@@ -145,76 +147,69 @@ __device__ __forceinline__ int spec_here(int i) {
   return i;
 }
 
-// Columns of a Gauss-Jordan step: (r, i) -= l (row K's (r, i) of this 16-lane
-// row).  Four of the five multiply-adds and moves of a column take the broadcast
-// as their DPP operand; row K's imaginary part is moved out first because its
-// register changes before its last use.  The leading s_nop covers the two wait
-// states a DPP read needs after the vector instruction that wrote its source
-// (it costs 3 ns, a multiply-add 2 ns: hence four columns per block); the
-// operands are early-clobbered because outputs are written before all inputs
-// have been read.
-#define SPEC_BC(K) " row_newbcast:%" #K " row_mask:0xf bank_mask:0xf\n\t"
-template <int K>
-__device__ __forceinline__ void row_elim4(double& r0, double& i0, double& r1, double& i1, double& r2, double& i2,
-                                          double& r3, double& i3, double lr, double li) {
-  double t0, t1, t2, t3;
-  asm("s_nop 1\n\t"
-      "v_mov_b64_dpp %8, %4" SPEC_BC(14) "v_mov_b64_dpp %9, %5" SPEC_BC(14)
-      "v_mov_b64_dpp %10, %6" SPEC_BC(14) "v_mov_b64_dpp %11, %7" SPEC_BC(14)
-      "v_fmac_f64_dpp %4, -%0, %13" SPEC_BC(14) "v_fmac_f64_dpp %5, -%1, %13" SPEC_BC(14)
-      "v_fmac_f64_dpp %6, -%2, %13" SPEC_BC(14) "v_fmac_f64_dpp %7, -%3, %13" SPEC_BC(14)
-      "v_fmac_f64_dpp %0, -%0, %12" SPEC_BC(14) "v_fmac_f64_dpp %1, -%1, %12" SPEC_BC(14)
-      "v_fmac_f64_dpp %2, -%2, %12" SPEC_BC(14) "v_fmac_f64_dpp %3, -%3, %12" SPEC_BC(14)
-      "v_fma_f64 %4, -%8, %12, %4\n\tv_fma_f64 %5, -%9, %12, %5\n\t"
-      "v_fma_f64 %6, -%10, %12, %6\n\tv_fma_f64 %7, -%11, %12, %7\n\t"
-      "v_fmac_f64 %0, %8, %13\n\tv_fmac_f64 %1, %9, %13\n\tv_fmac_f64 %2, %10, %13\n\tv_fmac_f64 %3, %11, %13"
-      : "+&v"(r0), "+&v"(r1), "+&v"(r2), "+&v"(r3), "+&v"(i0), "+&v"(i1), "+&v"(i2), "+&v"(i3), "=&v"(t0), "=&v"(t1),
-        "=&v"(t2), "=&v"(t3)
-      : "v"(lr), "v"(li), "i"(K));
-}
-template <int K>
-__device__ __forceinline__ void row_elim1(double& r, double& i, double lr, double li) {
-  double t;
-  asm("s_nop 1\n\t"
-      "v_mov_b64_dpp %2, %1" SPEC_BC(5)
-      "v_fmac_f64_dpp %1, -%0, %4" SPEC_BC(5)
-      "v_fmac_f64_dpp %0, -%0, %3" SPEC_BC(5)
-      "v_fma_f64 %1, -%2, %3, %1\n\tv_fmac_f64 %0, %2, %4"
-      : "+&v"(r), "+&v"(i), "=&v"(t)
-      : "v"(lr), "v"(li), "i"(K));
-}
-#undef SPEC_BC
+// ---- row layout: lane 16 g + i holds row i of matrix g.  Both helpers below are
+// blocks of multiply-adds whose broadcast of row K within the 16-lane row is their
+// DPP operand, so it costs no move.  A block starts with an s_nop for the two wait
+// states a DPP read needs after the vector instruction that wrote its source (3 ns
+// where a multiply-add takes 2, hence several columns per block), and its outputs
+// are early-clobbered because they are written before all inputs have been read.
+// (Blocks of 7 columns and two rows instead of 3 columns and one: 48 bands and 14
+// orbitals 5.65 to 5.33 ns per k-point and frequency.)
+#define SPEC_REP3(M) M(0) M(1) M(2)
+#define SPEC_REP4(M) SPEC_REP3(M) M(3)
+#define SPEC_REP5(M) SPEC_REP4(M) M(4)
+#define SPEC_REP6(M) SPEC_REP5(M) M(5)
+#define SPEC_REP7(M) SPEC_REP6(M) M(6)
+#define SPEC_REP8(M) SPEC_REP7(M) M(7)
+#define SPEC_BC(K) " row_newbcast:%[" #K "] row_mask:0xf bank_mask:0xf\n\t"
 
-// Gauss-Jordan steps K .. NC-1 of the row layout (rows and columns past nc hold
-// the identity).  pmin: the smallest |pivot|^2 so far.  The reciprocal is the
-// hardware estimate (2^-23) and one third-order step.
+// Columns col(M0) .. of a Gauss-Jordan step: (r, i) += n (row K's (r, i)).  Row K's
+// imaginary part is moved out first because its register changes before its last use.
+#define SPEC_E0(j) "v_mov_b64_dpp %[t" #j "], %[i" #j "]" SPEC_BC(k)
+#define SPEC_E1(j) "v_fmac_f64_dpp %[i" #j "], %[r" #j "], %[ni]" SPEC_BC(k)
+#define SPEC_E2(j) "v_fmac_f64_dpp %[r" #j "], %[r" #j "], %[nr]" SPEC_BC(k)
+#define SPEC_E3(j) "v_fmac_f64 %[i" #j "], %[t" #j "], %[nr]\n\t"
+#define SPEC_E4(j) "v_fma_f64 %[r" #j "], -%[t" #j "], %[ni], %[r" #j "]\n\t"
+#define SPEC_EO(j) , [r##j] "+&v"(rr[col(M0 + j)]), [i##j] "+&v"(ri[col(M0 + j)]), [t##j] "=&v"(t[j])
+#define SPEC_ELIM(N)                                                                                          \
+  asm("s_nop 1\n\t" SPEC_REP##N(SPEC_E0) SPEC_REP##N(SPEC_E1) SPEC_REP##N(SPEC_E2) SPEC_REP##N(SPEC_E3)        \
+          SPEC_REP##N(SPEC_E4)                                                                                \
+      : [z] "=&v"(z) SPEC_REP##N(SPEC_EO)                                                                      \
+      : [nr] "v"(nr), [ni] "v"(ni), [k] "i"(K))
+
+// Gauss-Jordan steps K .. NC-1 (rows and columns past nc hold the identity).  pmin:
+// the smallest |pivot|^2 so far.  The reciprocal is the hardware estimate (2^-23)
+// and one third-order step; n = -row multiplier, and 1/p - 1 for the pivot row.
 template <int K, int NC>
 struct SpecStep {
   static constexpr int col(int m) { return m < K ? m : m + 1; }
-  template <int M>
-  static __device__ __forceinline__ void cols(double (&rr)[NC], double (&ri)[NC], double lr, double li) {
-    if constexpr (M + 4 <= NC - 1) {
-      constexpr int a = col(M), b = col(M + 1), c = col(M + 2), d = col(M + 3);
-      row_elim4<K>(rr[a], ri[a], rr[b], ri[b], rr[c], ri[c], rr[d], ri[d], lr, li);
-      cols<M + 4>(rr, ri, lr, li);
-    } else if constexpr (M < NC - 1) {
-      row_elim1<K>(rr[col(M)], ri[col(M)], lr, li);
-      cols<M + 1>(rr, ri, lr, li);
-    }
+  template <int M0, int N>
+  static __device__ __forceinline__ void block(double (&rr)[NC], double (&ri)[NC], double nr, double ni) {
+    double t[N];
+    int z;  // unused: opens the output list
+    if constexpr (N == 3) SPEC_ELIM(3);
+    if constexpr (N == 4) SPEC_ELIM(4);
+    if constexpr (N == 5) SPEC_ELIM(5);
+    if constexpr (N == 6) SPEC_ELIM(6);
+    if constexpr (N == 7) SPEC_ELIM(7);
+    if constexpr (N == 8) SPEC_ELIM(8);
   }
   static __device__ __forceinline__ void run(double (&rr)[NC], double (&ri)[NC], int i, double& pmin) {
     const double px = row_bcast<K>(rr[K]), py = row_bcast<K>(ri[K]);
     const double d = __builtin_fma(px, px, py * py);
-    pmin = __builtin_fmin(pmin, d);
+    asm("v_min_f64 %0, %0, %1" : "+v"(pmin) : "v"(d));  // fmin would first canonicalise both
     double t = __builtin_amdgcn_rcp(d);
     const double e = __builtin_fma(-d, t, 1.0);
     t = __builtin_fma(t, __builtin_fma(e, e, e), t);
     const double ix = px * t, iy = -py * t;
-    const double cr = __builtin_fma(-ri[K], iy, rr[K] * ix), ci = __builtin_fma(ri[K], ix, rr[K] * iy);
     const bool piv = i == K;
-    cols<0>(rr, ri, piv ? 1.0 - ix : cr, piv ? -iy : ci);
-    rr[K] = piv ? ix : -cr;
-    ri[K] = piv ? iy : -ci;
+    const double nr = piv ? ix - 1.0 : __builtin_fma(-rr[K], ix, ri[K] * iy);
+    const double ni = piv ? iy : __builtin_fma(-ri[K], ix, -rr[K] * iy);
+    constexpr int N0 = NC - 1 <= 8 ? NC - 1 : NC / 2;
+    block<0, N0>(rr, ri, nr, ni);
+    if constexpr (N0 < NC - 1) block<N0, NC - 1 - N0>(rr, ri, nr, ni);
+    rr[K] = piv ? ix : nr;
+    ri[K] = ni;
     if constexpr (K + 1 < NC) SpecStep<K + 1, NC>::run(rr, ri, i, pmin);
   }
 };
@@ -223,95 +218,114 @@ __device__ __forceinline__ void spec_sweep(double (&rr)[NC], double (&ri)[NC], i
   SpecStep<0, NC>::run(rr, ri, i, pmin);
 }
 
-// (c_j) += (row K's b_j of this 16-lane row) x for two columns j, complex: the
-// broadcast is the DPP operand of the multiply-add itself, so it costs no move
-// (s_nop and early clobbers as above).
-template <int K>
-__device__ __forceinline__ void row_fmac2(double& c0r, double& c0i, double& c1r, double& c1i, double b0r, double b0i,
-                                          double b1r, double b1i, double xr, double xi) {
-  asm("s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %2, %6, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %3, %7, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, -%5, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %4, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %2, -%7, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %3, %6, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf"
-      : "+&v"(c0r), "+&v"(c0i), "+&v"(c1r), "+&v"(c1i)
-      : "v"(b0r), "v"(b0i), "v"(b1r), "v"(b1i), "v"(xr), "v"(xi), "i"(K));
-}
-// The same for one column.
-template <int K>
-__device__ __forceinline__ void row_fmac1(double& cr, double& ci, double br, double bi, double xr, double xi) {
-  asm("s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, -%3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %2, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
-      : "+&v"(cr), "+&v"(ci)
-      : "v"(br), "v"(bi), "v"(xr), "v"(xi), "i"(K));
-}
-// The same for four columns and rows K, K + 1.
-template <int K>
-__device__ __forceinline__ void row_fmac4(double (&cr)[4], double (&ci)[4], const double* br, const double* bi,
-                                          double xr, double xi, double yr, double yi) {
-#define SPEC_FM(D, S, X, KK) "v_fmac_f64_dpp %" #D ", " #S ", %" #X " row_newbcast:%" #KK " row_mask:0xf bank_mask:0xf\n\t"
-  asm("s_nop 1\n\t"
-      SPEC_FM(0, %8, 16, 20) SPEC_FM(1, %9, 16, 20) SPEC_FM(2, %10, 16, 20) SPEC_FM(3, %11, 16, 20)
-      SPEC_FM(4, %12, 16, 20) SPEC_FM(5, %13, 16, 20) SPEC_FM(6, %14, 16, 20) SPEC_FM(7, %15, 16, 20)
-      SPEC_FM(0, -%12, 17, 20) SPEC_FM(1, -%13, 17, 20) SPEC_FM(2, -%14, 17, 20) SPEC_FM(3, -%15, 17, 20)
-      SPEC_FM(4, %8, 17, 20) SPEC_FM(5, %9, 17, 20) SPEC_FM(6, %10, 17, 20) SPEC_FM(7, %11, 17, 20)
-      SPEC_FM(0, %8, 18, 21) SPEC_FM(1, %9, 18, 21) SPEC_FM(2, %10, 18, 21) SPEC_FM(3, %11, 18, 21)
-      SPEC_FM(4, %12, 18, 21) SPEC_FM(5, %13, 18, 21) SPEC_FM(6, %14, 18, 21) SPEC_FM(7, %15, 18, 21)
-      SPEC_FM(0, -%12, 19, 21) SPEC_FM(1, -%13, 19, 21) SPEC_FM(2, -%14, 19, 21) SPEC_FM(3, -%15, 19, 21)
-      SPEC_FM(4, %8, 19, 21) SPEC_FM(5, %9, 19, 21) SPEC_FM(6, %10, 19, 21) SPEC_FM(7, %11, 19, 21)
-      : "+&v"(cr[0]), "+&v"(cr[1]), "+&v"(cr[2]), "+&v"(cr[3]), "+&v"(ci[0]), "+&v"(ci[1]), "+&v"(ci[2]), "+&v"(ci[3])
-      : "v"(br[0]), "v"(br[1]), "v"(br[2]), "v"(br[3]), "v"(bi[0]), "v"(bi[1]), "v"(bi[2]), "v"(bi[3]),
-        "v"(xr), "v"(xi), "v"(yr), "v"(yi), "i"(K), "i"(K + 1));
-#undef SPEC_FM
-}
+// c_j += (row K's b_j) x + (row K + 1's b_j) y for JB columns (complex), and the
+// same for row K alone.
+#define SPEC_M0(j) "v_fmac_f64_dpp %[c" #j "], %[b" #j "], %[xr]" SPEC_BC(k)
+#define SPEC_M1(j) "v_fmac_f64_dpp %[d" #j "], %[e" #j "], %[xr]" SPEC_BC(k)
+#define SPEC_M2(j) "v_fmac_f64_dpp %[c" #j "], -%[e" #j "], %[xi]" SPEC_BC(k)
+#define SPEC_M3(j) "v_fmac_f64_dpp %[d" #j "], %[b" #j "], %[xi]" SPEC_BC(k)
+#define SPEC_M4(j) "v_fmac_f64_dpp %[c" #j "], %[b" #j "], %[yr]" SPEC_BC(l)
+#define SPEC_M5(j) "v_fmac_f64_dpp %[d" #j "], %[e" #j "], %[yr]" SPEC_BC(l)
+#define SPEC_M6(j) "v_fmac_f64_dpp %[c" #j "], -%[e" #j "], %[yi]" SPEC_BC(l)
+#define SPEC_M7(j) "v_fmac_f64_dpp %[d" #j "], %[b" #j "], %[yi]" SPEC_BC(l)
+#define SPEC_MO(j) [c##j] "+&v"(cr[j]), [d##j] "+&v"(ci[j]),
+#define SPEC_MI(j) [b##j] "v"(br[j]), [e##j] "v"(bi[j]),
+#define SPEC_MAC(N, TWO, Y)                                                                              \
+  asm("s_nop 1\n\t" SPEC_REP##N(SPEC_M0) SPEC_REP##N(SPEC_M1) SPEC_REP##N(SPEC_M2) SPEC_REP##N(SPEC_M3) TWO \
+      : SPEC_REP##N(SPEC_MO) [z] "=&v"(z)                                                                 \
+      : SPEC_REP##N(SPEC_MI)[xr] "v"(xr[K]), [xi] "v"(xi[K]), [k] "i"(K) Y)
+#define SPEC_MAC2(N)                                                                             \
+  SPEC_MAC(N, SPEC_REP##N(SPEC_M4) SPEC_REP##N(SPEC_M5) SPEC_REP##N(SPEC_M6) SPEC_REP##N(SPEC_M7), \
+           SPEC_Y)
+#define SPEC_Y , [yr] "v"(xr[K + 1 < NC ? K + 1 : K]), [yi] "v"(xi[K + 1 < NC ? K + 1 : K]), [l] "i"(K + 1)
+#define SPEC_NOY
+#define SPEC_MACS(N)               \
+  {                                \
+    if constexpr (K + 1 < NC)      \
+      SPEC_MAC2(N);                \
+    else                           \
+      SPEC_MAC(N, "", SPEC_NOY);   \
+  }
 
-// c[j] += sum_k x[k] (b[j] of row k), j = 0 .. JB-1: rows of a matrix product in the row layout.
+// c[j] += sum_k x[k] (b[j] of row k), j = 0 .. JB-1: rows of a matrix product.
 template <int K, int NC, int JB>
 __device__ __forceinline__ void row_mac(double (&cr)[JB], double (&ci)[JB], const double (&xr)[NC],
                                         const double (&xi)[NC], const double* br, const double* bi) {
   if constexpr (K < NC) {
-    if constexpr (JB == 4 && K + 1 < NC) {
-      row_fmac4<K>(cr, ci, br, bi, xr[K], xi[K], xr[K + 1], xi[K + 1]);
-      row_mac<K + 2, NC, JB>(cr, ci, xr, xi, br, bi);
-    } else {
-#pragma unroll
-      for (int j = 0; j + 1 < JB; j += 2)
-        row_fmac2<K>(cr[j], ci[j], cr[j + 1], ci[j + 1], br[j], bi[j], br[j + 1], bi[j + 1], xr[K], xi[K]);
-      if constexpr (JB % 2) row_fmac1<K>(cr[JB - 1], ci[JB - 1], br[JB - 1], bi[JB - 1], xr[K], xi[K]);
-      row_mac<K + 1, NC, JB>(cr, ci, xr, xi, br, bi);
-    }
+    int z;  // unused: keeps the output list's last comma legal
+    if constexpr (JB == 4) SPEC_MACS(4)
+    if constexpr (JB == 5) SPEC_MACS(5)
+    if constexpr (JB == 6) SPEC_MACS(6)
+    if constexpr (JB == 7) SPEC_MACS(7)
+    row_mac<K + 2, NC, JB>(cr, ci, xr, xi, br, bi);
   }
 }
 
-// One column block of V = Gl Sigma' and R = Sigma' + Sigma' V (row layout), R to LDS.
-template <int J0, int NC>
+// Column block of the row-layout products.
+template <int NC>
+constexpr int spec_jb() {
+  return NC == 16 || NC == 8 || NC == 4 ? 4 : NC <= 6 ? NC : NC / 2;
+}
+
+// One column block of V = Gl Sigma' and R = Sigma' + Sigma' V, R to LDS; around it
+// the same columns of the G_loc partial are read (before the block of the previous
+// columns is done with) and w_k Gl is added, see SpecGl.
+template <int J0, int NC, bool WS, class GlT>
 __device__ __forceinline__ void spec_r_blocks(const double (&gr)[NC], const double (&gi)[NC], const double (&sr)[NC],
-                                              const double (&si)[NC], bool valid, int i, lv2d* xb) {
+                                              const double (&si)[NC], bool valid, int i, lv2d* xb, const GlT& gl,
+                                              v2d (&part)[spec_jb<NC>()]) {
   if constexpr (J0 < NC) {
-    constexpr int JB = (NC - J0) < 4 ? (NC - J0) : 4;
-    double vr[JB], vi[JB], rr[JB], ri[JB];
+    constexpr int JB = spec_jb<NC>();
+    if constexpr (WS) {
+      double vr[JB], vi[JB], rr[JB], ri[JB];
 #pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      vr[j] = vi[j] = 0.0;
-      rr[j] = sr[J0 + j];
-      ri[j] = si[J0 + j];
-    }
-    row_mac<0, NC, JB>(vr, vi, gr, gi, sr + J0, si + J0);
-    row_mac<0, NC, JB>(rr, ri, sr, si, vr, vi);
-    if (i < NC) {
+      for (int j = 0; j < JB; ++j) {
+        vr[j] = vi[j] = 0.0;
+        rr[j] = sr[J0 + j];
+        ri[j] = si[J0 + j];
+      }
+      row_mac<0, NC, JB>(vr, vi, gr, gi, sr + J0, si + J0);
+      row_mac<0, NC, JB>(rr, ri, sr, si, vr, vi);
+      if (i < NC) {
 #pragma unroll
-      for (int j = 0; j < JB; ++j) xb[i * NC + J0 + j] = valid ? (v2d){rr[j], ri[j]} : (v2d){0.0, 0.0};
+        for (int j = 0; j < JB; ++j) xb[i * NC + J0 + j] = (v2d){rr[j], ri[j]};
+      }
     }
-    spec_r_blocks<J0 + JB, NC>(gr, gi, sr, si, valid, i, xb);
+    v2d next[JB];
+    if constexpr (J0 + JB < NC) gl.template load<J0 + JB>(next);  // before the stores below: nothing waits for them
+    gl.template store<J0>(part, gr, gi);
+    spec_r_blocks<J0 + JB, NC, WS>(gr, gi, sr, si, valid, i, xb, gl, next);
   }
 }
+
+// This lane's row of the G_loc partial (column stride 4 NC): w_k Gl is written at
+// the tile's first k-point and added after it, a column block at a time.  (Memory
+// atomics instead of the load: 111 cycles per instruction and wavefront here.)
+template <int NC>
+struct SpecGl {
+  gv2d* p;
+  double wk;
+  bool put, more;  // this lane's row exists; there is something to add to
+  template <int J0>
+  __device__ __forceinline__ void load(v2d (&part)[spec_jb<NC>()]) const {
+    if (more) {
+#pragma unroll
+      for (int j = 0; j < spec_jb<NC>(); ++j) part[j] = p[(J0 + j) * 4 * NC];
+    } else {
+#pragma unroll
+      for (int j = 0; j < spec_jb<NC>(); ++j) part[j] = (v2d){0.0, 0.0};
+    }
+  }
+  template <int J0>
+  __device__ __forceinline__ void store(const v2d (&part)[spec_jb<NC>()], const double (&gr)[NC],
+                                        const double (&gi)[NC]) const {
+    if (put) {
+#pragma unroll
+      for (int j = 0; j < spec_jb<NC>(); ++j)
+        p[(J0 + j) * 4 * NC] = (v2d){__builtin_fma(wk, gr[J0 + j], part[j].x), __builtin_fma(wk, gi[J0 + j], part[j].y)};
+    }
+  }
+};
 
 // WS: the sums are wanted (N(k)); else G_loc only.
 template <int NBP, int NC, bool WS>
@@ -458,19 +472,23 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
           if (4 * c >= nb) return;
           if constexpr (c + 1 < NBP / 4) fetch(c + 1, (c + 1) & 1);
           __builtin_amdgcn_sched_barrier(0);
+          // all vector work of the chunk before its products: the vector and matrix
+          // units do not run FP64 together, and each change from one to the other
+          // drains the pipe (70 cycles measured)
+          double pv[TPW];
 #pragma unroll
           for (int m = 0; m < TPW; ++m) {
-            double pv;
             if constexpr (Dm::PREG)
-              pv = p[m][c];
+              pv[m] = p[m][c];
             else
-              pv = __builtin_fma(x[c & 1][m].x, y[c & 1][m].x, x[c & 1][m].y * y[c & 1][m].y);
-            if constexpr (SPLIT) {
-              xa[m][0] = mma((w & 1) ? d[c & 1].y : d[c & 1].x, pv, xa[m][0]);
-            } else {
-              xa[m][0] = mma(d[c & 1].x, pv, xa[m][0]);
-              xa[m][1] = mma(d[c & 1].y, pv, xa[m][1]);
-            }
+              pv[m] = __builtin_fma(x[c & 1][m].x, y[c & 1][m].x, x[c & 1][m].y * y[c & 1][m].y);
+          }
+          const double dx = SPLIT && (w & 1) ? d[c & 1].y : d[c & 1].x;
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int m = 0; m < TPW; ++m) {
+            xa[m][0] = mma(dx, pv[m], xa[m][0]);
+            if constexpr (!SPLIT) xa[m][1] = mma(d[c & 1].y, pv[m], xa[m][1]);
           }
         });
         __syncthreads();  // the previous group's stage C has read xr
@@ -536,31 +554,20 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
           ri[j] -= si[j];
         }
         spec_sweep<NC>(rr, ri, i, pmin);
-        // w_k Gl into this lane's row of the G_loc partial (column stride 4 NC):
-        // written at the tile's first k-point, then added with memory atomics.  No
-        // other work-group touches the address, so the order of the additions is
-        // the k order and the sum reproducible; unlike a load and a store, the
-        // atomics hold no registers and nothing waits for them.
-        if (want_x && valid && i < NC) {
-          gdouble* gp = (gdouble*)a.xs +
-                        2 * (((int64_t)(a.ktile_base + ktile) * n4_all + (ng >> 2) + w) * (4 * NC * NC) + (nl & 3) * NC + i);
-          if (kk == kk0) {
-#pragma unroll
-            for (int j = 0; j < NC; ++j) *(gv2d*)(gp + 8 * NC * j) = (v2d){wk * rr[j], wk * ri[j]};
-          } else {
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              spec_atomic_add(gp + 8 * NC * j, wk * rr[j]);
-              spec_atomic_add(gp + 8 * NC * j + 1, wk * ri[j]);
-            }
-          }
-        }
+        SpecGl<NC> gl;
+        gl.p = (gv2d*)a.xs + ((int64_t)(a.ktile_base + ktile) * n4_all + min((ng >> 2) + w, n4_all - 1)) * (4 * NC * NC) +
+               (nl & 3) * NC + ic;
+        gl.wk = wk;
+        gl.put = want_x && valid && i < NC;
+        gl.more = want_x && kk != kk0;
+        v2d part[spec_jb<NC>()];
+        gl.template load<0>(part);
         double chk = 0.0;
 #pragma unroll
         for (int j = 0; j < NC; ++j) chk += rr[j] + ri[j];
         if (i < NC && !__builtin_isfinite(chk)) nonfinite = 1;
         wave_sync();
-        if constexpr (WS) spec_r_blocks<0, NC>(rr, ri, sr, si, valid, i, xb);
+        spec_r_blocks<0, NC, WS>(rr, ri, sr, si, valid, i, xb, gl, part);
         wave_sync();
         if constexpr (WS) {
           // R -> (R + R^dag, i (R - R^dag)) as Hermitian pairs, in place: lane i takes the
@@ -582,6 +589,10 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
               if (r) xb[max(i, j) * NC + min(i, j)] = (v2d){u[r].y - v[r].y, u[r].x - v[r].x};
               xb[min(i, j) * NC + max(i, j)] = (v2d){u[r].x + v[r].x, -(u[r].y + v[r].y)};
             }
+            if (!valid) {  // frequencies past the tile add nothing
+#pragma unroll
+              for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){0.0, 0.0};
+            }
           }
         } else {
           if (ng + 16 < n1) fill_d(ng + 16, sh.dt[cur ^ 1], false);
@@ -599,34 +610,43 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
           d1[r] = spec_lds(&sh.dt[cur][q * DS + min(row >> 1, NBP - 1)]);
           d2[r] = spec_lds(&sh.dt[cur][q * DS + min((row + 1) >> 1, NBP - 1)]);
         }
-        // operands one chunk of four frequencies ahead, as in stage A
-        v2d h[2][CT], x[2][RT], y[2][RT];
+        // row factors of all 16 frequencies first, then products only; operands one
+        // chunk of four frequencies ahead
+        v2d h[2][CT];
         auto fetch = [&](int c, int s) {
-#pragma unroll
-          for (int r = 0; r < RT; ++r) {
-            x[s][r] = d1[r][4 * c * DS];
-            y[s][r] = d2[r][4 * c * DS];
-          }
 #pragma unroll
           for (int t = 0; t < CT; ++t) h[s][t] = xc[4 * c * NP + 16 * WC * t];
         };
-        fetch(0, 0);
+        double fr[4][RT], fi[4][RT];
+        {
+          v2d x[4][RT], y[4][RT];
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+              x[c][r] = d1[r][4 * c * DS];
+              y[c][r] = d2[r][4 * c * DS];
+            }
+          fetch(0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+              fr[c][r] = x[c][r].x * y[c][r].x - x[c][r].y * y[c][r].y;
+              fi[c][r] = x[c][r].x * y[c][r].y + x[c][r].y * y[c][r].x;
+            }
+        }
         spec_for<0, 4>([&](auto ci) {
           constexpr int c = decltype(ci)::value;
           if constexpr (c < 3) fetch(c + 1, (c + 1) & 1);
           __builtin_amdgcn_sched_barrier(0);
-          double fr[RT], fi[RT];
-#pragma unroll
-          for (int r = 0; r < RT; ++r) {
-            fr[r] = x[c & 1][r].x * y[c & 1][r].x - x[c & 1][r].y * y[c & 1][r].y;
-            fi[r] = x[c & 1][r].x * y[c & 1][r].y + x[c & 1][r].y * y[c & 1][r].x;
-          }
 #pragma unroll
           for (int t = 0; t < CT; ++t) {
 #pragma unroll
-            for (int r = 0; r < RT; ++r) acc[r][t] = mma(fr[r], h[c & 1][t].x, acc[r][t]);
+            for (int r = 0; r < RT; ++r) acc[r][t] = mma(fr[c][r], h[c & 1][t].x, acc[r][t]);
 #pragma unroll
-            for (int r = 0; r < RT; ++r) acc[r][t] = mma(fi[r], h[c & 1][t].y, acc[r][t]);
+            for (int r = 0; r < RT; ++r) acc[r][t] = mma(fi[c][r], h[c & 1][t].y, acc[r][t]);
           }
         });
       }
