@@ -37,7 +37,10 @@ namespace dmft {
 namespace {
 
 constexpr int kMaxM = 80;         // largest pseudo-Hamiltonian (nb + np)
+constexpr size_t kCuLds = 160 * 1024;  // LDS of a CU
 constexpr int kDosThreads = 256;
+constexpr int kDosTiles = 2;      // 16-energy tiles per work-group of the DOS sum
+typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kDosChunk = 512;    // eigenpairs per slice of the DOS sum
 constexpr int kMaxSlices = 128;
 
@@ -83,14 +86,12 @@ __device__ __forceinline__ double pole_block_sum(double v, double* red) {
   return r;
 }
 
-// n_F(x) = 1 / (exp(beta x) + 1) without overflow.
+// n_F(x) = 1 / (exp(beta x) + 1) without overflow (one exponential and one division
+// for both signs: lanes of a wavefront hold levels on either side).
 __device__ __forceinline__ double fermi(double x, double beta) {
   const double y = beta * x;
-  if (y > 0.0) {
-    const double e = exp(-y);
-    return e / (1.0 + e);
-  }
-  return 1.0 / (1.0 + exp(y));
+  const double e = exp(-fabs(y));
+  return (y > 0.0 ? e : 1.0) / (1.0 + e);
 }
 
 // Weight of one level at x in the positive-frequency Matsubara sum truncated at
@@ -107,7 +108,7 @@ __device__ double truncated_weight(double x, double beta, int nw) {
   return 0.5 - beta * x / 4.0 + 2.0 * s / beta;
 }
 
-// One pair's rotation of a Jacobi step, read by the update pass as two 16-byte words.
+// One pair's rotation of a Jacobi step, read by the update passes as two 16-byte words.
 struct __align__(16) JRot {
   double c, sr, si;  // U = [[c, g], [-conj(g), c]], g = sr + i si
   int pq;            // p | q << 16
@@ -118,7 +119,7 @@ struct __align__(16) JRot {
 // (r, c), r <= c, of an mq x mq matrix sits at r mq - r (r - 1) / 2 + c - r;
 // (c, r) is its conjugate.  hget/hput pick the stored element and conjugate by
 // select, so lanes reading either triangle do not diverge.
-__device__ __forceinline__ int up_idx(int r, int c, int mq) { return r * mq - ((r * (r - 1)) >> 1) + (c - r); }
+__device__ __forceinline__ int up_idx(int r, int c, int mq) { return (__mul24(r, 2 * mq - 1 - r) >> 1) + c; }
 __device__ __forceinline__ double2 hget(const double2* A, int r, int c, int mq) {
   const double2 v = A[up_idx(min(r, c), max(r, c), mq)];
   return pz(v.x, r <= c ? v.y : -v.y);
@@ -132,17 +133,22 @@ __device__ __forceinline__ void k_window(const PoleArgs& a, int k, int& nb, int6
   ob = a.nb_uniform > 0 ? (int64_t)k * nb : a.off_b[k];
 }
 
-// NT threads per work-group (256, 512 or 1024, chosen at launch from the
-// number of update items per step).
+// NT threads per work-group (256, 512 or 1024, see launch_pole_eig).  Wavefront 0
+// computes a step's rotations (and writes the pairs' own 2x2 blocks, which nobody
+// else touches meanwhile) while the others apply the previous step's to the
+// eigenvector rows; then all of them apply the step to the other blocks of the
+// matrix.  The rotations are double-buffered by step parity.  Bound by LDS: a step
+// reads and writes the stored triangle and the eigenvector rows once each (160 KB at
+// 62 x 62 with 48 physical rows, 1250 cycles), and by the latency of the rotation
+// chain, which is hidden behind the eigenvector pass of this work-group and behind
+// the second work-group of the CU: nothing but the two matrices and the rotations is
+// kept in LDS, so that two fit at that size.  512 such matrices: 1993 us with the
+// rotations, both updates and two barriers in sequence and one work-group of 1024
+// threads per CU, 1140 us now.
 template <int NT>
 __global__ void __launch_bounds__(NT) pole_eig_kernel(PoleArgs a) {
   constexpr int kEigThreads = NT;
   extern __shared__ double2 lds[];
-  __shared__ JRot s_r[kMaxM / 2];
-  __shared__ double s_dp[kMaxM / 2], s_dq[kMaxM / 2];
-  __shared__ int s_inv[kMaxM], s_any[2];
-  __shared__ double s_lam[kMaxM];
-  __shared__ double red[kEigThreads];
   const int k = blockIdx.x, t = threadIdx.x;
   int nb;
   int64_t ob;
@@ -152,6 +158,8 @@ __global__ void __launch_bounds__(NT) pole_eig_kernel(PoleArgs a) {
   const int ldv = nb + 1;
   double2* A = lds;                          // packed upper triangle, mq (mq + 1) / 2
   double2* VT = lds + mq * (mq + 1) / 2;     // mq x ldv: row l = physical components of eigenvector l
+  JRot* s_r = reinterpret_cast<JRot*>(VT + mq * ldv);  // [2][P]
+  int* s_any = reinterpret_cast<int*>(s_r + 2 * P);    // [2]
   const double2* S = reinterpret_cast<const double2*>(a.proj) + ob * nc;
   const double* E = a.eps + ob;
   const double2* SI = reinterpret_cast<const double2*>(a.sigma_inf);
@@ -189,36 +197,59 @@ __global__ void __launch_bounds__(NT) pole_eig_kernel(PoleArgs a) {
   if (m & 1)  // odd size: one decoupled zero row/column completes the pairing
     for (int j = t; j < mq; j += kEigThreads) A[up_idx(j, m, mq)] = pz(0.0, 0.0);
   __syncthreads();
-  for (int idx = t; idx < mq * nb; idx += kEigThreads) {
-    const int l = idx / nb, i = idx - l * nb;
-    VT[l * ldv + i] = pz(l == i ? 1.0 : 0.0, 0.0);
-  }
   double ss = 0.0;
   for (int idx = t; idx < mq * mq; idx += kEigThreads) {
     const int i = idx / mq, j = idx - i * mq;
     if (i <= j) ss += (i == j ? 1.0 : 2.0) * pabs2(A[up_idx(i, j, mq)]);
   }
-  const double tol = 1e-17 * sqrt(pole_block_sum<kEigThreads>(ss, red));
+  // the partial sums take what follows the triangle (pole_eig_lds_bytes leaves room for them)
+  const double tol = 1e-17 * sqrt(pole_block_sum<kEigThreads>(ss, reinterpret_cast<double*>(VT)));
+  for (int idx = t; idx < mq * nb; idx += kEigThreads) {
+    const int l = idx / nb, i = idx - l * nb;
+    VT[l * ldv + i] = pz(l == i ? 1.0 : 0.0, 0.0);
+  }
+  __syncthreads();
 
-  // item walks of the two update passes without divisions: item b = t + 256 j
-  // is (b / P, b % P) in the block pass and (b / nb, b % nb) in the vector pass
-  const int bI0 = t / P, bJ0 = t - bI0 * P, bdI = kEigThreads / P, bdJ = kEigThreads - bdI * P;
-  const int vJ0 = t / nb, vi0 = t - vJ0 * nb, vdJ = kEigThreads / nb, vdi = kEigThreads - vdJ * nb;
-  int sweep = 0, converged = 0;
+  // item walks of the update passes without divisions.  Matrix pass: item b = t + NT j
+  // joins pairs I = b % P and (I + 1 + b / P) % P, each unordered two once; vector pass
+  // (all wavefronts but the first): (b / nb, b % nb), b = t - 64 + (NT - 64) j.
+  const int nblk = P * (P - 1) / 2;
+  const int bd0 = t / P, bI0 = t - bd0 * P, bdd = kEigThreads / P, bdI = kEigThreads - bdd * P;
+  auto vectors = [&](const JRot* rs, int t0, int nt) {
+    int J = t0 / nb, i = t0 - J * nb;
+    const int dJ = nt / nb, di = nt - dJ * nb;
+    while (J < P) {
+      const JRot R = rs[J];
+      if (R.rot) {  // eigenvector columns (rows of VT): p' = c p - conj(g) q, q' = g p + c q
+        const int p = R.pq & 0xffff, q = R.pq >> 16;
+        const double2 g = pz(R.sr, R.si);
+        const double2 vp = VT[p * ldv + i], vq = VT[q * ldv + i];
+        VT[p * ldv + i] = psub(pscal(R.c, vp), pmul(pconj(g), vq));
+        VT[q * ldv + i] = padd(pmul(g, vp), pscal(R.c, vq));
+      }
+      J += dJ;
+      i += di;
+      if (i >= nb) {
+        i -= nb;
+        ++J;
+      }
+    }
+  };
+  // round-robin: position 0 holds index 0, position j >= 1 index 1 + (j - 1 + s) mod (mq - 1);
+  // pair t joins positions t and mq - 1 - t.  Both indices of the next step:
+  int pn = t, qn = mq - 1 - t;
+  int sweep = 0, converged = 0, parity = 0, pending = 0;
   while (sweep < a.max_sweeps) {
     ++sweep;
     int any = 0;
-    for (int s = 0; s < mq - 1; ++s) {
-      // rotation parameters: pairs live in wave 0 (P <= 32); its ballot tells
-      // every wave whether the step rotates (flag double-buffered by step parity,
-      // so a wave still reading step s never sees step s + 1's flag)
+    for (int s = 0; s < mq - 1; ++s, parity ^= 1) {
+      // pairs live in wave 0 (P <= 40); its ballot tells every wave whether the step rotates
       if (t < 64) {
         int rot = 0;
         if (t < P) {
-          // round-robin: position 0 holds index 0, position j >= 1 index 1 + (j - 1 + s) mod (mq - 1);
-          // pair t joins positions t and mq - 1 - t
-          const int p = t == 0 ? 0 : 1 + (t - 1 + s) % (mq - 1);
-          const int q = 1 + (mq - 2 - t + s) % (mq - 1);
+          const int p = pn, q = qn;
+          if (t > 0) pn = pn == mq - 1 ? 1 : pn + 1;
+          qn = qn == mq - 1 ? 1 : qn + 1;
           const double2 apq = hget(A, p, q, mq);
           const double app = A[up_idx(p, p, mq)].x, aqq = A[up_idx(q, q, mq)].x;
           const double r = sqrt(pabs2(apq));
@@ -241,75 +272,58 @@ __global__ void __launch_bounds__(NT) pole_eig_kernel(PoleArgs a) {
             const double sn = tt * R.c * ir;
             R.sr = sn * apq.x;
             R.si = sn * apq.y;
-            s_dp[t] = app - tt * r;
-            s_dq[t] = aqq + tt * r;
+            A[up_idx(p, p, mq)] = pz(app - tt * r, 0.0);
+            A[up_idx(q, q, mq)] = pz(aqq + tt * r, 0.0);
+            hput(A, p, q, mq, pz(0.0, 0.0));
             rot = 1;
           }
           R.rot = rot;
-          s_r[t] = R;
+          s_r[parity * P + t] = R;
         }
         const unsigned long long bal = __ballot(rot);
-        if (t == 0) s_any[s & 1] = bal != 0ull;
+        if (t == 0) s_any[parity] = bal != 0ull;
+      } else if (pending) {
+        vectors(s_r + (parity ^ 1) * P, t - 64, kEigThreads - 64);
       }
       __syncthreads();
-      if (!s_any[s & 1]) continue;
+      pending = s_any[parity];
+      if (!pending) continue;
       any = 1;
-      // A <- U^dag A U, one 2x2 block (pair I rows, pair J columns) per item, I <= J
-      for (int I = bI0, J = bJ0; I < P;) {
-        if (I <= J) {
-          const JRot R1 = s_r[I], R2 = s_r[J];
-          if (R1.rot | R2.rot) {
-            const int p1 = R1.pq & 0xffff, q1 = R1.pq >> 16;
-            if (I == J) {
-              A[up_idx(p1, p1, mq)] = pz(s_dp[I], 0.0);
-              A[up_idx(q1, q1, mq)] = pz(s_dq[I], 0.0);
-              hput(A, p1, q1, mq, pz(0.0, 0.0));
-            } else {
-              const int p2 = R2.pq & 0xffff, q2 = R2.pq >> 16;
-              const double c1 = R1.c, c2 = R2.c;
-              const double2 g1 = pz(R1.sr, R1.si), g2 = pz(R2.sr, R2.si);
-              const double2 x11 = hget(A, p1, p2, mq), x12 = hget(A, p1, q2, mq);
-              const double2 x21 = hget(A, q1, p2, mq), x22 = hget(A, q1, q2, mq);
-              // rows: p' = c p - g q, q' = conj(g) p + c q
-              const double2 y11 = psub(pscal(c1, x11), pmul(g1, x21));
-              const double2 y12 = psub(pscal(c1, x12), pmul(g1, x22));
-              const double2 y21 = padd(pmul(pconj(g1), x11), pscal(c1, x21));
-              const double2 y22 = padd(pmul(pconj(g1), x12), pscal(c1, x22));
-              // columns: p' = c p - conj(g) q, q' = g p + c q
-              const double2 z11 = psub(pscal(c2, y11), pmul(pconj(g2), y12));
-              const double2 z12 = padd(pmul(g2, y11), pscal(c2, y12));
-              const double2 z21 = psub(pscal(c2, y21), pmul(pconj(g2), y22));
-              const double2 z22 = padd(pmul(g2, y21), pscal(c2, y22));
-              // each mirrored pair has one slot, written by this block only
-              hput(A, p1, p2, mq, z11);
-              hput(A, p1, q2, mq, z12);
-              hput(A, q1, p2, mq, z21);
-              hput(A, q1, q2, mq, z22);
-            }
-          }
+      const JRot* rs = s_r + parity * P;
+      // A <- U^dag A U, one 2x2 block (pair I rows, pair J columns) per item, I < J
+      for (int b = t, d = bd0, I0 = bI0; b < nblk; b += kEigThreads) {
+        int J0 = I0 + 1 + d;
+        if (J0 >= P) J0 -= P;
+        const int I = min(I0, J0), J = max(I0, J0);
+        const JRot R1 = rs[I], R2 = rs[J];
+        if (R1.rot | R2.rot) {
+          const int p1 = R1.pq & 0xffff, q1 = R1.pq >> 16;
+          const int p2 = R2.pq & 0xffff, q2 = R2.pq >> 16;
+          const double c1 = R1.c, c2 = R2.c;
+          const double2 g1 = pz(R1.sr, R1.si), g2 = pz(R2.sr, R2.si);
+          const double2 x11 = hget(A, p1, p2, mq), x12 = hget(A, p1, q2, mq);
+          const double2 x21 = hget(A, q1, p2, mq), x22 = hget(A, q1, q2, mq);
+          // rows: p' = c p - g q, q' = conj(g) p + c q
+          const double2 y11 = psub(pscal(c1, x11), pmul(g1, x21));
+          const double2 y12 = psub(pscal(c1, x12), pmul(g1, x22));
+          const double2 y21 = padd(pmul(pconj(g1), x11), pscal(c1, x21));
+          const double2 y22 = padd(pmul(pconj(g1), x12), pscal(c1, x22));
+          // columns: p' = c p - conj(g) q, q' = g p + c q
+          const double2 z11 = psub(pscal(c2, y11), pmul(pconj(g2), y12));
+          const double2 z12 = padd(pmul(g2, y11), pscal(c2, y12));
+          const double2 z21 = psub(pscal(c2, y21), pmul(pconj(g2), y22));
+          const double2 z22 = padd(pmul(g2, y21), pscal(c2, y22));
+          // each mirrored pair has one slot, written by this block only
+          hput(A, p1, p2, mq, z11);
+          hput(A, p1, q2, mq, z12);
+          hput(A, q1, p2, mq, z21);
+          hput(A, q1, q2, mq, z22);
         }
-        I += bdI;
-        J += bdJ;
-        if (J >= P) {
-          J -= P;
-          ++I;
-        }
-      }
-      // eigenvector columns (rows of VT): p' = c p - conj(g) q, q' = g p + c q
-      for (int J = vJ0, i = vi0; J < P;) {
-        const JRot R = s_r[J];
-        if (R.rot) {
-          const int p = R.pq & 0xffff, q = R.pq >> 16;
-          const double2 g = pz(R.sr, R.si);
-          const double2 vp = VT[p * ldv + i], vq = VT[q * ldv + i];
-          VT[p * ldv + i] = psub(pscal(R.c, vp), pmul(pconj(g), vq));
-          VT[q * ldv + i] = padd(pmul(g, vp), pscal(R.c, vq));
-        }
-        J += vdJ;
-        i += vdi;
-        if (i >= nb) {
-          i -= nb;
-          ++J;
+        I0 += bdI;
+        d += bdd;
+        if (I0 >= P) {
+          I0 -= P;
+          ++d;
         }
       }
       __syncthreads();
@@ -319,13 +333,20 @@ __global__ void __launch_bounds__(NT) pole_eig_kernel(PoleArgs a) {
       break;
     }
   }
+  if (pending) vectors(s_r + (parity ^ 1) * P, t, kEigThreads);  // the last step's, where it rotated
+  const double lam_t = t < m ? A[up_idx(t, t, mq)].x : 0.0;
+  __syncthreads();
+  double* s_lam = reinterpret_cast<double*>(s_r);      // [mq], over the rotations
+  int* s_inv = reinterpret_cast<int*>(s_lam + mq);     // [mq]
 
   // eigenvalues in ascending order (ties by index)
-  if (t < m) s_lam[t] = A[up_idx(t, t, mq)].x;
-  if (t < kMaxM) s_inv[t] = t < m ? t : 0;
+  if (t < m) {
+    s_lam[t] = lam_t;
+    s_inv[t] = t;
+  }
   __syncthreads();
   if (t < m) {
-    const double lt = s_lam[t];
+    const double lt = lam_t;
     int r = 0;
     for (int j = 0; j < m; ++j) {
       const double lj = s_lam[j];
@@ -423,18 +444,46 @@ __global__ void __launch_bounds__(256) pole_density_kernel(PoleArgs a, double mu
   }
 }
 
+// The search of mu, one work-group (a pass waits for the one before), bound by one CU's
+// rate for the exponentials and divisions and by the latency of the loads, of which each
+// thread has 3 x 4 in flight.  31744 levels: 161 us with both branches of the Fermi
+// function taken and an index division per level and pass, 115 us now.
 __global__ void __launch_bounds__(1024) pole_mu_kernel(PoleArgs a, double n_target, double tol, int method,
                                                        double lo, double hi, double mu0, int max_iter, double* res) {
   __shared__ double red[1024];
   const int64_t total = (int64_t)a.nk * a.mp;
+  const int dk = 1024 / a.mp, dr = 1024 - dk * a.mp;  // k-point and level of idx + 1024, without a division
   auto eval = [&](double mu, double& nv, double& dv) {
     double sn = 0.0, sd = 0.0;
-    for (int64_t idx = threadIdx.x; idx < total; idx += 1024) {
-      const int kk = (int)(idx / a.mp);
-      const double w = a.wk[kk] * a.wphys[idx];
-      const double f = fermi(a.evals[idx] - mu, a.beta);
-      sn += w * f;
-      sd += w * a.beta * f * (1.0 - f);
+    int k = threadIdx.x / a.mp, r = threadIdx.x - k * a.mp;
+    for (int64_t idx = threadIdx.x; idx < total;) {
+      double lam[4], w[4], wk[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j, idx += 1024) {
+        const bool in = idx < total;
+        lam[j] = a.evals[in ? idx : 0];
+        w[j] = a.wphys[in ? idx : 0];
+        wk[j] = a.wk[in ? k : 0];
+        if (!in) wk[j] = w[j] = 0.0;
+        k += dk;
+        r += dr;
+        if (r >= a.mp) {
+          r -= a.mp;
+          ++k;
+        }
+      }
+#pragma unroll 1
+      for (int j = 0; j < 4; ++j) {
+        const double f = fermi(lam[0] - mu, a.beta), wf = wk[0] * w[0];
+        sn += wf * f;
+        sd += wf * a.beta * f * (1.0 - f);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          lam[u] = lam[u + 1];
+          w[u] = w[u + 1];
+          wk[u] = wk[u + 1];
+        }
+      }
     }
     nv = pole_block_sum<1024>(sn, red);
     dv = pole_block_sum<1024>(sd, red);
@@ -489,45 +538,74 @@ __global__ void __launch_bounds__(1024) pole_mu_kernel(PoleArgs a, double n_targ
   }
 }
 
+// DOS and PDOS of 16 kDosTiles energies over one slice of the levels: PDOS is the matrix
+// product L W of the Lorentzians L(e, l) and the orbital weights, on 16x16x4 matrix
+// cores with each lane's one Lorentzian (e = its row, l = its quarter) as the A operand;
+// the total is summed beside it on the vector units.  The slice's levels are dealt to the
+// four wavefronts and summed in wavefront order.  Bound by the Lorentzians' divisions and
+// the products (about 30 ns each per 64 values and SIMD).  501 energies, 31744 levels, 14
+// orbitals: 319 us with an energy per thread (two rows of work-groups, 16 predicated
+// sums each), 44 us now.
 __global__ void __launch_bounds__(kDosThreads) pole_dos_kernel(PoleArgs a, double mu, double eta, double e_min,
                                                                double de, int ne, int nslices, double* part) {
-  __shared__ double s_lam[kDosThreads], s_w[kDosThreads], s_wo[kDosThreads * 16];
-  const int t = threadIdx.x, e = blockIdx.x * kDosThreads + t, slice = blockIdx.y;
+  __shared__ double s_lam[kDosThreads], s_w[kDosThreads], s_wo[kDosThreads * 17];
+  __shared__ double s_sum[4][kDosTiles][17 * 16];
+  const int t = threadIdx.x, q = (t >> 4) & 3, c16 = t & 15, slice = blockIdx.y;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int e0 = blockIdx.x * 16 * kDosTiles;
   const int nc = a.nc;
   const int64_t total = (int64_t)a.nk * a.mp;
   const int64_t per = (total + nslices - 1) / nslices;
   const int64_t s0 = (int64_t)slice * per, s1 = s0 + per < total ? s0 + per : total;
-  const double ee = e_min + (double)e * de + mu;
   const double scale = eta / M_PI, eta2 = eta * eta;
-  double d = 0.0, pd[16];
+  double ee[kDosTiles], d[kDosTiles];
+  v4d pd[kDosTiles];
 #pragma unroll
-  for (int al = 0; al < 16; ++al) pd[al] = 0.0;
+  for (int m = 0; m < kDosTiles; ++m) {
+    ee[m] = e_min + (double)(e0 + 16 * m + c16) * de + mu;
+    d[m] = 0.0;
+    pd[m] = (v4d){0.0, 0.0, 0.0, 0.0};
+  }
   for (int64_t c0 = s0; c0 < s1; c0 += kDosThreads) {
     __syncthreads();
     const int64_t idx = c0 + t;
-    if (idx < s1) {
-      const double w = a.wk[idx / a.mp];
-      s_lam[t] = a.evals[idx];
-      s_w[t] = w * a.wphys[idx];
-      for (int al = 0; al < nc; ++al) s_wo[t * 16 + al] = a.worb ? w * a.worb[idx * nc + al] : 0.0;
-    }
+    const bool in = idx < s1;  // levels past the slice weigh nothing (at the first one's energy)
+    const int64_t ix = in ? idx : s0;
+    const double w = in ? a.wk[ix / a.mp] : 0.0;
+    s_lam[t] = a.evals[ix];
+    s_w[t] = in ? w * a.wphys[ix] : 0.0;
+#pragma unroll
+    for (int al = 0; al < 16; ++al) s_wo[t * 17 + al] = (in && a.worb && al < nc) ? w * a.worb[ix * nc + al] : 0.0;
     __syncthreads();
     const int cnt = (int)(s1 - c0 < kDosThreads ? s1 - c0 : kDosThreads);
-    for (int j = 0; j < cnt; ++j) {
-      const double x = ee - s_lam[j];
-      const double L = scale / (x * x + eta2);
-      d += s_w[j] * L;
+    const int j1 = min(64 * wave + 64, cnt);
+    for (int j = 64 * wave + q; j - q < j1; j += 4) {
+      const double lam = s_lam[j], wt = s_w[j], wo = s_wo[j * 17 + c16];
 #pragma unroll
-      for (int al = 0; al < 16; ++al)
-        if (al < nc) pd[al] += s_wo[j * 16 + al] * L;
+      for (int m = 0; m < kDosTiles; ++m) {
+        const double x = ee[m] - lam;
+        const double L = j < cnt ? scale / (x * x + eta2) : 0.0;
+        d[m] = __builtin_fma(wt, L, d[m]);
+        pd[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(L, wo, pd[m], 0, 0, 0);
+      }
     }
   }
-  if (e < ne) {
-    double* o = part + ((int64_t)slice * ne + e) * (1 + nc);
-    o[0] = d;
 #pragma unroll
-    for (int al = 0; al < 16; ++al)
-      if (al < nc) o[1 + al] = pd[al];
+  for (int m = 0; m < kDosTiles; ++m) {
+    d[m] += __shfl_xor(d[m], 16);
+    d[m] += __shfl_xor(d[m], 32);
+    if (q == 0) s_sum[wave][m][c16 * 17] = d[m];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_sum[wave][m][(4 * i + q) * 17 + 1 + c16] = pd[m][i];
+  }
+  __syncthreads();
+  for (int idx = t; idx < kDosTiles * 16 * (1 + nc); idx += kDosThreads) {
+    const int el = idx / (1 + nc), c = idx - el * (1 + nc), e = e0 + el;
+    if (e >= ne) break;
+    double v = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v += s_sum[u][el >> 4][(el & 15) * 17 + c];
+    part[((int64_t)slice * ne + e) * (1 + nc) + c] = v;
   }
 }
 
@@ -536,7 +614,13 @@ __global__ void pole_dos_reduce_kernel(int ne, int nc, int nslices, const double
   const int64_t n = (int64_t)ne * (1 + nc);
   if (idx >= n) return;
   double s = 0.0;
-  for (int sl = 0; sl < nslices; ++sl) s += part[(int64_t)sl * n + idx];
+  for (int s0 = 0; s0 < nslices; s0 += 16) {  // 16 loads in flight: the sum is bound by their latency
+    double v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = part[(int64_t)min(s0 + j, nslices - 1) * n + idx];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s += s0 + j < nslices ? v[j] : 0.0;
+  }
   const int e = (int)(idx / (1 + nc)), c = (int)(idx - (int64_t)e * (1 + nc));
   if (c == 0) dos[e] = s;
   else if (pdos) pdos[(int64_t)e * nc + c - 1] = s;
@@ -619,7 +703,9 @@ hipError_t allow_lds(const void* fn, size_t bytes) {
 
 size_t pole_eig_lds_bytes(int nb, int np) {
   const int m = nb + np, mq = m + (m & 1);
-  return (size_t)(mq * (mq + 1) / 2 + mq * (nb + 1)) * 16;
+  // matrix; eigenvector rows, two steps' rotations and flags (or the partial sums of the norm)
+  const size_t rows = (size_t)mq * (nb + 1) * 16 + (size_t)mq * sizeof(JRot) + 16;
+  return (size_t)(mq * (mq + 1) / 2) * 16 + (rows > 8192 ? rows : 8192);
 }
 
 template <int NT>
@@ -631,11 +717,13 @@ hipError_t launch_pole_eig_nt(const PoleArgs& a, size_t lds_bytes, hipStream_t s
 }
 
 hipError_t launch_pole_eig(const PoleArgs& a, size_t lds_bytes, hipStream_t s) {
-  // update items of one step at the largest size: 2x2 blocks I <= J and eigenvector pairs
-  const int m = a.nb_max + a.np, mq = m + (m & 1), P = mq / 2;
+  // eigenvector items of one step at the largest size, and what fits: where two
+  // work-groups share a CU, 512 threads each overlap best (512 of 62 x 62: 1140 us, and
+  // 1993 with the CU to itself); a larger matrix has it to itself and takes 1024
+  const int m = a.nb_max + a.np, P = (m + 1) / 2;
   const int items = P * (P + 1) / 2 + P * a.nb_max;
   if (items <= 512) return launch_pole_eig_nt<256>(a, lds_bytes, s);
-  if (items <= 1536) return launch_pole_eig_nt<512>(a, lds_bytes, s);
+  if (items <= 1536 || 2 * lds_bytes <= kCuLds) return launch_pole_eig_nt<512>(a, lds_bytes, s);
   return launch_pole_eig_nt<1024>(a, lds_bytes, s);
 }
 
@@ -665,7 +753,7 @@ hipError_t launch_pole_dos(const PoleArgs& a, double mu, double eta, double e_mi
                            double* part, double* dos, double* pdos, hipStream_t s) {
   const int ns = pole_dos_kslices(a.nk, a.mp);
   const double de = ne > 1 ? (e_max - e_min) / (double)(ne - 1) : 0.0;
-  hipLaunchKernelGGL(pole_dos_kernel, dim3((ne + kDosThreads - 1) / kDosThreads, ns), dim3(kDosThreads), 0, s, a,
+  hipLaunchKernelGGL(pole_dos_kernel, dim3((ne + 16 * kDosTiles - 1) / (16 * kDosTiles), ns), dim3(kDosThreads), 0, s, a,
                      mu, eta, e_min, de, ne, ns, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
