@@ -276,6 +276,18 @@ int density_var(const dmft_handle h, int nbp, int nc, bool spec) {
   return var;
 }
 
+// Trace and adjoint kinds: the chosen variant, or where that is the spectral one and
+// has no class for nc orbitals the first other.
+int kind_var(const dmft_handle h, int kind, int nbp, int nc) {
+  const int var = choose_var(h, kind, nbp);
+  if (var != kSpectralVariant || spec_adj_fits(nc)) return var;
+  int v[16];
+  const int n = dyson_variants(nbp, kind, v, 16);
+  for (int i = 0; i < n; ++i)
+    if (v[i] != kSpectralVariant) return v[i];
+  return var;
+}
+
 // Build the workspace layout for one lattice.  form (density kind): by the
 // chosen variants with room for every other one too (so that one workspace size
 // holds whatever is chosen later), the same without that room, without the
@@ -302,10 +314,30 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.nbp_max = *std::max_element(L.nbp.begin(), L.nbp.end());
   L.kind = kind;
   L.tile = force ? *force : choose_tile(h, kind, nk, nw, L.nbp_max);
-  L.tile.wt = std::max(1, std::min(L.tile.wt, nw));
-  L.tile.kt = std::max(1, std::min(L.tile.kt, nk));
-  L.n_wtiles = (nw + L.tile.wt - 1) / L.tile.wt;
   const int ncls = spec_ncls(lat->nc);
+  // trace and adjoint kinds: the spectral kernels take their own default tile and
+  // whole groups of 16 frequencies; the partials are sized for either default, so
+  // that a workspace holds the pass whichever variant is chosen later
+  int kt_min = L.tile.kt, wtiles_max = 0;
+  if (kind != KIND_DENSITY) {
+    const Tile other = spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc);
+    bool spec = false;
+    for (int n : L.nbp)
+      spec = spec || kind_var(h, kind, n, lat->nc) == kSpectralVariant ||
+             (kind == KIND_ADJOINT && kind_var(h, KIND_GENERAL, n, lat->nc) == kSpectralVariant);
+    if (!force) {
+      const Tile legacy = heuristic_tile(nk, nw);
+      kt_min = std::min(kt_min, std::min(legacy.kt, other.kt));
+      wtiles_max = (nw + std::min(legacy.wt, other.wt) - 1) / std::min(legacy.wt, other.wt);
+      if (spec && !h->tune.count(tile_key(kind, L.nbp_max, nk, nw))) L.tile = other;
+    }
+    if (spec) L.tile.wt = (L.tile.wt + 15) / 16 * 16;
+  }
+  L.tile.wt = std::max(1, std::min(L.tile.wt, kind == KIND_DENSITY ? nw : (nw + 15) / 16 * 16));
+  L.tile.kt = std::max(1, std::min(L.tile.kt, nk));
+  kt_min = std::max(1, std::min(kt_min, L.tile.kt));
+  L.n_wtiles = (nw + L.tile.wt - 1) / L.tile.wt;
+  wtiles_max = std::max(wtiles_max, L.n_wtiles);
   if (kind == KIND_DENSITY) {
     const bool tuned = force || h->tune.count(tile_key(kind, L.nbp_max, nk, nw));
     L.stile = tuned ? L.tile : spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc);
@@ -331,7 +363,11 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       L.t_stride += size * spec_slot_doubles(s, ncls);
       sall += (size + L.stile.kt - 1) / L.stile.kt;
     }
-    all += (size + L.tile.kt - 1) / L.tile.kt;
+    if (kind == KIND_ADJOINT) {  // table of the general product
+      b.t_base = L.t_stride;
+      L.t_stride += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
+    }
+    all += (size + kt_min - 1) / kt_min;
     (b.spec ? sany : any) = true;
     const int kt = b.spec ? L.stile.kt : L.tile.kt;
     int& at = b.spec ? sbase : base;
@@ -371,8 +407,9 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.meta_offs = take(sizeof(int64_t) * (nk + 1));
   L.spart = take(any ? (size_t)L.n_wtiles * L.s_stride * 16 : 0);
   L.xpart = take(any ? (size_t)all * nw * 256 * 16 : 0);
-  L.tpart = take((size_t)L.n_wtiles * nk * 3 * sizeof(double));
-  L.tsum = take(sany ? (size_t)L.s_wtiles * L.t_stride * sizeof(double) : 0);
+  L.tpart = take((size_t)wtiles_max * nk * 3 * sizeof(double));
+  L.tsum = take(kind == KIND_ADJOINT ? (size_t)L.t_stride * sizeof(double)
+                : sany ? (size_t)L.s_wtiles * L.t_stride * sizeof(double) : 0);
   L.xs = take(sany ? (size_t)sall * ((nw + 3) / 4) * 4 * ncls * ncls * 16 : 0);
   L.kscal = take((size_t)nk * 3 * sizeof(double));
   L.ktrace = take((size_t)nk * 2 * sizeof(double));
@@ -501,19 +538,21 @@ int run_dyson(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, con
       }
       HIPCHK(h, hipEventRecord(ev.first, s));
     }
-    if (adj.gen == 0 && (choose_var(h, KIND_ADJOINT, b.nbp) & 8)) {
+    if (adj.gen == 0 && (kind_var(h, KIND_ADJOINT, b.nbp, lat->nc) & 8)) {
       // fused scalar adjoint in the low-rank form (same partials as the dense kernel)
       DysonArgs aa = a;
       aa.mode = MODE_ADJ;
-      HIPCHK(h, launch_dyson(b.nbp, choose_var(h, KIND_ADJOINT, b.nbp), aa, b.n_ktiles, s));
-    } else if (adj.gen == 1 && (choose_var(h, KIND_GENERAL, b.nbp) & 8)) {
+      HIPCHK(h, launch_dyson(b.nbp, kind_var(h, KIND_ADJOINT, b.nbp, lat->nc), aa, b.n_ktiles, s));
+    } else if (adj.gen == 1 && (kind_var(h, KIND_GENERAL, b.nbp, lat->nc) & 8)) {
       // general vector-Jacobian product in the low-rank form (same partials as the dense kernel)
       DysonArgs aa = a;
       aa.mode = MODE_GEN;
       aa.nbar = adj.nbar;
       aa.off_n = L.ragged ? (const int64_t*)(ws + L.meta_offn) : nullptr;
       aa.gbar = adj.gbar;
-      HIPCHK(h, launch_dyson(b.nbp, choose_var(h, KIND_GENERAL, b.nbp), aa, b.n_ktiles, s));
+      aa.tsum = (double*)(ws + L.tsum);
+      aa.t_base = b.t_base;
+      HIPCHK(h, launch_dyson(b.nbp, kind_var(h, KIND_GENERAL, b.nbp, lat->nc), aa, b.n_ktiles, s));
     } else if (adj.gen >= 0) {
       if (b.nbp > 48) return fail(h, DMFT_EUNSUPPORTED, "the dense adjoint supports band windows up to 48");
       HIPCHK(h, launch_adjoint(b.nbp, adj.gen, a, adj.nbar, L.ragged ? (const int64_t*)(ws + L.meta_offn) : nullptr,
@@ -521,7 +560,8 @@ int run_dyson(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, con
     } else {
       DysonArgs aa = a;
       if (b.spec) spec_args(L, b, ws, aa);
-      HIPCHK(h, launch_dyson(b.nbp, (mode & MODE_TRACE) ? choose_var(h, KIND_TRACE, b.nbp) : b.var, aa, b.n_ktiles, s));
+      const int var = (mode & MODE_TRACE) ? kind_var(h, KIND_TRACE, b.nbp, lat->nc) : b.var;
+      HIPCHK(h, launch_dyson(b.nbp, var, aa, b.n_ktiles, s));
     }
     if (h->timing) {
       HIPCHK(h, hipEventRecord(ev.second, s));
@@ -1163,12 +1203,14 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
     std::vector<double> ref(nres), got(nres);
     bool have_ref = false;
     double best_ms = 1e300;
-    Tile best_tile = vars[0] == kSpectralVariant ? sbase : base;
+    const bool spec0 = vars[0] == kSpectralVariant && (kind == KIND_DENSITY || spec_adj_fits(nc));
+    Tile best_tile = spec0 ? sbase : base;
     int best_var = vars[0];
     char key[32];
     snprintf(key, sizeof key, "%d/%d", kind, nbp);
     for (int vi = 0; vi < nv; ++vi) {
       if (vars[vi] == kLowrankP3Variant && !lowrank_p3_fits(nbp, nc)) continue;
+      if (vars[vi] == kSpectralVariant && kind != KIND_DENSITY && !spec_adj_fits(nc)) continue;
       h->tvar[key] = vars[vi];
       for (const Tile& t : vars[vi] == kSpectralVariant ? stiles : tiles) {
         Layout L;

@@ -34,6 +34,18 @@ constexpr int spec_wgs_per_cu(int nbp, int ncls) {
   return by_regs < by_lds ? by_regs : (by_lds < 1 ? 1 : by_lds);
 }
 
+// Trace and adjoint kernels (spectral_adj_impl.h): orbital classes (fewer than above:
+// five kernels per class and size), whether there is one, the table of the general
+// product (chunks of four of the 2 nb - 1 rows in lane order, then the diagonal), and
+// work-groups per CU, by the row matrices they hold (up to seven of 4 ncls registers;
+// 5 orbitals at three work-groups: 0.238 against 0.191 ms, spilling).
+constexpr int spec_adj_ncls(int nc) { return nc <= 5 ? 5 : nc <= 8 ? 8 : nc <= 10 ? 10 : 14; }
+constexpr bool spec_adj_fits(int nc) { return nc <= 14; }
+constexpr int64_t spec_adj_slot_doubles(int nbp, int ncls) {
+  return (int64_t)(nbp / 2) * spec_col_tiles(ncls) * 64 + nbp;
+}
+constexpr int spec_adj_wgs_per_cu(int ncls, int what) { return ncls <= 5 || (ncls <= 8 && what == 0) ? 2 : 1; }
+
 // Kernel modes (bit set).
 enum : int {
   MODE_S = 1,      // accumulate sum_n G_kn into per-(frequency tile, k) partials
@@ -82,7 +94,9 @@ struct DysonArgs {
   const double* gbar;          // MODE_GEN: complex G_loc cotangent [nw][nc][nc] or null
   // spectral form: per frequency tile (stride t_stride doubles) this bucket's
   // k-points have slots of spec_slot_doubles from t_base, in klist order; xs is
-  // the G_loc partial [n_ktiles][ceil(nw / 4)][ncls columns][4 frequencies][ncls rows] complex
+  // the G_loc partial
+  // [n_ktiles][ceil(nw / 4)][ncls columns][4 frequencies][ncls rows] complex.
+  // MODE_GEN: tsum holds the table slots of spec_adj_slot_doubles instead
   double* tsum;
   int64_t t_stride, t_base;
   double* xs;
@@ -141,7 +155,7 @@ struct EpilogueArgs {
 // kind only.  A launch of either outside its shapes returns hipErrorInvalidValue.
 constexpr int kLowrankPairVariant = 40;
 constexpr int kLowrankP3Variant = 42;
-// The spectral form (spectral_impl.h), density kind, every size.
+// The spectral form (spectral_impl.h; trace and adjoint kinds: spectral_adj_impl.h), every size.
 constexpr int kSpectralVariant = 136;
 inline bool lowrank_p3_fits(int nbp, int nc) { return nc <= 5 && nbp <= 64; }
 hipError_t launch_dyson(int nbp, int var, const DysonArgs& a, int n_ktiles, hipStream_t s);

@@ -25,6 +25,7 @@ bool dyson_supported(int nbp);
 hipError_t launch_spectral(int nbp, int ncls, const DysonArgs& a, const void* items, int n_items,
                            const DysonArgs* args, int* counter, int grid, hipStream_t s);
 hipError_t launch_spectral_epilogue(const EpilogueArgs& a, double* nk_out, hipStream_t s);
+hipError_t launch_spectral_adj(int nbp, const DysonArgs& a, int grid, hipStream_t s);
 
 // Kinds 0 and 1 without the spectral kernel: dense variants first, then the low-rank ones.
 static int band_variants(int nbp, int kind, int* out, int max) {
@@ -44,22 +45,32 @@ static int band_variants(int nbp, int kind, int* out, int max) {
 // low-rank variants first, then code 0 for the dense adjoint kernel, which
 // exists up to 48 bands.
 int dyson_variants(int nbp, int kind, int* out, int max) {
+  if (!dyson_supported(nbp) || max <= 0) return 0;
+  out[0] = kSpectralVariant;
+  int n = 1;
   if (kind == 2 || kind == 3) {
-    int n = lowrank_variants(nbp, kind, out, max);
-    if (nbp <= 48 && dyson_supported(nbp) && n < max) out[n++] = 0;
+    n += lowrank_variants(nbp, kind, out + n, max - n);
+    if (nbp <= 48 && n < max) out[n++] = 0;
     return n;
   }
-  if (kind == 0 && dyson_supported(nbp) && max > 0) {
-    out[0] = kSpectralVariant;
-    return 1 + band_variants(nbp, kind, out + 1, max - 1);
-  }
-  return band_variants(nbp, kind, out, max);
+  n += band_variants(nbp, kind, out + n, max - n);
+  if (kind == 1)  // the low-rank one that serves where the spectral one does not
+    for (int i = 2; i < n; ++i)
+      if (out[i] == (nbp <= 32 ? 14 : 10)) {
+        const int v = out[i];
+        for (int j = i; j > 1; --j) out[j] = out[j - 1];
+        out[1] = v;
+        break;
+      }
+  return n;
 }
 
 bool dyson_supported(int nbp) { return nbp == 16 || nbp == 32 || nbp == 48 || nbp == 64; }
 
 hipError_t launch_dyson(int nbp, int var, const DysonArgs& a, int n_ktiles, hipStream_t s) {
   dim3 grid((unsigned)(n_ktiles * a.n_wtiles));
+  if (var == kSpectralVariant && (a.mode & (MODE_TRACE | MODE_ADJ | MODE_GEN)))
+    return launch_spectral_adj(nbp, a, (int)grid.x, s);
   if (var == kSpectralVariant)
     return launch_spectral(nbp, spec_ncls(a.nc), a, nullptr, 0, nullptr, nullptr, (int)grid.x, s);
   if (var & 8) return launch_lowrank(nbp, var, a, grid, s);
@@ -182,23 +193,18 @@ __global__ void __launch_bounds__(256) nk_epilogue_kernel(EpilogueArgs a, double
   }
 }
 
-// Per-k tr N(k) and d tr N(k) / dmu from the frequency sums of Re tr G, Re tr G^2.
-__global__ void __launch_bounds__(64) trace_epilogue_kernel(EpilogueArgs a) {
-  __shared__ double red[64];
-  const int k = blockIdx.x;
-  const int nc = a.nc;
-  const int nb = a.nb_uniform > 0 ? a.nb_uniform : a.nb[k];
-  const int64_t ob = a.nb_uniform > 0 ? (int64_t)k * nb : a.off_b[k];
-  const double* eps = a.eps + ob;
-  const double2* P = reinterpret_cast<const double2*>(a.proj) + ob * nc;
+// This thread's share of tr M1 = sum_v (E_v - mu) + sum_{al,be} (Sigma_inf - V_DC)[al][be]
+// (S S^dag)[be][al]: band t % 64 of kTailThreads / 64 groups of threads, each group every
+// fourth al.  (256 k-points of 40 bands, 14 orbitals: 47 us with one group, bound by the
+// latency of nc^2 dependent steps, 18 with four.)
+constexpr int kTailThreads = 256;
+__device__ double tail_trace(const EpilogueArgs& a, const double* eps, const double2* P, int nb, double mu) {
+  const int nc = a.nc, g = threadIdx.x >> 6;
   const double2* sinf = reinterpret_cast<const double2*>(a.sigma_inf);
-  const double mu = a.mu_ptr ? *a.mu_ptr : a.mu;
-  const double beta = a.beta;
-  // tr M1 = sum_v (E_v - mu) + sum_{al,be} (Sigma_inf - V_DC)[al][be] (S S^dag)[be][al]
   double trm = 0.0;
-  for (int v = threadIdx.x; v < nb; v += blockDim.x) {
-    trm += eps[v] - mu;
-    for (int al = 0; al < nc; ++al)
+  for (int v = threadIdx.x & 63; v < nb; v += 64) {
+    if (g == 0) trm += eps[v] - mu;
+    for (int al = g; al < nc; al += kTailThreads / 64)
       for (int be = 0; be < nc; ++be) {
         double2 m = sinf ? sinf[al * nc + be] : make_double2(0.0, 0.0);
         if (al == be) m.x -= a.e_dc[al];
@@ -207,7 +213,20 @@ __global__ void __launch_bounds__(64) trace_epilogue_kernel(EpilogueArgs a) {
         trm += m.x * ss.x - m.y * ss.y;
       }
   }
-  trm = block_sum(trm, red);
+  return trm;
+}
+
+// Per-k tr N(k) and d tr N(k) / dmu from the frequency sums of Re tr G, Re tr G^2.
+__global__ void __launch_bounds__(kTailThreads) trace_epilogue_kernel(EpilogueArgs a) {
+  __shared__ double red[kTailThreads];
+  const int k = blockIdx.x;
+  const int nb = a.nb_uniform > 0 ? a.nb_uniform : a.nb[k];
+  const int64_t ob = a.nb_uniform > 0 ? (int64_t)k * nb : a.off_b[k];
+  const double* eps = a.eps + ob;
+  const double2* P = reinterpret_cast<const double2*>(a.proj) + ob * a.nc;
+  const double mu = a.mu_ptr ? *a.mu_ptr : a.mu;
+  const double beta = a.beta;
+  const double trm = block_sum(tail_trace(a, eps, P, nb, mu), red);
   if (threadIdx.x == 0) {
     double trg = 0.0, trg2 = 0.0;
     for (int w = 0; w < a.n_wtiles; ++w) {
@@ -227,32 +246,21 @@ __global__ void __launch_bounds__(64) trace_epilogue_kernel(EpilogueArgs a) {
 
 // Per-k [tr N, d tr N/dmu, mubar_k] from the adjoint kernel's [n_wtiles][nk][3]
 // partials; mubar_k gets the tail term (beta/4 - 2 s2/beta) Re tr Nbar_k.
-__global__ void __launch_bounds__(64) adj_epilogue_kernel(EpilogueArgs a, const double* nbar) {
-  __shared__ double red[64];
+__global__ void __launch_bounds__(kTailThreads) adj_epilogue_kernel(EpilogueArgs a, const double* nbar) {
+  __shared__ double red[kTailThreads];
   const int k = blockIdx.x;
-  const int nc = a.nc;
   const int nb = a.nb_uniform > 0 ? a.nb_uniform : a.nb[k];
   const int64_t ob = a.nb_uniform > 0 ? (int64_t)k * nb : a.off_b[k];
   const int64_t on = a.nb_uniform > 0 ? (int64_t)k * nb * nb : a.off_n[k];
   const double* eps = a.eps + ob;
-  const double2* P = reinterpret_cast<const double2*>(a.proj) + ob * nc;
-  const double2* sinf = reinterpret_cast<const double2*>(a.sigma_inf);
+  const double2* P = reinterpret_cast<const double2*>(a.proj) + ob * a.nc;
   const double mu = a.mu_ptr ? *a.mu_ptr : a.mu;
   const double beta = a.beta;
-  double trm = 0.0, trn = 0.0;
-  for (int v = threadIdx.x; v < nb; v += blockDim.x) {
-    trm += eps[v] - mu;
-    for (int al = 0; al < nc; ++al)
-      for (int be = 0; be < nc; ++be) {
-        double2 m = sinf ? sinf[al * nc + be] : make_double2(0.0, 0.0);
-        if (al == be) m.x -= a.e_dc[al];
-        double2 pb = P[be * nb + v], pa = P[al * nb + v];
-        double2 ss = make_double2(pb.x * pa.x + pb.y * pa.y, pb.y * pa.x - pb.x * pa.y);
-        trm += m.x * ss.x - m.y * ss.y;
-      }
-    if (nbar) trn += reinterpret_cast<const double2*>(nbar)[on + (int64_t)v * nb + v].x;
-  }
-  trm = block_sum(trm, red);
+  double trn = 0.0;
+  if (nbar)
+    for (int v = threadIdx.x; v < nb; v += kTailThreads)
+      trn += reinterpret_cast<const double2*>(nbar)[on + (int64_t)v * nb + v].x;
+  const double trm = block_sum(tail_trace(a, eps, P, nb, mu), red);
   trn = block_sum(trn, red);
   if (threadIdx.x == 0) {
     double trg = 0.0, trg2 = 0.0, mub = 0.0;
@@ -276,7 +284,7 @@ __global__ void __launch_bounds__(64) adj_epilogue_kernel(EpilogueArgs a, const 
 }
 
 hipError_t launch_adj_epilogue(const EpilogueArgs& a, const double* nbar, hipStream_t s) {
-  hipLaunchKernelGGL(adj_epilogue_kernel, dim3(a.nk), dim3(64), 0, s, a, nbar);
+  hipLaunchKernelGGL(adj_epilogue_kernel, dim3(a.nk), dim3(kTailThreads), 0, s, a, nbar);
   return hipGetLastError();
 }
 
@@ -321,7 +329,7 @@ hipError_t launch_nk_epilogue(const EpilogueArgs& a, double* nk_out, hipStream_t
 }
 
 hipError_t launch_trace_epilogue(const EpilogueArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(trace_epilogue_kernel, dim3(a.nk), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(trace_epilogue_kernel, dim3(a.nk), dim3(kTailThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -40,11 +40,6 @@ hipError_t launch_spectral(int nbp, int ncls, const DysonArgs& a, const void* it
 
 namespace {
 
-// Smallest energy step the weighted mean of adjacent sums resolves: steps below
-// it (equal energies) count as this much, so that a group of equal energies gets
-// the plain mean of its sums instead of 0 / 0.
-constexpr double kTinyStep = 1e-200;
-
 // Sum over the four lanes of a quad.
 __device__ __forceinline__ double quad_sum(double v) {
   v += __builtin_amdgcn_update_dpp(0.0, v, 0xB1, 0xf, 0xf, true);  // quad_perm 1, 0, 3, 2

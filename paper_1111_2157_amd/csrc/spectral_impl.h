@@ -124,6 +124,11 @@ struct SpecShared {
   int next;
 };
 
+// Smallest energy step the weighted mean of adjacent sums resolves: steps below
+// it (equal energies) count as this much, so that a group of equal energies gets
+// the plain mean of its sums instead of 0 / 0.
+constexpr double kTinyStep = 1e-200;
+
 // Order-preserving integer image of a double (a total order, NaN included, so
 // that the ranks are a permutation for any input).
 __device__ __forceinline__ unsigned long long spec_key(double e) {
