@@ -44,7 +44,11 @@ struct Bucket {
   bool spec = false;   // it is the spectral kernel
   int n_ktiles = 0;
   int ktile_base = 0;  // first k-tile among those of the buckets of the same form
-  int64_t t_base = 0;  // spectral form: first slot of the sums within a frequency tile (doubles)
+  // spectral form (density kind): its own tile, frequency tiles, and the sums (doubles from
+  // L.tsum): the first slot and the stride of a frequency tile
+  Tile tile;
+  int wtiles = 0;
+  int64_t t_base = 0, t_stride = 0;
 };
 
 // Forms make_layout may choose between for the density kind.
@@ -57,10 +61,10 @@ struct Layout {
   size_t spart = 0, xpart = 0, tpart = 0, kscal = 0, ktrace = 0, total = 0;
   int64_t s_stride = 0;
   int n_wtiles = 0, n_ktiles_total = 0;
-  // spectral form (density kind)
-  Tile stile;
-  int s_wtiles = 0, s_ktiles_total = 0;
-  int64_t t_stride = 0;
+  // spectral form: k-tiles of all buckets (density kind), doubles of the sums
+  int s_ktiles_total = 0;
+  int64_t t_total = 0;
+  bool tuned = false;  // the tile was measured or forced
   size_t tsum = 0, xs = 0;
   std::vector<Bucket> buckets;
   std::vector<int32_t> nb, nbp;
@@ -209,20 +213,21 @@ Tile heuristic_tile(int nk, int nw) {
   return t;
 }
 
-// Tile of the spectral form: the cheapest (k-tile, frequency tile) under a model
-// of its pass.  A group of 16 frequencies of one k-point costs a work-group its
-// matrix products at 64 cycles and its row operations at 4 cycles a wavefront
-// (measured within 15% at 32 to 64 bands), a k-point about two groups' worth of
-// set-up and write-out, and items run in rounds over the work-group slots of 256
-// CUs.  Smaller k-tiles mean more G_loc partials and smaller frequency tiles more
-// partial sums, each written and read once at about 4 TB/s, and both are kept to
-// about 2 GB.
+// Tile of the spectral form for nk k-points of one padded size: the cheapest (k-tile,
+// frequency tile) under a model of its pass.  A group of 16 frequencies of one k-point
+// costs a CU its matrix products at 64 cycles and its row operations at 4 cycles a
+// wavefront, however many work-groups share the CU (5 orbitals, 64 bands: 4.0 us alone,
+// 4.3 with three; up to 40% more is charged where too few share it, which 8 orbitals, 32
+// bands show), a k-point its set-up and
+// write-out, shared among those work-groups, and items are dealt to 256 CUs.  Smaller k-tiles mean more G_loc partials and smaller
+// frequency tiles more partial sums, each written and read once at about 4 TB/s, and
+// both are kept to about 2 GB.
 Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc) {
   const int ncls = spec_ncls(nc), nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
   const double per_cu = spec_wgs_per_cu(nbp, ncls);
-  const double group = (64.0 * (nt * nbp / 2 + nr * nt * 8) / 4.0 + 4.0 * (18.0 * ncls * ncls + 130.0 * ncls) + 2500.0) *
-                       std::max(1.0, per_cu * 0.9) / 2.2e9;
-  const double setup = 2.5e-5, slots = 256.0 * per_cu;
+  const double group = (64.0 * (nt * nbp / 2 + nr * nt * 8) / 4.0 + 4.0 * (18.0 * ncls * ncls + 130.0 * ncls) + 2500.0) /
+                       2.2e9;
+  const double setup = 1.8e-6 * ncls;
   const int nwr = (nw + 15) / 16 * 16;
   Tile best;
   double best_t = 1e300;
@@ -233,7 +238,9 @@ Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc) {
       const double items = ktiles * wtiles;
       const double xs = ktiles * nw * 16.0 * ncls * ncls, ts = wtiles * nk * 8.0 * spec_slot_doubles(nbp, ncls);
       if ((xs > 2e9 && kt < std::min(nk, 64) / 2) || (ts > 2e9 && f > 1)) continue;
-      const double t = std::ceil(items / slots) * kt * (setup + (wt / 16) * group) + xs * 2.0 / 4e12 + ts * 2.0 / 1.5e12;
+      const double thin = 1.4 - 0.4 * std::min(1.0, items / (256.0 * per_cu));
+      const double t = std::ceil(items / 256.0) * kt * (setup / per_cu + (wt / 16) * group) * thin + xs * 2.0 / 4e12 +
+                       ts * 2.0 / 1.5e12;
       if (t < best_t) {
         best_t = t;
         best.kt = kt;
@@ -338,14 +345,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   kt_min = std::max(1, std::min(kt_min, L.tile.kt));
   L.n_wtiles = (nw + L.tile.wt - 1) / L.tile.wt;
   wtiles_max = std::max(wtiles_max, L.n_wtiles);
-  if (kind == KIND_DENSITY) {
-    const bool tuned = force || h->tune.count(tile_key(kind, L.nbp_max, nk, nw));
-    L.stile = tuned ? L.tile : spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc);
-    // whole groups of 16 frequencies
-    L.stile.wt = std::min((L.stile.wt + 15) / 16 * 16, (nw + 15) / 16 * 16);
-    L.stile.kt = std::max(1, std::min(L.stile.kt, nk));
-    L.s_wtiles = (nw + L.stile.wt - 1) / L.stile.wt;
-  }
+  const bool tuned = L.tuned = force || h->tune.count(tile_key(kind, L.nbp_max, nk, nw));
   L.buckets.clear();
   int base = 0, sbase = 0, all = 0, sall = 0;
   bool any = false, sany = false;
@@ -359,17 +359,23 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
     if (kind == KIND_DENSITY) {
       b.var = form == LAYOUT_SPEC ? kSpectralVariant : density_var(h, s, lat->nc, form != LAYOUT_NO_SPEC);
       b.spec = b.var == kSpectralVariant;
-      b.t_base = L.t_stride;
-      L.t_stride += size * spec_slot_doubles(s, ncls);
-      sall += (size + L.stile.kt - 1) / L.stile.kt;
+      b.tile = tuned ? L.tile : spec_heuristic_tile(size, nw, s, lat->nc);
+      // whole groups of 16 frequencies
+      b.tile.wt = std::min((b.tile.wt + 15) / 16 * 16, (nw + 15) / 16 * 16);
+      b.tile.kt = std::max(1, std::min(b.tile.kt, size));
+      b.wtiles = (nw + b.tile.wt - 1) / b.tile.wt;
+      b.t_base = L.t_total;
+      b.t_stride = size * spec_slot_doubles(s, ncls);
+      L.t_total += b.wtiles * b.t_stride;
+      sall += (size + b.tile.kt - 1) / b.tile.kt;
     }
     if (kind == KIND_ADJOINT) {  // table of the general product
-      b.t_base = L.t_stride;
-      L.t_stride += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
+      b.t_base = L.t_total;
+      L.t_total += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
     }
     all += (size + kt_min - 1) / kt_min;
     (b.spec ? sany : any) = true;
-    const int kt = b.spec ? L.stile.kt : L.tile.kt;
+    const int kt = b.spec ? b.tile.kt : L.tile.kt;
     int& at = b.spec ? sbase : base;
     b.n_ktiles = (size + kt - 1) / kt;
     b.ktile_base = at;
@@ -408,8 +414,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.spart = take(any ? (size_t)L.n_wtiles * L.s_stride * 16 : 0);
   L.xpart = take(any ? (size_t)all * nw * 256 * 16 : 0);
   L.tpart = take((size_t)wtiles_max * nk * 3 * sizeof(double));
-  L.tsum = take(kind == KIND_ADJOINT ? (size_t)L.t_stride * sizeof(double)
-                : sany ? (size_t)L.s_wtiles * L.t_stride * sizeof(double) : 0);
+  L.tsum = take(kind == KIND_ADJOINT || sany ? (size_t)L.t_total * sizeof(double) : 0);
   L.xs = take(sany ? (size_t)sall * ((nw + 3) / 4) * 4 * ncls * ncls * 16 : 0);
   L.kscal = take((size_t)nk * 3 * sizeof(double));
   L.ktrace = take((size_t)nk * 2 * sizeof(double));
@@ -486,11 +491,11 @@ struct AdjReq {
 
 // The arguments of a bucket in the spectral form.
 void spec_args(const Layout& L, const Bucket& b, char* ws, DysonArgs& a) {
-  a.kt = L.stile.kt;
-  a.wt = L.stile.wt;
-  a.n_wtiles = L.s_wtiles;
+  a.kt = b.tile.kt;
+  a.wt = b.tile.wt;
+  a.n_wtiles = b.wtiles;
   a.tsum = (double*)(ws + L.tsum);
-  a.t_stride = L.t_stride;
+  a.t_stride = b.t_stride;
   a.t_base = b.t_base;
   a.xs = (double*)(ws + L.xs);
 }
@@ -603,6 +608,20 @@ EpilogueArgs epilogue_args(const dmft_lattice* lat, const dmft_sigma* sig, const
   return e;
 }
 
+// A pass for G_loc alone writes no sums, so smaller frequency tiles cost it nothing: the
+// default ones are halved until nine tenths of the work-group slots have an item (123
+// k-points of 27 bands, 7 orbitals, 333 frequencies: 59 us with the 246 items of the
+// full pass, 54 with 492, 57 with 861, which spend more on their set-up).  The sums'
+// part of the workspace keeps its size.
+void gloc_tiles(Layout& L, int nw, int nc) {
+  for (Bucket& b : L.buckets)
+    while (b.spec && !L.tuned && b.tile.wt > 16 &&
+           b.n_ktiles * b.wtiles < 230 * spec_wgs_per_cu(b.nbp, spec_ncls(nc))) {
+      b.tile.wt = (b.tile.wt / 2 + 15) / 16 * 16;
+      b.wtiles = (nw + b.tile.wt - 1) / b.tile.wt;
+    }
+}
+
 int prepare(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, void* ws, size_t ws_bytes,
             Layout& L, int kind, hipStream_t s) {
   int r = check_shapes(h, lat, sig);
@@ -625,20 +644,18 @@ int nk_epilogues(dmft_handle h, const Layout& L, char* ws, const EpilogueArgs& b
     else
       others = true;
   if (others) HIPCHK(h, launch_nk_epilogue(e, nk, s));
-  size_t at = 0;
-  for (const Bucket& b : L.buckets) {
-    if (b.spec) {
-      e.spec_nbp = b.nbp;
-      e.klist = L.ragged || L.buckets.size() > 1 ? (const int32_t*)(ws + L.meta_klist) + at : nullptr;
-      e.nklist = (int)b.klist.size();
-      e.n_wtiles = L.s_wtiles;
-      e.tsum = (double*)(ws + L.tsum);
-      e.t_stride = L.t_stride;
-      e.t_base = b.t_base;
-      HIPCHK(h, launch_nk_epilogue(e, nk, s));
-    }
-    at += b.klist.size();
+  // the spectral buckets in one launch, the widest windows (the longest blocks) first
+  e.klist = L.ragged || L.buckets.size() > 1 ? (const int32_t*)(ws + L.meta_klist) : nullptr;
+  e.tsum = (double*)(ws + L.tsum);
+  size_t at = L.nb.size();
+  for (auto b = L.buckets.rbegin(); b != L.buckets.rend(); ++b) {
+    at -= b->klist.size();
+    if (!b->spec) continue;
+    e.spec_nbp = std::max(e.spec_nbp, b->nbp);
+    e.sizes[e.n_sizes++] = {b->nbp, e.nklist, (int)at, b->wtiles, b->t_base, b->t_stride};
+    e.nklist += (int)b->klist.size();
   }
+  if (e.n_sizes) HIPCHK(h, launch_nk_epilogue(e, nk, s));
   return DMFT_OK;
 }
 
@@ -719,7 +736,7 @@ int density_noalloc_impl(dmft_handle h, const dmft_lattice* lat, const dmft_sigm
     L = Layout();
     r = make_layout(h, &u, sig, L, KIND_DENSITY, nullptr, form);
     if (r) return r;
-    Tile t = L.buckets[0].spec ? L.stile : L.tile;
+    Tile t = L.buckets[0].spec ? L.buckets[0].tile : L.tile;
     while (L.total > cap) {
       // fewer k tiles shrink the G_loc partials, fewer frequency tiles those of sum_n G
       if (t.kt < u.nk)
@@ -860,6 +877,7 @@ int gloc_compute(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, 
   Layout L;
   int r = prepare(h, lat, sig, ws, ws_bytes, L, KIND_DENSITY, stream);
   if (r) return r;
+  gloc_tiles(L, sig->nw, lat->nc);
   return density_impl(h, lat, sig, L, (char*)ws, mu, nullptr, 2, nullptr, gloc, nullptr, stream);
 }
 
@@ -898,6 +916,7 @@ int density_matrix(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig
   Layout L;
   int r = prepare(h, lat, sig, ws, ws_bytes, L, KIND_DENSITY, stream);
   if (r) return r;
+  if (!nk && !scalars) gloc_tiles(L, sig->nw, lat->nc);
   return density_impl(h, lat, sig, L, (char*)ws, mu, nullptr, tail_order, nk, gloc, scalars, stream);
 }
 
@@ -1315,7 +1334,7 @@ int batched_layout(dmft_handle h, int n_iter, const dmft_lattice* const* lat, co
     o = align_up(o + Ls[s].total);
     for (const Bucket& b : Ls[s].buckets) {
       ++na;
-      ni += b.n_ktiles * (lowrank ? Ls[s].s_wtiles : Ls[s].n_wtiles);
+      ni += b.n_ktiles * (lowrank ? b.wtiles : Ls[s].n_wtiles);
     }
   }
   *o_args = o;
@@ -1639,7 +1658,7 @@ int batched_candidates(dmft_handle h, int n_iter, const dmft_lattice* const* lat
   int r = batched_layout(h, n_iter, lat, sig, Ls, base, nullptr, lowrank, &total, &a, &b, &c, &d, &na, &ni);
   if (r) return r;
   std::vector<Tile> tiles;
-  for (auto& L : Ls) tiles.push_back(lowrank ? L.stile : L.tile);
+  for (auto& L : Ls) tiles.push_back(L.tile);
   out = batched_tile_candidates(tiles);
   return DMFT_OK;
 }

@@ -128,13 +128,19 @@ struct EpilogueArgs {
   double* ktrace;              // [nk][2] per-k  tr N, d tr N / dmu   (trace mode)
   double s2;                   // sum_n 1 / w_n^2, summed in increasing n
   int skip_sizes;              // bit nbp / 16: k-points of that padded size are left to the spectral epilogue
-  // spectral form: when spec_nbp > 0 launch_nk_epilogue runs the spectral
-  // epilogue on the bucket klist[0 .. nklist) instead (fields as in DysonArgs)
-  int spec_nbp;
+  // spectral form: when spec_nbp > 0 (the largest padded size) launch_nk_epilogue
+  // runs the spectral epilogue instead, on the nklist k-points of n_sizes buckets: the
+  // one that starts at block `first` holds klist[at ..] (null: k = 0, 1, ...), its sums
+  // n_wtiles frequency tiles as in DysonArgs
+  struct SpecSize {
+    int nbp, first, at, n_wtiles;
+    int64_t t_base, t_stride;
+  };
+  int spec_nbp, n_sizes;
+  SpecSize sizes[4];
   const int32_t* klist;
   int nklist;
   double* tsum;
-  int64_t t_stride, t_base;
   // ... or, when gloc_out is set, the reduction of n_xs G_loc partials (added to
   // gloc_out's contents if gloc_add)
   const double* xs;

@@ -72,8 +72,12 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
   __shared__ unsigned long long key[64];
   __shared__ int rank[64], inv[64];
   const int tid = threadIdx.x, nth = blockDim.x;
-  const int slot = blockIdx.x;
-  const int k = a.klist ? a.klist[slot] : slot;
+  int bucket = 0;
+  while (bucket + 1 < a.n_sizes && (int)blockIdx.x >= a.sizes[bucket + 1].first) ++bucket;
+  const int n_wtiles = a.sizes[bucket].n_wtiles, nbp = a.sizes[bucket].nbp;
+  const int64_t t_stride = a.sizes[bucket].t_stride;
+  const int slot = blockIdx.x - a.sizes[bucket].first;
+  const int k = a.klist ? a.klist[a.sizes[bucket].at + slot] : slot;
   const int nc = a.nc;
   const int nb = a.nb_uniform > 0 ? a.nb_uniform : a.nb[k];
   const int64_t ob = a.nb_uniform > 0 ? (int64_t)k * nb : a.off_b[k];
@@ -84,7 +88,6 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
   const double mu = a.mu_ptr ? *a.mu_ptr : a.mu;
   const double beta = a.beta, ctail = 2.0 * a.s2 / beta - 0.25 * beta;  // coefficient of M1
   const bool tail = a.tail_order == 2;
-  const int nbp = a.spec_nbp;
   const int64_t sd = spec_slot_doubles(nbp, NC);
   double2* ps = lds;                                            // [NC][nb] projectors, sorted columns
   double2* wv = lds + NC * nb;                                  // [nb][NC] W of a level
@@ -105,11 +108,11 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
     ps[al * nb + rank[v]] = al < nc ? P[idx] : make_double2(0.0, 0.0);
   }
   // element p of row r of the sums, added over the frequency tiles in order
-  double* base = a.tsum + a.t_base + (int64_t)slot * sd;
+  double* base = a.tsum + a.sizes[bucket].t_base + (int64_t)slot * sd;
   auto sum_at = [&](int64_t o) {
     double x = 0.0;
 #pragma unroll 4
-    for (int w = 0; w < a.n_wtiles; ++w) x += base[(int64_t)w * a.t_stride + o];
+    for (int w = 0; w < n_wtiles; ++w) x += base[(int64_t)w * t_stride + o];
     return x;
   };
   auto elem = [&](int r, int p) {
@@ -125,9 +128,9 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
       o[i] = elem(2 * (idx / NP) + 1, idx % NP);
       x[i] = 0.0;
     }
-    for (int w = 0; w < a.n_wtiles; ++w)
+    for (int w = 0; w < n_wtiles; ++w)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] += base[(int64_t)w * a.t_stride + o[i]];
+      for (int i = 0; i < 8; ++i) x[i] += base[(int64_t)w * t_stride + o[i]];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (i0 + i * nth < (nb - 1) * NP) (ULDS ? u[i0 + i * nth] : base[o[i]]) = x[i];
@@ -200,10 +203,10 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
     double t[PL], f = 0.0;
 #pragma unroll
     for (int i = 0; i < PL; ++i) t[i] = 0.0;
-    for (int w = 0; w < a.n_wtiles; ++w)
+    for (int w = 0; w < n_wtiles; ++w)
 #pragma unroll
       for (int i = 0; i < PL; ++i)
-        t[i] += base[(int64_t)w * a.t_stride + elem(2 * min(v, nb - 1), min(l + 16 * i, NP - 1))];
+        t[i] += base[(int64_t)w * t_stride + elem(2 * min(v, nb - 1), min(l + 16 * i, NP - 1))];
     if (v < nb)
 #pragma unroll
       for (int i = 0; i < PL; ++i) {
@@ -346,9 +349,10 @@ hipError_t epilogue_launch(const EpilogueArgs& a, size_t lds, double* nk_out, hi
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  // a thread per (band, orbital)
+  // a thread per (band, orbital), for small windows up to four (12 bands, 5 orbitals:
+  // 27 us with 64 threads, 20 with 256; 64 and 5: 60 with 1024, 46 with 512)
   int threads = 64;
-  while (threads < 1024 && threads < nbm * NC) threads *= 2;
+  while (threads < 1024 && (threads < nbm * NC || (threads < 256 && threads < 4 * nbm * NC))) threads *= 2;
   lds = lds < threads * sizeof(double) ? threads * sizeof(double) : lds;  // the final reduction's scratch
   hipLaunchKernelGGL((spec_epilogue_kernel<NC, ULDS>), dim3(a.nklist), dim3(threads), lds, s, a, nk_out);
   return hipGetLastError();
