@@ -436,7 +436,7 @@ int check_ws(dmft_handle h, const Layout& L, void* ws, size_t ws_bytes) {
 // Upload the per-k metadata (sizes, offsets, bucket k lists) into ws.
 int upload_meta(dmft_handle h, const Layout& L, char* ws, hipStream_t s, bool sync) {
   size_t nk = L.nb.size();
-  size_t need = sizeof(int32_t) * nk * 3 + sizeof(int64_t) * (nk + 1) * 3;
+  const size_t first = L.meta_nb, need = L.meta_offs + sizeof(int64_t) * (nk + 1) - first;
   if (h->staged) HIPCHK(h, hipEventSynchronize(h->staged));
   if (need > h->pinned_bytes) {
     if (h->pinned) HIPCHK(h, hipHostFree(h->pinned));
@@ -444,29 +444,17 @@ int upload_meta(dmft_handle h, const Layout& L, char* ws, hipStream_t s, bool sy
     HIPCHK(h, hipHostMalloc(&h->pinned, need, hipHostMallocDefault));
     h->pinned_bytes = need;
   }
-  char* p = (char*)h->pinned;
-  int32_t* nbv = (int32_t*)p;
-  int64_t* offb = (int64_t*)(nbv + nk);
-  int64_t* offn = offb + nk + 1;
-  int32_t* nbpv = (int32_t*)(offn + nk + 1);
-  int32_t* kl = nbpv + nk;
-  int64_t* offs = (int64_t*)(kl + nk);
-  std::copy(L.nb.begin(), L.nb.end(), nbv);
-  std::copy(L.off_b.begin(), L.off_b.end(), offb);
-  std::copy(L.off_n.begin(), L.off_n.end(), offn);
-  std::copy(L.nbp.begin(), L.nbp.end(), nbpv);
-  std::copy(L.off_s.begin(), L.off_s.end(), offs);
-  size_t at = 0;
-  for (const Bucket& b : L.buckets) {
-    std::copy(b.klist.begin(), b.klist.end(), kl + at);
-    at += b.klist.size();
-  }
-  HIPCHK(h, hipMemcpyAsync(ws + L.meta_nb, nbv, sizeof(int32_t) * nk, hipMemcpyHostToDevice, s));
-  HIPCHK(h, hipMemcpyAsync(ws + L.meta_offb, offb, sizeof(int64_t) * (nk + 1), hipMemcpyHostToDevice, s));
-  HIPCHK(h, hipMemcpyAsync(ws + L.meta_offn, offn, sizeof(int64_t) * (nk + 1), hipMemcpyHostToDevice, s));
-  HIPCHK(h, hipMemcpyAsync(ws + L.meta_nbp, nbpv, sizeof(int32_t) * nk, hipMemcpyHostToDevice, s));
-  HIPCHK(h, hipMemcpyAsync(ws + L.meta_klist, kl, sizeof(int32_t) * nk, hipMemcpyHostToDevice, s));
-  HIPCHK(h, hipMemcpyAsync(ws + L.meta_offs, offs, sizeof(int64_t) * (nk + 1), hipMemcpyHostToDevice, s));
+  // an image of the arrays as they lie in the workspace: one copy instead of six (about
+  // 5 us each)
+  auto at = [&](size_t offset) { return (char*)h->pinned + (offset - first); };
+  std::copy(L.nb.begin(), L.nb.end(), (int32_t*)at(L.meta_nb));
+  std::copy(L.off_b.begin(), L.off_b.end(), (int64_t*)at(L.meta_offb));
+  std::copy(L.off_n.begin(), L.off_n.end(), (int64_t*)at(L.meta_offn));
+  std::copy(L.nbp.begin(), L.nbp.end(), (int32_t*)at(L.meta_nbp));
+  std::copy(L.off_s.begin(), L.off_s.end(), (int64_t*)at(L.meta_offs));
+  int32_t* kl = (int32_t*)at(L.meta_klist);
+  for (const Bucket& b : L.buckets) kl = std::copy(b.klist.begin(), b.klist.end(), kl);
+  HIPCHK(h, hipMemcpyAsync(ws + first, h->pinned, need, hipMemcpyHostToDevice, s));
   if (!h->staged) HIPCHK(h, hipEventCreateWithFlags(&h->staged, hipEventDisableTiming));
   HIPCHK(h, hipEventRecord(h->staged, s));
   if (sync) HIPCHK(h, hipEventSynchronize(h->staged));
@@ -631,6 +619,9 @@ int prepare(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, void*
   r = check_ws(h, L, ws, ws_bytes);
   if (r) return r;
   HIPCHK(h, hipSetDevice(h->device));
+  // uniform windows: the kernels take nb from the argument and read no per-k arrays,
+  // except the band-window and low-rank density kernels and their epilogue
+  if (!L.ragged && L.buckets.size() == 1 && (kind != KIND_DENSITY || L.buckets[0].spec)) return DMFT_OK;
   return upload_meta(h, L, (char*)ws, s, false);
 }
 
