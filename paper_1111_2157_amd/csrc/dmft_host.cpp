@@ -222,25 +222,29 @@ Tile heuristic_tile(int nk, int nw) {
 // write-out, shared among those work-groups, and items are dealt to 256 CUs.  Smaller k-tiles mean more G_loc partials and smaller
 // frequency tiles more partial sums, each written and read once at about 4 TB/s, and
 // both are kept to about 2 GB.
-Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc) {
-  const int ncls = spec_ncls(nc), nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
-  const double per_cu = spec_wgs_per_cu(nbp, ncls);
-  const double group = (64.0 * (nt * nbp / 2 + nr * nt * 8) / 4.0 + 4.0 * (18.0 * ncls * ncls + 130.0 * ncls) + 2500.0) /
-                       2.2e9;
+Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc, bool adj = false) {
+  const int ncls = adj ? spec_adj_ncls(nc) : spec_ncls(nc), nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
+  const bool lane = !adj && spec_lane(ncls);
+  const double per_cu = adj ? spec_adj_wgs_per_cu(ncls, 0) : spec_wgs_per_cu(nbp, ncls);
+  double group = (64.0 * (nt * nbp / 2 + nr * nt * 8) / 4.0 + 4.0 * (18.0 * ncls * ncls + 130.0 * ncls) + 2500.0) / 2.2e9;
+  // one matrix per lane: a wavefront's group of 64 frequencies on its own SIMD
+  if (lane)
+    group = (nbp * (128.0 * nt + 60.0) + 16.0 * (128.0 * nt * nr + 400.0) + 100.0 * ncls * ncls * ncls) / 2.2e9;
   const double setup = 1.8e-6 * ncls;
-  const int nwr = (nw + 15) / 16 * 16;
+  const int unit = lane ? 64 : 16, nwr = (nw + unit - 1) / unit * unit;
   Tile best;
   double best_t = 1e300;
   for (int kt = 1; kt <= std::min(nk, 64); kt *= 2)
-    for (int f = 1; f <= nwr / 16; f = f < 8 ? f + 1 : f * 2) {
-      const int wt = (nwr / 16 + f - 1) / f * 16;
+    for (int f = 1; f <= nwr / unit; f = f < 8 ? f + 1 : f * 2) {
+      const int wt = (nwr / unit + f - 1) / f * unit;
       const double ktiles = (nk + kt - 1) / kt, wtiles = (nw + wt - 1) / wt;
       const double items = ktiles * wtiles;
       const double xs = ktiles * nw * 16.0 * ncls * ncls, ts = wtiles * nk * 8.0 * spec_slot_doubles(nbp, ncls);
       if ((xs > 2e9 && kt < std::min(nk, 64) / 2) || (ts > 2e9 && f > 1)) continue;
       const double thin = 1.4 - 0.4 * std::min(1.0, items / (256.0 * per_cu));
-      const double t = std::ceil(items / 256.0) * kt * (setup / per_cu + (wt / 16) * group) * thin + xs * 2.0 / 4e12 +
-                       ts * 2.0 / 1.5e12;
+      double t = std::ceil(items / 256.0) * kt * (setup / per_cu + (wt / unit) * group) * thin;
+      if (lane) t = std::ceil(items / 1024.0) * kt * (setup + (wt / unit) * group);
+      t += xs * 2.0 / 4e12 + ts * 2.0 / 1.5e12;
       if (t < best_t) {
         best_t = t;
         best.kt = kt;
@@ -327,7 +331,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   // that a workspace holds the pass whichever variant is chosen later
   int kt_min = L.tile.kt, wtiles_max = 0;
   if (kind != KIND_DENSITY) {
-    const Tile other = spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc);
+    const Tile other = spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc, true);
     bool spec = false;
     for (int n : L.nbp)
       spec = spec || kind_var(h, kind, n, lat->nc) == kSpectralVariant ||
@@ -360,8 +364,9 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       b.var = form == LAYOUT_SPEC ? kSpectralVariant : density_var(h, s, lat->nc, form != LAYOUT_NO_SPEC);
       b.spec = b.var == kSpectralVariant;
       b.tile = tuned ? L.tile : spec_heuristic_tile(size, nw, s, lat->nc);
-      // whole groups of 16 frequencies
-      b.tile.wt = std::min((b.tile.wt + 15) / 16 * 16, (nw + 15) / 16 * 16);
+      // whole groups of frequencies
+      const int unit = spec_wt_unit(ncls);
+      b.tile.wt = std::min((b.tile.wt + unit - 1) / unit * unit, (nw + unit - 1) / unit * unit);
       b.tile.kt = std::max(1, std::min(b.tile.kt, size));
       b.wtiles = (nw + b.tile.wt - 1) / b.tile.wt;
       b.t_base = L.t_total;
@@ -602,10 +607,10 @@ EpilogueArgs epilogue_args(const dmft_lattice* lat, const dmft_sigma* sig, const
 // full pass, 54 with 492, 57 with 861, which spend more on their set-up).  The sums'
 // part of the workspace keeps its size.
 void gloc_tiles(Layout& L, int nw, int nc) {
+  const int ncls = spec_ncls(nc), unit = spec_wt_unit(ncls);
   for (Bucket& b : L.buckets)
-    while (b.spec && !L.tuned && b.tile.wt > 16 &&
-           b.n_ktiles * b.wtiles < 230 * spec_wgs_per_cu(b.nbp, spec_ncls(nc))) {
-      b.tile.wt = (b.tile.wt / 2 + 15) / 16 * 16;
+    while (b.spec && !L.tuned && b.tile.wt > unit && b.n_ktiles * b.wtiles < 230 * spec_wgs_per_cu(b.nbp, ncls)) {
+      b.tile.wt = (b.tile.wt / 2 + unit - 1) / unit * unit;
       b.wtiles = (nw + b.tile.wt - 1) / b.tile.wt;
     }
 }
@@ -1188,7 +1193,7 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
     int nbp = L0.nbp_max, nk = lat->nk, nw = sig->nw, nc = lat->nc;
     int vars[16];
     int nv = dyson_variants(nbp, kind, vars, 16);
-    const Tile base = heuristic_tile(nk, nw), sbase = spec_heuristic_tile(nk, nw, nbp, nc);
+    const Tile base = heuristic_tile(nk, nw), sbase = spec_heuristic_tile(nk, nw, nbp, nc, kind != KIND_DENSITY);
     // frequency tiles around the default, then the k-tile halved and doubled
     // with the frequency tile scaled the other way (the same number of items;
     // fewer G_loc partial read-backs against fewer partials of the running sum).

@@ -24,7 +24,11 @@ constexpr int64_t spec_slot_doubles(int nbp, int ncls) {
 // many as leave its frequency loop without register spills (per lane 2 rt ct
 // registers of sums and about 8 nc + 100 for the rows of the inversions and the
 // operands in flight) and fit their LDS tables in 160 KB.
+// (One matrix per lane, up to five orbitals: four work-groups of one wavefront.)
+constexpr bool spec_lane(int ncls) { return ncls <= 5; }
+constexpr int spec_wt_unit(int ncls) { return spec_lane(ncls) ? 64 : 16; }  // frequencies a work-group takes at a time
 constexpr int spec_wgs_per_cu(int nbp, int ncls) {
+  if (spec_lane(ncls)) return 4;
   const int nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
   const int regs = nr * nt * 2 + 8 * ncls + 110 + (ncls <= 6 ? nbp / 2 : 0);
   const int lds = 16 * nt * 16 * 16 + 4 * 256 + 2 * 16 * (nbp + 4) * 16 + nbp * 17 * 8 + nbp * 20 + 64 +

@@ -341,6 +341,37 @@ __global__ void __launch_bounds__(256) spec_gloc_kernel(const double* xs, int n_
   }
 }
 
+// The same from the partials of the one-matrix-per-lane kernel ([k-tile][element][n]):
+// a thread per element and frequency.
+__global__ void __launch_bounds__(256) spec_gloc_lane_kernel(const double* xs, int n_xs, int nw4, int ncls, int nc, int nw,
+                                                             double* gloc, int add) {
+  __shared__ double2 part[4][64];
+  const int w = threadIdx.x >> 6, n = blockIdx.x * 64 + (threadIdx.x & 63), row = blockIdx.y, col = blockIdx.z;
+  const int64_t stride = (int64_t)ncls * ncls * nw4;
+  const double2* p = reinterpret_cast<const double2*>(xs) + (int64_t)(row * ncls + col) * nw4 + min(n, nw - 1);
+  double2 acc = make_double2(0.0, 0.0);
+#pragma unroll 8
+  for (int t = w; t < n_xs; t += 4) {
+    const double2 v = p[t * stride];
+    acc.x += v.x;
+    acc.y += v.y;
+  }
+  part[w][threadIdx.x & 63] = acc;
+  __syncthreads();
+  if (w == 0 && n < nw) {
+    for (int j = 1; j < 4; ++j) {
+      acc.x += part[j][threadIdx.x].x;
+      acc.y += part[j][threadIdx.x].y;
+    }
+    double2* g = reinterpret_cast<double2*>(gloc) + ((int64_t)n * nc + row) * nc + col;
+    if (add) {
+      acc.x += g->x;
+      acc.y += g->y;
+    }
+    *g = acc;
+  }
+}
+
 template <int NC, bool ULDS>
 hipError_t epilogue_launch(const EpilogueArgs& a, size_t lds, double* nk_out, hipStream_t s) {
   const int nbm = a.nb_uniform > 0 ? a.nb_uniform : a.spec_nbp;
@@ -372,6 +403,11 @@ hipError_t launch_spectral_epilogue(const EpilogueArgs& a, double* nk_out, hipSt
   const int ncls = spec_ncls(a.nc);
   if (a.gloc_out) {
     const int n4 = (a.nw + 3) / 4;
+    if (spec_lane(ncls)) {
+      hipLaunchKernelGGL(spec_gloc_lane_kernel, dim3((a.nw + 63) / 64, a.nc, a.nc), dim3(256), 0, s, a.xs, a.n_xs, 4 * n4,
+                         ncls, a.nc, a.nw, a.gloc_out, a.gloc_add);
+      return hipGetLastError();
+    }
     hipLaunchKernelGGL(spec_gloc_kernel, dim3(n4, a.nc), dim3(256), 0, s, a.xs, a.n_xs, n4, ncls, a.nc, a.nw, a.gloc_out,
                        a.gloc_add);
     return hipGetLastError();

@@ -1,6 +1,6 @@
 // Body of a spectral instantiation unit: SPEC_NAME launches spec_kernel<SPEC_NBP,
 // ncls, SPEC_WS>, a grid of one item each (items null) or a drain of a queue.
-#include "spectral_impl.h"
+#include "spectral_lane_impl.h"
 
 namespace dmft {
 hipError_t SPEC_NAME(int ncls, const DysonArgs& a, const void* items, int n_items, const DysonArgs* args, int* counter,
@@ -11,9 +11,14 @@ hipError_t SPEC_NAME(int ncls, const DysonArgs& a, const void* items, int n_item
     hipLaunchKernelGGL((spec_kernel<SPEC_NBP, NC, SPEC_WS>), dim3(grid), dim3(256), 0, s, a, it, n_items, args, \
                        counter);                                                                                \
     break;
+#define SPEC_LANE_CASE(NC)                                                                                        \
+  case NC:                                                                                                       \
+    hipLaunchKernelGGL((spec_lane_kernel<SPEC_NBP, NC, SPEC_WS>), dim3(grid), dim3(64), 0, s, a, it, n_items, args, \
+                       counter);                                                                                 \
+    break;
   switch (ncls) {
-    SPEC_CASE(4)
-    SPEC_CASE(5)
+    SPEC_LANE_CASE(4)
+    SPEC_LANE_CASE(5)
     SPEC_CASE(6)
     SPEC_CASE(8)
     SPEC_CASE(10)
@@ -23,6 +28,7 @@ hipError_t SPEC_NAME(int ncls, const DysonArgs& a, const void* items, int n_item
     default: return hipErrorInvalidValue;
   }
 #undef SPEC_CASE
+#undef SPEC_LANE_CASE
   return hipGetLastError();
 }
 }  // namespace dmft
