@@ -118,21 +118,29 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
   auto elem = [&](int r, int p) {
     return (int64_t)(((r >> 4) * NT + (p >> 4)) * 4 + ((r >> 2) & 3)) * 64 + (r & 3) * 16 + (p & 15);
   };
-  // eight elements per thread in flight
-  for (int i0 = tid; i0 < (nb - 1) * NP; i0 += 8 * nth) {
-    double x[8];
-    int64_t o[8];
+  // four elements of four frequency tiles per thread in flight
+  for (int i0 = tid; i0 < (nb - 1) * NP; i0 += 4 * nth) {
+    double x[4];
+    int64_t o[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 4; ++i) {
       const int idx = min(i0 + i * nth, (nb - 1) * NP - 1);
       o[i] = elem(2 * (idx / NP) + 1, idx % NP);
       x[i] = 0.0;
     }
-    for (int w = 0; w < n_wtiles; ++w)
+    for (int w0 = 0; w0 < n_wtiles; w0 += 4) {
+      double y[4][4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] += base[(int64_t)w * t_stride + o[i]];
+      for (int w = 0; w < 4; ++w)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 4; ++i) y[w][i] = base[(int64_t)min(w0 + w, n_wtiles - 1) * t_stride + o[i]];
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] += w0 + w < n_wtiles ? y[w][i] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
       if (i0 + i * nth < (nb - 1) * NP) (ULDS ? u[i0 + i * nth] : base[o[i]]) = x[i];
   }
   auto u_at = [&](int j, int p) { return ULDS ? u[j * NP + p] : base[elem(2 * j + 1, p)]; };
@@ -203,6 +211,7 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
     double t[PL], f = 0.0;
 #pragma unroll
     for (int i = 0; i < PL; ++i) t[i] = 0.0;
+#pragma unroll 2
     for (int w = 0; w < n_wtiles; ++w)
 #pragma unroll
       for (int i = 0; i < PL; ++i)
@@ -283,25 +292,25 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
       emit(v, x, f);
     }
   }
-  // fixed-order sums of the work-group (nth is a power of two)
+  // fixed-order sums of the work-group: lanes, then wavefronts
   double* red = reinterpret_cast<double*>(lds);
-  auto total = [&](double v) {
-    __syncthreads();
-    red[tid] = v;
-    __syncthreads();
-    for (int s = nth / 2; s > 0; s >>= 1) {
-      if (tid < s) red[tid] += red[tid + s];
-      __syncthreads();
-    }
-    return red[0];
-  };
-  tr = total(tr);
-  ncor = total(ncor);
-  hks = total(hks);
-  if (tid == 0) {
-    a.kscal[k * 3 + 0] = tr;
-    a.kscal[k * 3 + 1] = ncor;
-    a.kscal[k * 3 + 2] = hks;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    tr += __shfl_xor(tr, o);
+    ncor += __shfl_xor(ncor, o);
+    hks += __shfl_xor(hks, o);
+  }
+  __syncthreads();
+  if ((tid & 63) == 0) {
+    red[3 * (tid >> 6) + 0] = tr;
+    red[3 * (tid >> 6) + 1] = ncor;
+    red[3 * (tid >> 6) + 2] = hks;
+  }
+  __syncthreads();
+  if (tid < 3) {
+    double s = 0.0;
+    for (int w = 0; w < nth / 64; ++w) s += red[3 * w + tid];
+    a.kscal[k * 3 + tid] = s;
   }
 }
 
@@ -384,7 +393,7 @@ hipError_t epilogue_launch(const EpilogueArgs& a, size_t lds, double* nk_out, hi
   // 27 us with 64 threads, 20 with 256; 64 and 5: 60 with 1024, 46 with 512)
   int threads = 64;
   while (threads < 1024 && (threads < nbm * NC || (threads < 256 && threads < 4 * nbm * NC))) threads *= 2;
-  lds = lds < threads * sizeof(double) ? threads * sizeof(double) : lds;  // the final reduction's scratch
+  lds = lds < 48 * sizeof(double) ? 48 * sizeof(double) : lds;  // the final reduction's scratch
   hipLaunchKernelGGL((spec_epilogue_kernel<NC, ULDS>), dim3(a.nklist), dim3(threads), lds, s, a, nk_out);
   return hipGetLastError();
 }
