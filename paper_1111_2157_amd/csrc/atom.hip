@@ -22,29 +22,36 @@
 namespace dmft {
 namespace {
 
-constexpr int kAtomThreads = 256;
-
-template <int NT>
-__device__ __forceinline__ double atom_block_reduce(double v, double* red, bool take_min) {
-  const int t = threadIdx.x;
-  red[t] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (t < s) red[t] = take_min ? fmin(red[t], red[t + s]) : red[t] + red[t + s];
-    __syncthreads();
-  }
-  const double r = red[0];
-  __syncthreads();
-  return r;
+// Term M of this lane's row of 16, for all of the row.
+template <int M>
+__device__ __forceinline__ double row_term(double v) {
+  const int2 x = *reinterpret_cast<const int2*>(&v);
+  int2 y;
+  y.x = __builtin_amdgcn_update_dpp(0, x.x, 0x150 + M, 0xf, 0xf, true);  // row_newbcast
+  y.y = __builtin_amdgcn_update_dpp(0, x.y, 0x150 + M, 0xf, 0xf, true);
+  return *reinterpret_cast<const double*>(&y);
+}
+// Sum of the 16 terms of this lane's row, first to last.
+template <int M = 0>
+__device__ __forceinline__ double row_sum(double v, double s = 0.0) {
+  if constexpr (M < 16)
+    return row_sum<M + 1>(v, s + row_term<M>(v));
+  else
+    return s;
 }
 
-// One work-group per (atom, orbital a).
-__global__ void __launch_bounds__(kAtomThreads) hubbard1_kernel(int nc, const double* eps, const double* Uv,
-                                                                const double* muv, double beta, double wtol,
-                                                                double* sigma_inf, int32_t* npoles, double* pos,
-                                                                double* wgt, double* occ, double* e_u) {
-  __shared__ double red[kAtomThreads];
+// One work-group of NT threads (1024 from 11 orbitals on, else 256) per (atom, orbital
+// a).  Bound by latency: the passes over the 2^nc states, the reductions (one barrier
+// for all values, after sums within wavefronts) and the bisections, about 55 steps
+// each; a step's terms, one per lane of 16, are added in the order of the poles.  One atom
+// of 10 orbitals: 38 us with 256 threads, a barrier per halving of each of nc + 4 sums
+// and one lane per bisection, 28 us now; of 14: 168 and 76.
+template <int NT>
+__global__ void __launch_bounds__(NT) hubbard1_kernel(int nc, const double* eps, const double* Uv, const double* muv,
+                                                      double beta, double wtol, double* sigma_inf, int32_t* npoles,
+                                                      double* pos, double* wgt, double* occ, double* e_u) {
+  constexpr int kAtomThreads = NT, NW = NT / 64;
+  __shared__ double s_part[NW][20], s_sum[20];
   __shared__ double sP[16], sV[16];
   __shared__ int s_nr;
   const int atom = blockIdx.x / nc, a = blockIdx.x - atom * nc, t = threadIdx.x;
@@ -60,7 +67,13 @@ __global__ void __launch_bounds__(kAtomThreads) hubbard1_kernel(int nc, const do
   };
   double emin = INFINITY;
   for (int g = t; g < nstates; g += kAtomThreads) emin = fmin(emin, energy(g));
-  emin = atom_block_reduce<kAtomThreads>(emin, red, true);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) emin = fmin(emin, __shfl_xor(emin, o));
+  if ((t & 63) == 0) s_part[t >> 6][0] = emin;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) emin = fmin(emin, s_part[w][0]);
+  __syncthreads();
   const double ea = e[a] - mu;
   double z = 0.0, hu = 0.0, na = 0.0, acc[16];
 #pragma unroll
@@ -80,19 +93,40 @@ __global__ void __launch_bounds__(kAtomThreads) hubbard1_kernel(int nc, const do
       for (int j = 0; j < 16; ++j) acc[j] += (j == n) ? v : 0.0;
     }
   }
-  z = atom_block_reduce<kAtomThreads>(z, red, false);
-  hu = atom_block_reduce<kAtomThreads>(hu, red, false);
-  na = atom_block_reduce<kAtomThreads>(na, red, false);
 #pragma unroll
-  for (int j = 0; j < 16; ++j)
-    if (j < nc) acc[j] = atom_block_reduce<kAtomThreads>(acc[j], red, false);
+  for (int o = 32; o > 0; o >>= 1) {
+    z += __shfl_xor(z, o);
+    hu += __shfl_xor(hu, o);
+    na += __shfl_xor(na, o);
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      if (j < nc) acc[j] += __shfl_xor(acc[j], o);
+  }
+  if ((t & 63) == 0) {
+    double* sp = s_part[t >> 6];
+    sp[0] = z;
+    sp[1] = hu;
+    sp[2] = na;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) sp[3 + j] = acc[j];
+  }
+  __syncthreads();
+  if (t < 19) {
+    double s = 0.0;
+    for (int w = 0; w < NW; ++w) s += s_part[w][t];
+    s_sum[t] = s;
+  }
+  __syncthreads();
+  z = s_sum[0];
+  hu = s_sum[1];
+  na = s_sum[2];
   const int64_t o = (int64_t)atom * nc + a;
   if (t == 0) {
     // retained G poles in ascending position (equal positions merged: U = 0)
     int nr = 0;
     double vsum = 0.0;
     for (int j = 0; j < nc; ++j) {
-      const double v = acc[j] / z;
+      const double v = s_sum[3 + j] / z;
       if (!(v > wtol)) continue;
       const double p = ea + U * j;
       int at = nr;
@@ -123,24 +157,23 @@ __global__ void __launch_bounds__(kAtomThreads) hubbard1_kernel(int nc, const do
   }
   __syncthreads();
   const int nr = s_nr;
-  if (t < nr - 1) {
-    double lo = sP[t], hi = sP[t + 1];
+  // interval t / 16, pole t % 16 of its sum
+  if (t < 16 * (nr - 1)) {
+    const int iv = t >> 4, m = t & 15;
+    const double pm = sP[min(m, nr - 1)], vm = m < nr ? sV[m] : 0.0;
+    double lo = sP[iv], hi = sP[iv + 1];
     for (int it = 0; it < 200; ++it) {
       const double mid = 0.5 * (lo + hi);
       if (!(mid > lo && mid < hi)) break;
-      double gsum = 0.0;
-      for (int m = 0; m < nr; ++m) gsum += sV[m] / (mid - sP[m]);
-      if (gsum > 0.0) lo = mid;
+      if (row_sum(m < nr ? vm / (mid - pm) : 0.0) > 0.0) lo = mid;
       else hi = mid;
     }
-    const double q = 0.5 * (lo + hi);
-    double d = 0.0;
-    for (int m = 0; m < nr; ++m) {
-      const double r = q - sP[m];
-      d += sV[m] / (r * r);
+    const double q = 0.5 * (lo + hi), r = q - pm;
+    const double d = row_sum(m < nr ? vm / (r * r) : 0.0);
+    if (m == 0) {
+      pos[o * nc + iv] = q + mu;
+      wgt[o * nc + iv] = 1.0 / d;
     }
-    pos[o * nc + t] = q + mu;
-    wgt[o * nc + t] = 1.0 / d;
   }
   for (int j = t; j < nc; j += kAtomThreads)
     if (j >= nr - 1 || nr == 0) {
@@ -204,8 +237,12 @@ __global__ void hubbard1_poles_kernel(int nc, int nc_lat, int a0, const int32_t*
 hipError_t launch_hubbard1(int natoms, int nc, const double* eps, const double* U, const double* mu, double beta,
                            double wtol, double* sigma_inf, int32_t* npoles, double* pos, double* wgt, double* occ,
                            double* e_u, hipStream_t s) {
-  hipLaunchKernelGGL(hubbard1_kernel, dim3(natoms * nc), dim3(kAtomThreads), 0, s, nc, eps, U, mu, beta, wtol,
-                     sigma_inf, npoles, pos, wgt, occ, e_u);
+  if (nc > 10)
+    hipLaunchKernelGGL(hubbard1_kernel<1024>, dim3(natoms * nc), dim3(1024), 0, s, nc, eps, U, mu, beta, wtol,
+                       sigma_inf, npoles, pos, wgt, occ, e_u);
+  else
+    hipLaunchKernelGGL(hubbard1_kernel<256>, dim3(natoms * nc), dim3(256), 0, s, nc, eps, U, mu, beta, wtol,
+                       sigma_inf, npoles, pos, wgt, occ, e_u);
   return hipGetLastError();
 }
 
