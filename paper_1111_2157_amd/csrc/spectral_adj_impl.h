@@ -28,7 +28,7 @@
 // Measured, per k-point and frequency, with the frequency-at-a-time low-rank kernels in
 // brackets (256 k-points, 512 or 1024 frequencies): trace, 64 bands and 5 orbitals 1.4 ns
 // (6.1), 30 and 10 3.3 (4.8), 40 and 14 5.8 (6.8); scalar adjoint 2.1 (8.4), 4.4 (7.3)
-// and 8.7 (10); general product, 40 and 14, 18.3 (28.3).  At 40 bands and 14 orbitals the
+// and 8.1 (10); general product, 40 and 14, 17.0 (28.3).  At 40 bands and 14 orbitals the
 // products and inversions would take 4.7, 5.8 and 9.9 ns at full rate: the scalar
 // adjoint and the traces lose the rest to stage changes, and the general product to
 // fetching its 132 KB of straight-line code through the 64 KB instruction cache.  For
@@ -47,9 +47,10 @@ enum { SPEC_TRACE = 0, SPEC_ADJ = 1, SPEC_GEN = 2, SPEC_GEN_N = 3, SPEC_GEN_G = 
 template <int NBP, int NC, int WHAT>
 struct SpecAdjShared {
   using Dm = SpecDims<NBP, NC>;
-  // widest class, scalar adjoint: V' waits here for its use instead of in registers (80 spilled
-  // registers less; 48 bands, 14 orbitals: 11.1 to 8.2 ns per k-point and frequency)
-  static constexpr bool STASH = WHAT == SPEC_ADJ && NC >= 14;
+  // widest class: V' (scalar adjoint), or the Gbar part of Sigmabar (general product),
+  // waits here for its use instead of in registers (48 bands, 14 orbitals: 11.1 to 8.2 and
+  // 18.3 to 17.0 ns per k-point and frequency)
+  static constexpr bool STASH = (WHAT == SPEC_ADJ || WHAT == SPEC_GEN) && NC >= 14;
   double2 st[STASH ? 16 * NC * NC : 1];
   double2 xr[16 * Dm::NP];  // a moment of the group's frequencies, [n][nc^2] Hermitian pairs
   double2 dt[16 * Dm::DS];  // d_v(n)
@@ -123,7 +124,7 @@ __device__ __forceinline__ void spec_zero(double (&ar)[NC], double (&ai)[NC]) {
 // step(first), step(first + 1), ... while they return true, to N - 1 at most.  Unrolled: as a
 // loop around one copy of the product the code of the widest class fits the 64 KB
 // instruction cache, but every matrix stays alive through it and spills (general
-// product at 48 bands, 14 orbitals: 34.7 ns per k-point and frequency against 18.2).
+// product at 48 bands, 14 orbitals: 34.7 ns per k-point and frequency against 18.3).
 template <int N, class F>
 __device__ __forceinline__ void spec_steps(int first, const F& step) {
   bool on = true;
@@ -152,6 +153,11 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
   constexpr bool GEN = WHAT >= SPEC_GEN, has_n = WHAT == SPEC_GEN || WHAT == SPEC_GEN_N,
                  has_g = WHAT == SPEC_GEN || WHAT == SPEC_GEN_G;
   constexpr bool STASH = SpecAdjShared<NBP, NC, WHAT>::STASH;
+  // one copy of the inversion's code where the kernel is well past the 64 KB instruction
+  // cache and does not spill more for it (48 bands, 14 orbitals: scalar adjoint 86 to 75 KB,
+  // 2.27 to 2.13 ms for 256 k-points x 1024 frequencies; the traces gain nothing, the full
+  // product loses 3%)
+  constexpr bool ROLL = (WHAT == SPEC_ADJ || WHAT == SPEC_GEN_N || WHAT == SPEC_GEN_G) && NC >= 14;
   const int w = uniform_i(tid >> 6);
   const int n0 = wtile * a.wt, n1 = min(n0 + a.wt, a.nw);
   const int kk0 = ktile * a.kt, kk1 = min(kk0 + a.kt, a.nklist);
@@ -422,7 +428,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
           si[j] = i < nc && j < nc ? si[j] : 0.0;
         }
       }
-      spec_steps<2>(0, [&](int t) {
+      auto invert = [&](int t) {
         spec_sweep<NC>(gr, gi, i, pmin);
         if (t == 0) {
 #pragma unroll
@@ -432,8 +438,14 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
             gi[j] -= si[j];
           }
         }
-        return true;
-      });
+      };
+      if constexpr (ROLL) {
+#pragma clang loop unroll(disable)
+        for (int t = 0; t < 2; ++t) invert(t);
+      } else {
+        invert(0);
+        invert(1);
+      }
       if (nc < NC) {  // the identity of rows past nc must not count as part of Gl
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
@@ -483,7 +495,10 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
             }
             return true;
           });
-          spec_set<NC>(nr, ni, cr, ci);
+          if constexpr (STASH)
+            stash(cr, ci);
+          else
+            spec_set<NC>(nr, ni, cr, ci);
         }
       }
       // V = Gl Sigma', V' = Sigma' Gl (not for the traces), R = Sigma' + Sigma' V (in c; x = Sigma')
@@ -510,7 +525,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
         }
         if (WHAT == SPEC_TRACE || t == 2) return false;
         if constexpr (WHAT != SPEC_TRACE) {
-          if constexpr (STASH)
+          if constexpr (STASH && WHAT == SPEC_ADJ)
             stash(cr, ci);
           else
             spec_set<NC>(ur, ui, cr, ci);
@@ -645,6 +660,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
             if (t == 0) {  // L Q; L Q L' next, on top of the Gbar part
               spec_set<NC>(xr, xi, cr, ci);
               spec_set<NC>(br, bi, ur, ui);
+              if constexpr (STASH) unstash(nr, ni);
 #pragma unroll
               for (int j = 0; j < NC; ++j) {
                 cr[j] += nr[j];
