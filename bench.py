@@ -15,8 +15,8 @@ The JSON line also carries
     kernels of one pass, which run concurrently) from its average duration,
     measured with hipEvents captured into the graph around it and read after
     every replay of the timed region, against the MI355X FP64 peak; the
-    algorithmic count is the low-rank form's 8 (Nb^2 Nc + 2 Nb Nc^2 + 5 Nc^3)
-    flop per (k, i w_n) evaluation, summed over the ragged windows;
+    algorithmic count is that of the spectral form the kernels run, 12 Nb Nc^2 +
+    32 Nc^3 flop per (k, i w_n) evaluation, summed over the ragged windows;
   * "cpu_baseline": the FP64 CPU oracle timed on a bounded k-sample of every
     iterate on this host's cores;
   * "mu_search": Newton (dN/dmu from the adjoint trace pass) against
@@ -49,8 +49,8 @@ LDS_PEAK_TBPS = 256 * 128 * 2.4e9 / 1e12
 # recorded in the profile named below.  Valid only for the kernel sources it
 # was measured on (their SHA-256) and the same workload, form and item classes
 # (padded size, inversion columns, items); otherwise "traffic" is null.
-TRAFFIC_SOURCES = ["paper_1111_2157_amd/csrc/spectral_impl.h", "paper_1111_2157_amd/csrc/lowrank_impl.h",
-                   "paper_1111_2157_amd/csrc/dyson_impl.h"]
+TRAFFIC_SOURCES = ["paper_1111_2157_amd/csrc/spectral_impl.h", "paper_1111_2157_amd/csrc/spectral_lane_impl.h",
+                   "paper_1111_2157_amd/csrc/lowrank_impl.h", "paper_1111_2157_amd/csrc/dyson_impl.h"]
 TRAFFIC = {}
 
 
@@ -92,13 +92,23 @@ def flops_per_eval_lowrank(nb, nc):
     return 8.0 * (nb * nb * nc + 2.0 * nb * nc * nc + 5.0 * nc ** 3)
 
 
+def flops_per_eval_spectral(nb, nc):
+    """Algorithmic FP64 flops of one density-pass evaluation in the spectral
+    form, 12 Nb Nc^2 + 32 Nc^3: X = S D S^dag as Nc^2 real sums over the bands
+    with complex weights (4 Nb Nc^2), the 2 Nb - 1 sums over frequencies that
+    determine N(k) (8 Nb Nc^2), and the nc x nc work -- two inversions and
+    R = Sigma' + Sigma' Gl Sigma' (8 Nc^3 each product or inversion)."""
+    return 12.0 * nb * nc * nc + 32.0 * nc ** 3
+
+
 def density_kernel(ctx, nb, nc):
     """(kernel name, algorithmic flops per evaluation) of the density-pass
     kernel the context will run for this band window."""
     nbp = (nb + 15) // 16 * 16
     var = ctx.get_variant(0, nbp)
     if var == 136:
-        return ("spec_kernel<%d, %d orbitals> (low-rank, spectral form)" % (nbp, nc), flops_per_eval_lowrank(nb, nc))
+        return ("%s<%d, %d orbitals> (low-rank, spectral form)"
+                % ("spec_lane_kernel" if nc <= 5 else "spec_kernel", nbp, nc), flops_per_eval_spectral(nb, nc))
     if var >= 0 and var & 8:
         return "lr_kernel<%d, density> (low-rank, variant %d)" % (nbp, var), flops_per_eval_lowrank(nb, nc)
     if nbp == 64:
@@ -505,10 +515,10 @@ def mu_search(ctx, tune=True):
 
 
 def batched_flops(wl):
-    """Algorithmic low-rank flops of one batched pass, summed over the ragged windows."""
+    """Algorithmic flops of one batched pass (spectral form), summed over the ragged windows."""
     fl = 0.0
     for lat, sig in zip(wl.lattices, wl.sigmas):
-        fl += sig.nw * float(np.sum(flops_per_eval_lowrank(lat.nb.astype(float), float(lat.nc))))
+        fl += sig.nw * float(np.sum(flops_per_eval_spectral(lat.nb.astype(float), float(lat.nc))))
     return fl
 
 
@@ -650,7 +660,7 @@ def main():
                      "kernel_ms": m["kernel_s"] * 1e3, "timed_launches": m["launches"],
                      "dyson_section_ms_direct": m["direct_pass_ms"],
                      "flop_per_pass": m["flops"],
-                     "flop_count": "8 (Nb^2 Nc + 2 Nb Nc^2 + 5 Nc^3) per (k, i w_n), low-rank form"},
+                     "flop_count": "12 Nb Nc^2 + 32 Nc^3 per (k, i w_n), spectral form"},
         "batched_classes": m["classes"],
         "plan_seconds": m["plan_seconds"],
         "plan_tile_candidate": m["tile_candidate"],

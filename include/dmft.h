@@ -256,8 +256,8 @@ int dmft_batched_set_form(dmft_handle h, int form);
 int dmft_batched_form(dmft_handle h);
 
 /* Item classes of the current low-rank batched plan.  Its items are grouped
- * by padded band-window size and column count of the nc x nc inversions; each
- * class is one persistent launch.  The launches of a pass run either
+ * by padded band-window size and padded orbital count; each class is one
+ * persistent launch.  The launches of a pass run either
  * concurrently on side streams of the handle (joined back into the pass's
  * stream, also inside a captured graph) or one after another on the pass's
  * stream, whichever the plan timed faster, in the order (by cost, or the
@@ -278,8 +278,9 @@ int dmft_batched_set_concurrent(dmft_handle h, int mode);
 /* Tile candidates of the batched plan, in the order the plan times them: the
  * default k- and frequency tiles of every iterate, the k-tile halved, the
  * k-tile quartered, the frequency tile halved, and the k-tile quartered with
- * the frequency tile rounded down to a multiple of 48 (candidates equal to an
- * earlier one are left out of the list).  dmft_batched_set_tile_candidate(h,
+ * the frequency tile rounded down to a multiple of 48 (the low-rank kernels then
+ * round it up to whole groups of 16 frequencies, 64 up to five orbitals; candidates
+ * equal to an earlier one are left out of the list).  dmft_batched_set_tile_candidate(h,
  * k) makes later plans take candidate k without timing the others (for
  * reproducible profiles; an index past the plan's list, or -1, restores the
  * timing; DMFT_EINVAL below -1); dmft_batched_tile_candidate returns the
@@ -317,7 +318,12 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
  * of X is P Im(D) P^dag, negative definite for w_n > 0); other bits of a code
  * tune registers and occupancy only.  Code 40 (bits 3 and 5, 64-band windows,
  * density kind) runs the low-rank step on two-wavefront work-groups that
- * share the nc x nc part of the step. */
+ * share the nc x nc part of the step.  Code 136, the default of every kind and
+ * size, is the low-rank step with its sums over bands as real matrix products
+ * shared by many frequencies; it also takes zero rows of P(k) (an orbital without
+ * weight in the window); where rows may be linearly dependent, select a dense code
+ * (bit 3 clear).  With code 136 selected, kinds 1 to 3 of a lattice of
+ * more than 14 orbitals run the next variant of the list. */
 int dmft_variants(int kind, int nbp, int* out, int max);
 int dmft_set_variant(dmft_handle h, int kind, int nbp, int var);
 int dmft_get_variant(dmft_handle h, int kind, int nbp);

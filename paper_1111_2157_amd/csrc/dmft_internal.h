@@ -191,10 +191,10 @@ struct BatchItemHost {
 };
 hipError_t launch_batched(const void* items, int n_big, int n_small, const DysonArgs* args, int* counters,
                           int n_workgroups, hipStream_t s);
-// The low-rank form: one persistent kernel per class (padded size nbp, ncls
-// columns of the row-layout inversions, lr_nc_class) over items[0 .. n_items),
-// pulling from *counter (reset to 0 before the launch); grid work-groups of 64
-// threads, or for nbp = 64 128 (two-wavefront items) or 256 (class 5, four).
+// The low-rank form: one persistent spectral kernel per class (padded size nbp, ncls
+// padded orbitals, lr_nc_class) over items[0 .. n_items), pulling from *counter (reset
+// to 0 before the launch); grid work-groups of 256 threads, or of 64 where one lane
+// holds a matrix (spec_lane).
 int lr_nc_class(int nbp, int nc);
 int lr_class_wgs_per_cu(int nbp, int ncls);  // resident work-groups per CU of a class kernel
 hipError_t launch_lr_class(int nbp, int ncls, const void* items, int n_items, const DysonArgs* args, int* counter,

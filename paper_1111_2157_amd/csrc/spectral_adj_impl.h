@@ -419,6 +419,8 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
       lv2d* xb = spec_lds(&sh.xr[nl * NP]);
       double gr[NC], gi[NC];
       spec_pair_row<NC, false>(gr, gi, xb, ic);
+      const unsigned long long absent = spec_absent(xb[ic * NC + ic], i, nc);
+      if (absent) spec_leave_out<NC>(gr, gi, absent, l, 1.0);
       if (nc < NC) {
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
@@ -437,6 +439,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
             gr[j] -= sr[j];
             gi[j] -= si[j];
           }
+          if (absent) spec_leave_out<NC>(gr, gi, absent, l, 1.0);
         }
       };
       if constexpr (ROLL) {
@@ -446,6 +449,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
         invert(0);
         invert(1);
       }
+      if (absent) spec_leave_out<NC>(gr, gi, absent, l, 0.0);
       if (nc < NC) {  // the identity of rows past nc must not count as part of Gl
 #pragma unroll
         for (int j = 0; j < NC; ++j) {

@@ -41,13 +41,13 @@
 // full 16x16x4 products and B on uniform row operations.
 //
 // Measured (512 k-points, 2048 frequencies, per k-point and frequency; in brackets
-// the frequency-at-a-time low-rank kernels): 32 bands and 10 orbitals 2.46 ns (5.3),
-// 48 and 14 5.33 ns (10.2), 64 and 14 5.85 ns (13.5), 64 and 5 1.04 ns.  At
-// 48 and 14 the matrix products alone would take 2.4 ns at the rate of a large
-// product and the row operations of B 1.6; what bounds the rest is that neither unit
-// runs while the other does: with 256 KB of accumulators, row matrices and
-// projectors a SIMD holds one wavefront, so the LDS round trips between the stages
-// (0.6 ns) and the changes between the units are exposed.
+// the frequency-at-a-time low-rank kernels, tuned): 32 bands and 10 orbitals 2.46 ns
+// (5.3), 48 and 14 5.33 (10.2), 64 and 14 5.85.  At 48 and 14 the matrix products with
+// their padding would take 2.0 ns at full rate and the row operations of B 2.1; what
+// bounds the rest is that the two units do not run FP64 together and a SIMD holds one
+// wavefront (its row matrices, sums and operands fill the registers), so the LDS round
+// trips between the stages and the changes between the units are exposed.  Up to five
+// orbitals spectral_lane_impl.h takes over.
 #pragma once
 
 #include "lowrank_impl.h"
@@ -221,6 +221,25 @@ struct SpecStep {
 template <int NC>
 __device__ __forceinline__ void spec_sweep(double (&rr)[NC], double (&ri)[NC], int i, double& pmin) {
   SpecStep<0, NC>::run(rr, ri, i, pmin);
+}
+
+// Orbitals without weight in a k-point's window (a zero projector row: X has a zero row
+// and column) are left out of the inversions: their rows and columns are set to `diag`
+// times the identity.  own: this lane's diagonal element of X; the mask holds a bit per lane.
+__device__ __forceinline__ unsigned long long spec_absent(v2d own, int i, int nc) {
+  return __ballot(i < nc && own.x == 0.0 && own.y == 0.0);
+}
+template <int NC>
+__device__ __forceinline__ void spec_leave_out(double (&rr)[NC], double (&ri)[NC], unsigned long long absent, int lane,
+                                               double diag) {
+  const unsigned row = (unsigned)(absent >> (lane & 48)) & 0xffffu;
+  const int i = lane & 15;
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const bool z = (row >> i | row >> j) & 1u;
+    rr[j] = z ? (i == j ? diag : 0.0) : rr[j];
+    ri[j] = z ? 0.0 : ri[j];
+  }
 }
 
 // c_j += (row K's b_j) x + (row K + 1's b_j) y for JB columns (complex), and the
@@ -519,6 +538,7 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
         const int ic = min(i, NC - 1);
         lv2d* xb = spec_lds(&sh.xr[nl * NP]);
         double rr[NC], ri[NC];
+        v2d own;  // X_ii
         // row i of X from its Hermitian pairs (lanes past the NC rows repeat the last
         // one; nothing of theirs is read by another lane or kept)
         {
@@ -529,6 +549,7 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
             re[j] = xb[lo * NC + hi];
             im[j] = xb[hi * NC + lo];
           }
+          own = xb[ic * NC + ic];
           __builtin_amdgcn_sched_barrier(0);  // every read issued before the first is waited for
 #pragma unroll
           for (int j = 0; j < NC; ++j) {
@@ -544,6 +565,8 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
             ri[j] = i < nc ? ri[j] : 0.0;
           }
         }
+        const unsigned long long absent = spec_absent(own, i, nc);
+        if (absent) spec_leave_out<NC>(rr, ri, absent, l, 1.0);
         spec_sweep<NC>(rr, ri, i, pmin);
         if (nc < NC) {
 #pragma unroll
@@ -558,7 +581,9 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
           rr[j] -= sr[j];
           ri[j] -= si[j];
         }
+        if (absent) spec_leave_out<NC>(rr, ri, absent, l, 1.0);
         spec_sweep<NC>(rr, ri, i, pmin);
+        if (absent) spec_leave_out<NC>(rr, ri, absent, l, 0.0);
         SpecGl<NC> gl;
         gl.p = (gv2d*)a.xs + ((int64_t)(a.ktile_base + ktile) * n4_all + min((ng >> 2) + w, n4_all - 1)) * (4 * NC * NC) +
                (nl & 3) * NC + ic;

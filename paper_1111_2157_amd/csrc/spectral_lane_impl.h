@@ -198,6 +198,22 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
               gi[j][i] = re.y - im.x;
             }
           }
+        // orbitals without weight in this window (see spec_absent; the same in every lane)
+        int absent = 0;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) absent |= i < nc && gr[i][i] == 0.0 && gi[i][i] == 0.0 ? 1 << i : 0;
+        absent = __builtin_amdgcn_readfirstlane(absent);
+        auto leave_out = [&](double diag) {
+#pragma unroll
+          for (int i = 0; i < NC; ++i)
+#pragma unroll
+            for (int j = 0; j < NC; ++j)
+              if ((absent >> i | absent >> j) & 1) {
+                gr[i][j] = i == j ? diag : 0.0;
+                gi[i][j] = 0.0;
+              }
+        };
+        if (absent) leave_out(1.0);
         // orbitals past nc and frequencies past the tile: X = 1, Sigma' = 0
         if (!whole) {
 #pragma unroll
@@ -229,7 +245,9 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
             gr[i][j] -= sr[i][j];
             gi[i][j] -= si[i][j];
           }
+        if (absent) leave_out(1.0);
         lane_inverse<NC>(gr, gi, pmin);
+        if (absent) leave_out(0.0);
         double chk = 0.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i)
