@@ -51,7 +51,14 @@ LDS_PEAK_TBPS = 256 * 128 * 2.4e9 / 1e12
 # (padded size, inversion columns, items); otherwise "traffic" is null.
 TRAFFIC_SOURCES = ["paper_1111_2157_amd/csrc/spectral_impl.h", "paper_1111_2157_amd/csrc/spectral_lane_impl.h",
                    "paper_1111_2157_amd/csrc/lowrank_impl.h", "paper_1111_2157_amd/csrc/dyson_impl.h"]
-TRAFFIC = {}
+TRAFFIC = {
+    ("batched-Nk4096-Nb20..64-x8-Nw2048", "low-rank",
+     ((32, 5, 4664), (32, 14, 2336), (48, 5, 5820), (48, 14, 2912), (64, 5, 5900), (64, 14, 2952))): {
+        "bytes": 218.03e9,  # FETCH 92.9 GB + WRITE 125.1 GB
+        "profile": "profiles/batched_cfg4.md",
+        "sources_sha256": "9f0def504012fa2c3484ed7e7497c2f7a518b99ffca1ffba07974807e78254e9",
+    },
+}
 
 
 def class_key(classes):

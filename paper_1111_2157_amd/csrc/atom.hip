@@ -40,7 +40,7 @@ __device__ __forceinline__ double row_sum(double v, double s = 0.0) {
     return s;
 }
 
-// One work-group of NT threads (1024 from 11 orbitals on, else 256) per (atom, orbital
+// One work-group of NT threads (256 or 1024, see launch_hubbard1) per (atom, orbital
 // a).  Bound by latency: the passes over the 2^nc states, the reductions (one barrier
 // for all values, after sums within wavefronts) and the bisections, about 55 steps
 // each; a step's terms, one per lane of 16, are added in the order of the poles.  One atom
@@ -237,7 +237,9 @@ __global__ void hubbard1_poles_kernel(int nc, int nc_lat, int a0, const int32_t*
 hipError_t launch_hubbard1(int natoms, int nc, const double* eps, const double* U, const double* mu, double beta,
                            double wtol, double* sigma_inf, int32_t* npoles, double* pos, double* wgt, double* occ,
                            double* e_u, hipStream_t s) {
-  if (nc > 10)
+  // 1024 threads where that leaves no work-group waiting: 24 atoms of 14 orbitals 136 us
+  // (188 with 256), 64 of them 266 (240)
+  if (nc > 10 && natoms * nc <= 512)
     hipLaunchKernelGGL(hubbard1_kernel<1024>, dim3(natoms * nc), dim3(1024), 0, s, nc, eps, U, mu, beta, wtol,
                        sigma_inf, npoles, pos, wgt, occ, e_u);
   else
