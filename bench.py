@@ -56,7 +56,14 @@ TRAFFIC = {
      ((32, 5, 4664), (32, 14, 2336), (48, 5, 5820), (48, 14, 2912), (64, 5, 5900), (64, 14, 2952))): {
         "bytes": 218.03e9,  # FETCH 92.9 GB + WRITE 125.1 GB
         "profile": "profiles/batched_cfg4.md",
-        "sources_sha256": "9f0def504012fa2c3484ed7e7497c2f7a518b99ffca1ffba07974807e78254e9",
+        "sources_sha256": "fd901cb1d1e17eab6bc1571e515eccb9fee97b20f5f3f36b3f3929ecf6203c73",
+    },
+    # the plan's quarter k-tile with the default frequency tile
+    ("batched-Nk4096-Nb20..64-x8-Nw2048", "low-rank",
+     ((32, 5, 4664), (32, 14, 1168), (48, 5, 5820), (48, 14, 1456), (64, 5, 5900), (64, 14, 1476))): {
+        "bytes": 213.81e9,  # FETCH 91.6 GB + WRITE 122.2 GB
+        "profile": "profiles/batched_cfg4.md",
+        "sources_sha256": "fd901cb1d1e17eab6bc1571e515eccb9fee97b20f5f3f36b3f3929ecf6203c73",
     },
 }
 

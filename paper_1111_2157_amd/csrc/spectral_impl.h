@@ -192,7 +192,6 @@ struct SpecStep {
   static __device__ __forceinline__ void block(double (&rr)[NC], double (&ri)[NC], double nr, double ni) {
     double t[N];
     int z;  // unused: opens the output list
-    if constexpr (N == 3) SPEC_ELIM(3);
     if constexpr (N == 4) SPEC_ELIM(4);
     if constexpr (N == 5) SPEC_ELIM(5);
     if constexpr (N == 6) SPEC_ELIM(6);
@@ -288,7 +287,7 @@ __device__ __forceinline__ void row_mac(double (&cr)[JB], double (&ci)[JB], cons
 // Column block of the row-layout products.
 template <int NC>
 constexpr int spec_jb() {
-  return NC == 16 || NC == 8 || NC == 4 ? 4 : NC <= 6 ? NC : NC / 2;
+  return NC == 16 || NC == 8 ? 4 : NC <= 6 ? NC : NC / 2;
 }
 
 // One column block of V = Gl Sigma' and R = Sigma' + Sigma' V, R to LDS; around it
