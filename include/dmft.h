@@ -322,8 +322,10 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
  * size, is the low-rank step with its sums over bands as real matrix products
  * shared by many frequencies; it also takes zero rows of P(k) (an orbital without
  * weight in the window); where rows may be linearly dependent, select a dense code
- * (bit 3 clear).  With code 136 selected, kinds 1 to 3 of a lattice of
- * more than 14 orbitals run the next variant of the list. */
+ * (bit 3 clear).  With code 136 selected,
+ * kinds 1 to 3 of a lattice of more than 14 orbitals run the next variant of the
+ * list, and so does the density kind, unless the code was set or tuned, for more
+ * than 14 orbitals in windows of up to 16 bands. */
 int dmft_variants(int kind, int nbp, int* out, int max);
 int dmft_set_variant(dmft_handle h, int kind, int nbp, int var);
 int dmft_get_variant(dmft_handle h, int kind, int nbp);
