@@ -291,7 +291,8 @@ int dmft_batched_tile_candidate(dmft_handle h);
 /* Autotuner: times every compiled kernel variant of the three kinds (density
  * pass, trace pass, fused scalar adjoint) that fits this shape on the
  * handle's GPU, with a few frequency-tile sizes, after checking that each one
- * reproduces the reference variant to 1e-11, and caches the fastest in the
+ * reproduces a dense variant (kind 2 at 64 bands, which has none: the first
+ * candidate) to 1e-11 and flags no error, and caches the fastest in the
  * handle (used by all later calls of that shape).  best_out (HOST, may be
  * NULL) receives a short description. */
 int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, double mu,

@@ -1166,20 +1166,13 @@ int find_mu(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, int t
   return DMFT_OK;
 }
 
-
-
-
-
-
-
-
-
-
-
-// Autotuner: for each kind (density pass, trace pass) time every instantiated
-// kernel variant of the shape's largest padded size on a few frequency-tile
-// sizes, after checking that each candidate reproduces the default candidate
-// (G_loc and the scalars, or N and dN/dmu, to 1e-11 relative); keep the fastest.
+// Autotuner: for each kind (density pass, trace pass, scalar adjoint) time every
+// instantiated kernel variant of the shape's largest padded size on a few
+// frequency-tile sizes, after checking that each candidate reproduces the
+// reference (G_loc and the scalars, or N and dN/dmu, to 1e-11 relative) and
+// leaves the error word clear; keep the fastest.  The reference is a dense code,
+// which takes any projectors; the scalar adjoint at 64 bands has none, there it
+// is the first candidate that fits.
 int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, double mu, void* ws,
                   size_t ws_bytes, hipStream_t stream, char* best_out, size_t best_len) {
   int r = check_shapes(h, lat, sig);
@@ -1191,12 +1184,20 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
   hipEvent_t e0, e1;
   HIPCHK(h, hipEventCreate(&e0));
   HIPCHK(h, hipEventCreate(&e1));
+  // the error word as it was, with what the references flag; a candidate's own bits only reject it
+  size_t err_at = 0;
+  int word = 0;
   for (int kind : {KIND_DENSITY, KIND_TRACE, KIND_ADJOINT}) {
     Layout L0;
     r = make_layout(h, lat, sig, L0, kind);
     if (r) return r;
     r = check_ws(h, L0, ws, ws_bytes);
     if (r) return r;
+    if (kind == KIND_DENSITY) {
+      err_at = L0.err;  // the same in every layout
+      HIPCHK(h, hipStreamSynchronize(stream));
+      HIPCHK(h, hipMemcpy(&word, w + err_at, sizeof(int), hipMemcpyDeviceToHost));
+    }
     int nbp = L0.nbp_max, nk = lat->nk, nw = sig->nw, nc = lat->nc;
     int vars[16];
     int nv = dyson_variants(nbp, kind, vars, 16);
@@ -1225,52 +1226,82 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
     std::vector<double> ref(nres), got(nres);
     bool have_ref = false;
     double best_ms = 1e300;
+    int dense = -1;
+    for (int vi = nv - 1; vi >= 0; --vi)
+      if (!(vars[vi] & 8)) dense = vars[vi];
     const bool spec0 = vars[0] == kSpectralVariant && (kind == KIND_DENSITY || spec_adj_fits(nc));
     Tile best_tile = spec0 ? sbase : base;
     int best_var = vars[0];
     char key[32];
     snprintf(key, sizeof key, "%d/%d", kind, nbp);
+    // one candidate: its results (to res), the time of a pass and the bits it left in the
+    // error word; skipped (fits = false) where it does not fit the workspace
+    auto measure = [&](int var, const Tile& t, int reps, std::vector<double>& res, float& ms, int& err,
+                       bool& fits) -> int {
+      h->tvar[key] = var;
+      Layout L;
+      int r = make_layout(h, lat, sig, L, kind, &t);
+      if (r) return r;
+      fits = check_ws(h, L, ws, ws_bytes) == DMFT_OK;
+      if (!fits) return DMFT_OK;
+      r = upload_meta(h, L, w, stream, true);
+      if (r) return r;
+      double* out = (double*)(w + (have_ref ? L.tune_b : L.tune_a));
+      auto run = [&]() -> int {
+        if (kind == KIND_DENSITY)
+          return density_impl(h, lat, sig, L, w, mu, nullptr, 2, nullptr, out, out + (size_t)nw * nc * nc * 2,
+                              stream);
+        if (kind == KIND_ADJOINT) return ntot_vjp_impl(h, lat, sig, L, w, mu, 2, out + 2, out, stream);
+        return ntot_impl(h, lat, sig, L, w, mu, nullptr, 2, out, stream);
+      };
+      const int zero = 0;
+      HIPCHK(h, hipMemcpy(w + L.err, &zero, sizeof(int), hipMemcpyHostToDevice));
+      r = run();
+      if (r) return r;
+      ms = 1e30f;
+      for (int rep = 0; rep < reps; ++rep) {
+        HIPCHK(h, hipEventRecord(e0, stream));
+        r = run();
+        if (r) return r;
+        HIPCHK(h, hipEventRecord(e1, stream));
+        HIPCHK(h, hipEventSynchronize(e1));
+        float m = 0.f;
+        HIPCHK(h, hipEventElapsedTime(&m, e0, e1));
+        ms = std::min(ms, m);
+      }
+      HIPCHK(h, hipStreamSynchronize(stream));
+      HIPCHK(h, hipMemcpy(res.data(), out, nres * sizeof(double), hipMemcpyDeviceToHost));
+      HIPCHK(h, hipMemcpy(&err, w + L.err, sizeof(int), hipMemcpyDeviceToHost));
+      return DMFT_OK;
+    };
+    float ms = 0.f;
+    int err = 0;
+    bool fits = false;
+    if (dense >= 0)
+      for (size_t i = 0; i < tiles.size() && !have_ref; ++i) {
+        r = measure(dense, tiles[i], 0, ref, ms, err, fits);
+        if (r) return r;
+        have_ref = fits;
+        if (fits) word |= err;
+      }
     for (int vi = 0; vi < nv; ++vi) {
       if (vars[vi] == kLowrankP3Variant && !lowrank_p3_fits(nbp, nc)) continue;
       if (vars[vi] == kSpectralVariant && kind != KIND_DENSITY && !spec_adj_fits(nc)) continue;
-      h->tvar[key] = vars[vi];
       for (const Tile& t : vars[vi] == kSpectralVariant ? stiles : tiles) {
-        Layout L;
-        r = make_layout(h, lat, sig, L, kind, &t);
+        r = measure(vars[vi], t, 2, have_ref ? got : ref, ms, err, fits);
         if (r) return r;
-        if (check_ws(h, L, ws, ws_bytes)) continue;
-        r = upload_meta(h, L, w, stream, true);
-        if (r) return r;
-        double* out = (double*)(w + (have_ref ? L.tune_b : L.tune_a));
-        auto run = [&]() -> int {
-          if (kind == KIND_DENSITY)
-            return density_impl(h, lat, sig, L, w, mu, nullptr, 2, nullptr, out, out + (size_t)nw * nc * nc * 2,
-                                stream);
-          if (kind == KIND_ADJOINT) return ntot_vjp_impl(h, lat, sig, L, w, mu, 2, out + 2, out, stream);
-          return ntot_impl(h, lat, sig, L, w, mu, nullptr, 2, out, stream);
-        };
-        r = run();
-        if (r) return r;
-        float ms = 1e30f;
-        for (int rep = 0; rep < 2; ++rep) {
-          HIPCHK(h, hipEventRecord(e0, stream));
-          r = run();
-          if (r) return r;
-          HIPCHK(h, hipEventRecord(e1, stream));
-          HIPCHK(h, hipEventSynchronize(e1));
-          float m = 0.f;
-          HIPCHK(h, hipEventElapsedTime(&m, e0, e1));
-          ms = std::min(ms, m);
-        }
-        HIPCHK(h, hipMemcpy(have_ref ? got.data() : ref.data(), out, nres * sizeof(double), hipMemcpyDeviceToHost));
-        bool ok = true;
+        if (!fits) continue;
+        bool ok = err == 0;
         if (have_ref) {
           double dn = 0.0, rn = 0.0;
           for (size_t i = 0; i < nres; ++i) {
+            ok = ok && std::isfinite(got[i]) && std::isfinite(ref[i]);
             dn = std::max(dn, std::fabs(got[i] - ref[i]));
             rn = std::max(rn, std::fabs(ref[i]));
           }
-          ok = std::isfinite(dn) && dn <= 1e-11 * std::max(rn, 1e-300);
+          ok = ok && dn <= 1e-11 * std::max(rn, 1e-300);
+        } else {
+          word |= err;
         }
         have_ref = true;
         char line[160];
@@ -1291,6 +1322,7 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
              best_tile.wt, best_ms);
     report += line;
   }
+  HIPCHK(h, hipMemcpy(w + err_at, &word, sizeof(int), hipMemcpyHostToDevice));
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (best_out && best_len) {
