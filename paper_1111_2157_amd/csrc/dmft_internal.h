@@ -31,7 +31,7 @@ constexpr int spec_wgs_per_cu(int nbp, int ncls) {
   if (spec_lane(ncls)) return 4;
   const int nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
   const int regs = nr * nt * 2 + 8 * ncls + 110 + (ncls <= 6 ? nbp / 2 : 0);
-  const int lds = 16 * nt * 16 * 16 + 4 * 256 + 2 * 16 * (nbp + 4) * 16 + nbp * 17 * 8 + nbp * 20 + 64 +
+  const int lds = 16 * nt * 16 * 16 + 4 * 256 + 2 * 16 * (nbp + 4) * 16 + nbp * 17 * 8 + nbp * 20 + 64 + 16 * ncls * ncls +
                   (ncls <= 6 ? 16 : 2 * ncls * (nbp + 1) * 16);
   const int by_regs = regs <= 176 ? 3 : regs <= 256 ? 2 : 1;
   const int by_lds = 163840 / lds;

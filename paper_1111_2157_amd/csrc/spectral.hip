@@ -40,12 +40,6 @@ hipError_t launch_spectral(int nbp, int ncls, const DysonArgs& a, const void* it
 
 namespace {
 
-// Sum over the four lanes of a quad.
-__device__ __forceinline__ double quad_sum(double v) {
-  v += __builtin_amdgcn_update_dpp(0.0, v, 0xB1, 0xf, 0xf, true);  // quad_perm 1, 0, 3, 2
-  return v + __builtin_amdgcn_update_dpp(0.0, v, 0x4E, 0xf, 0xf, true);  // quad_perm 2, 3, 0, 1
-}
-
 // N(k) of one k-point (one work-group) from the sums of spec_kernel:
 //   N = 1/2 - (beta/4) M1 + (1/beta) (F + 2 s2 M1),   F = sum_n (G + G^dag),
 //   F[v][v'] = [v = v'] sum_n 2 Re d_v + S_v^dag H(v, v') S_v',
@@ -265,8 +259,8 @@ __global__ void __launch_bounds__(1024) spec_epilogue_kernel(EpilogueArgs a, dou
           s.x += x.x * re + x.y * im;
           s.y += x.x * im - x.y * re;
         }
-        s.x = quad_sum(s.x);
-        s.y = quad_sum(s.y);
+        s.x = spec_quad_sum(s.x);
+        s.y = spec_quad_sum(s.y);
         if (qd == 0) wv[v * NC + b] = s;
       }
     }

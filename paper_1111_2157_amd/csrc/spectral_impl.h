@@ -120,7 +120,9 @@ struct SpecShared {
   double sd[NBP * 17];            // running sum of Re d_v per (band, frequency of the group)
   double eps[NBP];                // sorted band energies
   unsigned long long key[NBP];
+  double2 lf[NC * NC];            // L of S = L Q where the rows of S are oblique
   int rank[NBP];
+  int oblique;
   int next;
 };
 
@@ -150,6 +152,162 @@ __device__ __forceinline__ int spec_rank(const unsigned long long* key, int v, i
 __device__ __forceinline__ int spec_here(int i) {
   asm volatile("" : "+v"(i));
   return i;
+}
+
+// ---- oblique projector rows.  X^-1 - Sigma' loses the square of the condition number of S:
+// rows that are nearly (or exactly) dependent would leave it no digits.  S = L Q with
+// orthonormal (or zero) rows of Q and lower triangular L takes that number out of the
+// inversions, X = Q D Q^dag then being as well conditioned as for orthonormal projectors:
+//   Gl = L (X^-1 - L^dag Sigma' L)^-1 L^dag,
+// four more row products per evaluation, so only a k-point whose rows ask for it is
+// taken this way.  (6 to 48 bands, one singular value of S from 1 down to 1e-13, or equal
+// rows, beta 40 and 1000: G_loc within 2e-12 of 80-bit values and N(k) within 5e-13, as the
+// band-window inversion (2e-13, 8e-14); with S itself 1e-8 at a singular value of 1e-4.
+// All k-points oblique against none: density passes of 64 k-points, 12 bands, 5 orbitals,
+// 256 frequencies 76 us against 50, of 256, 48, 14, 512 1.72 ms against 0.86; the band-window
+// kernels 158 us and 7.9 ms.)
+
+// Whether two rows ask for it, by the real or imaginary part z of their product and their
+// squared norms, or (same) one row by its own: past |z| = |x| |y| / (3 nc) (below it the
+// Gram matrix of the normalised rows has its eigenvalues in 1/2 .. 3/2), or at a norm far
+// from 1 (a pivot p leaves its row about max(1, |p|) roundings, see SpecStep).  Zero rows
+// do not (spec_absent), nor do NaN (they reach the error word).
+__device__ __forceinline__ bool spec_oblique(double xx, double yy, double z, bool same, int nc) {
+  return same ? xx > 0.0 && !(xx >= 1e-4 && xx <= 1e4) : z * z * (9.0 * nc * nc) > xx * yy;
+}
+
+// Sums over the four lanes of a quad, and over a wavefront.
+__device__ __forceinline__ double spec_quad_sum(double v) {
+  v += __builtin_amdgcn_update_dpp(0.0, v, 0xB1, 0xf, 0xf, true);  // quad_perm 1, 0, 3, 2
+  return v + __builtin_amdgcn_update_dpp(0.0, v, 0x4E, 0xf, 0xf, true);  // quad_perm 2, 3, 0, 1
+}
+__device__ __forceinline__ double spec_wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// S = L Q by one wavefront, a band per lane: Gram-Schmidt, every row twice against all
+// before it.  s: the rows in LDS (stride ss, zeros past the window), replaced by Q; a row
+// within 3.6e-15 of the span of those before it gets a zero row of Q.
+template <int NBP, int NC>
+__device__ __forceinline__ void spec_orthonormal(double2* s, int ss, double2* lf, int nc, int lane) {
+  const int j = lane & 15, h = lane >> 4;
+#pragma clang loop unroll(disable)
+  for (int i = 0; i < NC; ++i) {
+    double2 r = lane < NBP && i < nc ? s[i * ss + lane] : make_double2(0.0, 0.0);
+    const double n0 = spec_wave_sum(r.x * r.x + r.y * r.y);
+    double2 l = make_double2(0.0, 0.0);  // element (i, j) of L
+#pragma clang loop unroll(disable)
+    for (int pass = 0; pass < 2 && i < nc; ++pass) {
+      double2 c = make_double2(0.0, 0.0);  // row j of Q against this one
+      if (j < i)
+#pragma clang loop unroll(disable)
+        for (int v = h; v < NBP; v += 4) {
+          const double2 a = s[j * ss + v], b = s[i * ss + v];
+          c.x += a.x * b.x + a.y * b.y;
+          c.y += a.x * b.y - a.y * b.x;
+        }
+      c.x += __shfl_xor(c.x, 16);
+      c.y += __shfl_xor(c.y, 16);
+      c.x += __shfl_xor(c.x, 32);
+      c.y += __shfl_xor(c.y, 32);
+      l.x += c.x;
+      l.y += c.y;
+#pragma clang loop unroll(disable)
+      for (int m = 0; m < i; ++m) {
+        const double cx = __shfl(c.x, m), cy = __shfl(c.y, m);
+        const double2 a = s[m * ss + min(lane, NBP - 1)];
+        r.x -= cx * a.x - cy * a.y;
+        r.y -= cx * a.y + cy * a.x;
+      }
+      wave_sync();
+      if (lane < NBP) s[i * ss + lane] = r;
+      wave_sync();
+    }
+    const double n = spec_wave_sum(lane < NBP ? r.x * r.x + r.y * r.y : 0.0);
+    const bool drop = n <= 1.3e-29 * n0 && __builtin_isfinite(n0);  // not for NaN or infinity: they stay visible
+    const double len = drop ? 0.0 : __builtin_sqrt(n), inv = drop ? 0.0 : 1.0 / len;
+    if (lane < NBP && i < nc) s[i * ss + lane] = make_double2(r.x * inv, r.y * inv);
+    if (lane < NC) lf[i * NC + lane] = i < nc && j < i ? l : make_double2(i < nc && j == i ? len : 0.0, 0.0);
+    wave_sync();
+  }
+}
+
+// m = L^dag m L and m = L m L^dag in place, m in LDS: this lane's rows i0 .. i1 - 1, then
+// (the matrix's other lanes done with theirs) columns.  In loops over LDS, because they
+// run for oblique rows only: in registers they cost the kernels around them up to 110 VGPRs.
+template <int NC>
+__device__ __forceinline__ void spec_inner(lv2d* m, const lv2d* lf, int i0, int i1) {
+#pragma clang loop unroll(disable)
+  for (int i = i0; i < i1; ++i)
+#pragma clang loop unroll(disable)
+    for (int j = 0; j < NC; ++j) {
+      v2d s = (v2d){0.0, 0.0};
+#pragma clang loop unroll(disable)
+      for (int n = j; n < NC; ++n) {
+        const v2d x = m[i * NC + n], l = lf[n * NC + j];
+        s += (v2d){x.x * l.x - x.y * l.y, x.x * l.y + x.y * l.x};
+      }
+      m[i * NC + j] = s;
+    }
+  wave_sync();
+#pragma clang loop unroll(disable)
+  for (int i = i0; i < i1; ++i)
+#pragma clang loop unroll(disable)
+    for (int j = 0; j < NC; ++j) {
+      v2d s = (v2d){0.0, 0.0};
+#pragma clang loop unroll(disable)
+      for (int n = j; n < NC; ++n) {
+        const v2d x = m[n * NC + i], l = lf[n * NC + j];
+        s += (v2d){x.x * l.x + x.y * l.y, x.y * l.x - x.x * l.y};
+      }
+      m[j * NC + i] = s;
+    }
+  wave_sync();
+}
+template <int NC>
+__device__ __forceinline__ void spec_outer(lv2d* m, const lv2d* lf, int i0, int i1) {
+#pragma clang loop unroll(disable)
+  for (int i = i0; i < i1; ++i)
+#pragma clang loop unroll(disable)
+    for (int j = NC - 1; j >= 0; --j) {
+      v2d s = (v2d){0.0, 0.0};
+#pragma clang loop unroll(disable)
+      for (int n = 0; n <= j; ++n) {
+        const v2d x = m[i * NC + n], l = lf[j * NC + n];
+        s += (v2d){x.x * l.x + x.y * l.y, x.y * l.x - x.x * l.y};
+      }
+      m[i * NC + j] = s;
+    }
+  wave_sync();
+#pragma clang loop unroll(disable)
+  for (int i = i0; i < i1; ++i)
+#pragma clang loop unroll(disable)
+    for (int j = NC - 1; j >= 0; --j) {
+      v2d s = (v2d){0.0, 0.0};
+#pragma clang loop unroll(disable)
+      for (int n = 0; n <= j; ++n) {
+        const v2d x = m[n * NC + i], l = lf[j * NC + n];
+        s += (v2d){x.x * l.x - x.y * l.y, x.x * l.y + x.y * l.x};
+      }
+      m[j * NC + i] = s;
+    }
+  wave_sync();
+}
+// A row-layout matrix into LDS and out of it (lanes past the NC rows leave nothing and
+// repeat the last one).
+template <int NC>
+__device__ __forceinline__ void spec_put_row(lv2d* m, int i, const double (&ar)[NC], const double (&ai)[NC]) {
+  wave_sync();
+  if (i < NC) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+      m[i * NC + j] = (v2d){ar[j], ai[j]};
+    }
+  }
+  wave_sync();
 }
 
 // ---- row layout: lane 16 g + i holds row i of matrix g.  Both helpers below are
@@ -350,6 +508,46 @@ struct SpecGl {
   }
 };
 
+// Looks the staged rows of S over (four lanes to an unordered pair of them) and where they
+// are oblique puts Q in their place: sh.oblique.
+template <int NBP, int NC, class Sh>
+__device__ __forceinline__ void spec_rows_check(Sh& sh, int nc, int tid) {
+  using Dm = typename Sh::Dm;
+  double2* const s = Dm::PREG ? sh.xr : sh.sp;
+  constexpr int SS = Dm::PREG ? NBP : Dm::SS;
+#pragma clang loop unroll(disable)
+  for (int pr = tid >> 2; pr < nc * (nc / 2 + 1); pr += 64) {
+    const int d = pr / nc, i = pr - d * nc, j = i + d < nc ? i + d : i + d - nc;
+    double xx = 0.0, yy = 0.0, re = 0.0, im = 0.0;
+#pragma unroll 4
+    for (int c = 0; c < NBP; c += 4) {
+      const double2 x = s[i * SS + c + (tid & 3)], y = s[j * SS + c + (tid & 3)];
+      xx = __builtin_fma(x.x, x.x, __builtin_fma(x.y, x.y, xx));
+      yy = __builtin_fma(y.x, y.x, __builtin_fma(y.y, y.y, yy));
+      re = __builtin_fma(x.x, y.x, __builtin_fma(x.y, y.y, re));
+      im = __builtin_fma(x.x, y.y, __builtin_fma(-x.y, y.x, im));
+    }
+    xx = spec_quad_sum(xx);
+    yy = spec_quad_sum(yy);
+    re = spec_quad_sum(re);
+    im = spec_quad_sum(im);
+    if (spec_oblique(xx, yy, re, i == j, nc) || (i != j && spec_oblique(xx, yy, im, false, nc))) sh.oblique = 1;
+  }
+  __syncthreads();
+  if (!uniform_i(sh.oblique)) return;
+  if (tid < 64) spec_orthonormal<NBP, NC>(s, SS, sh.lf, nc, tid);
+  __syncthreads();
+  if constexpr (!Dm::PREG) {
+#pragma clang loop unroll(disable)
+    for (int idx = tid; idx < NC * NBP; idx += 256) {
+      const int al = idx / NBP, v = idx - al * NBP;
+      const double2 x = sh.sp[al * SS + v];
+      sh.sp[(NC + al) * SS + v] = make_double2(x.y, -x.x);
+    }
+    __syncthreads();
+  }
+}
+
 // WS: the sums are wanted (N(k)); else G_loc only.
 template <int NBP, int NC, bool WS>
 __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wtile, SpecShared<NBP, NC>& sh, int tid) {
@@ -383,6 +581,7 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
     // ---- bands sorted by energy, projector columns in that order (staged over xr)
     __syncthreads();
     if (tid < NBP) sh.key[tid] = tid < nb ? spec_key(eps[tid]) : ~0ull;
+    if (tid == 0) sh.oblique = 0;
     __syncthreads();
     if (tid < NBP) {
       const int r = tid < nb ? spec_rank(sh.key, tid, nb) : tid;
@@ -401,6 +600,7 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
       }
     }
     __syncthreads();
+    spec_rows_check<NBP, NC>(sh, nc, tid);
     // P_v of this wavefront's tiles as B operand: band 4 c + q, column 16 t + c16
     // = (al, be): Re S_al S_be^* for al <= be, else Im S_be S_al^*
     double p[Dm::PREG ? TPW : 1][Dm::PREG ? NBP / 4 : 1];
@@ -446,6 +646,11 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
       for (int t = 0; t < CT; ++t) acc[r][t] = (v4d){0.0, 0.0, 0.0, 0.0};
 
     int cur = 0;
+    // the frequencies, for oblique rows or others: two copies of the loop, because the
+    // former's extra work costs the latter registers where they share one (48 bands, 14
+    // orbitals 1.3%, 5 orbitals up to 10%)
+    auto frequencies = [&](auto obl) __attribute__((always_inline)) {
+    constexpr bool oblique = decltype(obl)::value;
     for (int ng = n0; ng < n1; ng += 16, cur ^= 1) {
       // row c16 of Sigma of this lane's stage-B frequency, in flight during stage A
       // (rows and columns past nc repeat the last one and are cleared below)
@@ -575,14 +780,38 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
           }
         }
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          sr[j] -= i == j ? edc : 0.0;
-          rr[j] -= sr[j];
-          ri[j] -= si[j];
+        for (int j = 0; j < NC; ++j) sr[j] -= i == j ? edc : 0.0;
+        if constexpr (oblique) {  // Sigma' of the rows of Q, by way of the matrix area
+          spec_put_row<NC>(xb, i, sr, si);
+          spec_inner<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // a few at a time: few registers
+            const v2d x = xb[ic * NC + j];
+            rr[j] -= x.x;
+            ri[j] -= x.y;
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            rr[j] -= sr[j];
+            ri[j] -= si[j];
+          }
         }
         if (absent) spec_leave_out<NC>(rr, ri, absent, l, 1.0);
         spec_sweep<NC>(rr, ri, i, pmin);
         if (absent) spec_leave_out<NC>(rr, ri, absent, l, 0.0);
+        if constexpr (oblique) {  // Gl of the rows of S
+          spec_put_row<NC>(xb, i, rr, ri);
+          spec_outer<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // a few at a time: few registers
+            const v2d x = xb[ic * NC + j];
+            rr[j] = x.x;
+            ri[j] = x.y;
+          }
+        }
         SpecGl<NC> gl;
         gl.p = (gv2d*)a.xs + ((int64_t)(a.ktile_base + ktile) * n4_all + min((ng >> 2) + w, n4_all - 1)) * (4 * NC * NC) +
                (nl & 3) * NC + ic;
@@ -680,6 +909,11 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
         });
       }
     }
+    };
+    if (uniform_i(sh.oblique))
+      frequencies(std::true_type());
+    else
+      frequencies(std::false_type());
     // ---- this k-point's sums: tiles in lane order, then sum_n Re d_v
     if constexpr (WS) {
       gdouble* slot = (gdouble*)a.tsum + (int64_t)wtile * a.t_stride + a.t_base + (int64_t)kk * spec_slot_doubles(NBP, NC);

@@ -33,6 +33,8 @@ struct SpecLaneShared {
   double2 d[2][4 * DS];    // d_v of four frequencies, two turns
   double eps[NBP];         // sorted band energies
   unsigned long long key[NBP];
+  double2 lf[NC * NC];     // L of S = L Q where the rows of S are oblique
+  double g[NC * NC];       // S S^dag
 };
 
 // In-place Gauss-Jordan inverse of one matrix per lane; pmin: smallest |pivot|^2 so far.
@@ -113,13 +115,46 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
       wave_sync();
     }
     double p[NT][NBP / 4];
+    auto load_p = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int q = (lane >> 4) & 3, ab = min(16 * t + (lane & 15), NN - 1), al = ab / NC, be = ab - al * NC;
+      for (int t = 0; t < NT; ++t) {
+        const int q = (lane >> 4) & 3, ab = min(16 * t + (lane & 15), NN - 1), al = ab / NC, be = ab - al * NC;
 #pragma unroll
-      for (int c = 0; c < NBP / 4; ++c) {
-        const double2 x = sh.x[al * NBP + 4 * c + q], y = sh.x[be * NBP + 4 * c + q];
-        p[t][c] = al <= be ? x.x * y.x + x.y * y.y : y.y * x.x - y.x * x.y;
+        for (int c = 0; c < NBP / 4; ++c) {
+          const double2 x = sh.x[al * NBP + 4 * c + q], y = sh.x[be * NBP + 4 * c + q];
+          p[t][c] = al <= be ? x.x * y.x + x.y * y.y : y.y * x.x - y.x * x.y;
+        }
+      }
+    };
+    load_p();
+    // oblique rows, from S S^dag = sum_v P_v (summed over the quarters of the lanes by a
+    // product with ones): Q in their place
+    bool any_oblique;
+    {
+      double g[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        double u = 0.0, v = 0.0;
+#pragma unroll
+        for (int c = 0; c < NBP / 4; c += 2) {
+          u += p[t][c];
+          v += p[t][c + 1];
+        }
+        g[t] = mma(1.0, u + v, (v4d){0.0, 0.0, 0.0, 0.0})[0];
+        const int ab = 16 * t + (lane & 15);
+        if (lane < 16 && ab < NN) sh.g[ab] = g[t];
+      }
+      wave_sync();
+      bool bad = false;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int ab = min(16 * t + (lane & 15), NN - 1), al = ab / NC, be = ab - al * NC;
+        bad |= al < nc && be < nc && spec_oblique(sh.g[al * (NC + 1)], sh.g[be * (NC + 1)], g[t], al == be, nc);
+      }
+      any_oblique = __ballot(bad) != 0;
+      if (any_oblique) {
+        spec_orthonormal<NBP, NC>(sh.x, NBP, sh.lf, nc, lane);
+        load_p();
       }
     }
     wave_sync();
@@ -133,6 +168,8 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
 #pragma unroll
     for (int m = 0; m < NBP / 16; ++m) sd[m] = 0.0;
 
+    auto frequencies = [&](auto obl) __attribute__((always_inline)) {  // two copies, see spec_tile
+    constexpr bool oblique = decltype(obl)::value;
     for (int ng = n0; ng < n1; ng += 64) {
       // ---- stage A
       {
@@ -238,16 +275,59 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
               si[i][j] = on ? si[i][j] : 0.0;
             }
         }
+        if constexpr (oblique) {  // Sigma' of the rows of Q, by way of this lane's part of the matrix area
 #pragma unroll
-        for (int i = 0; i < NC; ++i)
+          for (int i = 0; i < NC; ++i) {
+            __builtin_amdgcn_sched_barrier(0);  // a row at a time: few registers
 #pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            gr[i][j] -= sr[i][j];
-            gi[i][j] -= si[i][j];
+            for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){sr[i][j], si[i][j]};
           }
+          __builtin_amdgcn_sched_barrier(0);
+          spec_inner<NC>(xb, spec_lds(sh.lf), 0, NC);
+#pragma unroll
+          for (int i = 0; i < NC; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              const v2d x = xb[i * NC + j];
+              gr[i][j] -= x.x;
+              gi[i][j] -= x.y;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        } else {
+#pragma unroll
+          for (int i = 0; i < NC; ++i)
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              gr[i][j] -= sr[i][j];
+              gi[i][j] -= si[i][j];
+            }
+        }
         if (absent) leave_out(1.0);
         lane_inverse<NC>(gr, gi, pmin);
         if (absent) leave_out(0.0);
+        if constexpr (oblique) {  // Gl of the rows of S
+#pragma unroll
+          for (int i = 0; i < NC; ++i) {
+            __builtin_amdgcn_sched_barrier(0);  // a row at a time: few registers
+#pragma unroll
+            for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){gr[i][j], gi[i][j]};
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          spec_outer<NC>(xb, spec_lds(sh.lf), 0, NC);
+#pragma unroll
+          for (int i = 0; i < NC; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              const v2d x = xb[i * NC + j];
+              gr[i][j] = x.x;
+              gi[i][j] = x.y;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
         double chk = 0.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i)
@@ -360,6 +440,11 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
         }
       }
     }
+    };
+    if (any_oblique)
+      frequencies(std::true_type());
+    else
+      frequencies(std::false_type());
     // ---- this k-point's sums: tiles in lane order, then sum_n Re d_v
     if constexpr (WS) {
       gdouble* slot = (gdouble*)a.tsum + (int64_t)wtile * a.t_stride + a.t_base + (int64_t)kk * spec_slot_doubles(NBP, NC);

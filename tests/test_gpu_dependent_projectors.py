@@ -1,0 +1,140 @@
+"""Projector rows that are nearly or exactly dependent, or of very different norms: the
+default density passes against the FP64 oracle, which inverts the band-window matrix and
+never X = S D S^dag.
+
+1e-10 relative, as for every other input: an FP64 emulation of the passes, over the same
+rows, stays within 1e-12 of 80-bit values, and the oracle within the same."""
+import numpy as np
+import pytest
+
+from paper_1111_2157_amd import synth
+from gpu_util import assert_gloc_parity, assert_nk_parity, gpu_density
+
+pytestmark = pytest.mark.gpu
+
+
+def with_rows(kind, nk=4, nb=20, nc=5, nw=21):
+    """The f-shell workload with the rows of all k-points but the last changed: a singular
+    value of S (a number), a row equal to another or the sum of two, all rows equal, norms
+    from 1 down to 10^(1 - nc), a row of norm 1e-120, two rows 20 degrees apart."""
+    wl = synth.f_shell(nk=nk, nb=nb, nc=nc, nw=nw, n_narrow=nc)
+    p = wl.lattice.proj.reshape(nk, nc, nb)
+    rng = np.random.default_rng(nb + nc)
+    for k in range(nk - 1):
+        s = p[k]
+        if isinstance(kind, float):
+            u = np.linalg.qr(rng.standard_normal((nc, nc)) + 1j * rng.standard_normal((nc, nc)))[0]
+            s[:] = (u * np.where(np.arange(nc) == nc - 1, kind, 1.0)) @ s
+        elif kind == "equal":
+            s[nc - 1] = s[0]
+        elif kind == "sum":
+            s[nc // 2] = s[0] + (1.0 - 0.3j) * s[nc - 1]
+        elif kind == "one":
+            s[:] = s[0]
+        elif kind == "graded":
+            s *= 10.0 ** -np.arange(nc)[:, None]
+        elif kind == "tiny":
+            s[1] *= 1e-120
+        elif kind == "angle":
+            s[1] = np.cos(0.35) * s[0] + np.sin(0.35) * s[1]
+    return wl
+
+
+KINDS = [1e-1, 1e-2, 1e-3, 1e-4, 1e-6, 1e-9, 1e-13, "equal", "sum", "one", "graded", "tiny", "angle"]
+
+
+def check(c, wl, mu=0.2):
+    mats, gl, _ = gpu_density(c, wl, mu)  # raises on a flagged error word
+    assert_nk_parity(mats, wl.lattice, wl.sigma, mu, 2)
+    assert_gloc_parity(gl, wl.lattice, wl.sigma, mu)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1111_2157_amd.dyson import Context
+
+    c = Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("nb,nc", [(9, 3), (40, 5), (18, 7), (50, 14)])
+def test_density(ctx, kind, nb, nc):
+    print("dependent rows", nb, nc, kind, flush=True)
+    check(ctx, with_rows(kind, nb=nb, nc=nc))
+
+
+@pytest.mark.parametrize("kind", [1e-4, "equal"])
+@pytest.mark.parametrize("nb,nc", [(5, 4), (16, 6), (32, 5), (33, 8), (60, 5), (64, 10), (12, 12), (48, 16), (64, 16)])
+def test_density_sizes(ctx, kind, nb, nc):
+    print("dependent rows", nb, nc, kind, flush=True)
+    check(ctx, with_rows(kind, nb=nb, nc=nc, nw=70))
+
+
+def test_g_loc_alone_and_zero_rows(ctx):
+    """G_loc alone runs kernels of its own; a zero row among dependent ones."""
+    from paper_1111_2157_amd.dyson import Lattice, SelfEnergy
+
+    for nb, nc in ((14, 4), (30, 9), (60, 13)):
+        wl = with_rows("sum", nb=nb, nc=nc)
+        wl.lattice.proj.reshape(4, nc, nb)[1:3, 1] = 0.0
+        print("dependent and zero rows", nb, nc, flush=True)
+        gl = ctx.gloc_compute(Lattice.from_host(wl.lattice), SelfEnergy.from_host(wl.sigma), 0.1)
+        ctx.sync_status()
+        assert_gloc_parity(gl.cpu().numpy(), wl.lattice, wl.sigma, 0.1)
+        check(ctx, wl, 0.1)
+
+
+def test_many_k_points_per_item(ctx):
+    """Plain and oblique k-points in turn through the same work item: the G_loc partial and
+    the staged rows of one do not leak into the next."""
+    wl = synth.plain(nk=600, nb=9, nc=4, nw=18)
+    p = wl.lattice.proj.reshape(600, 4, 9)
+    p[::3, 2] = p[::3, 0]
+    p[1::7, 3] = p[1::7, 1] * (1.0 + 1e-6) + 1e-7 * p[1::7, 0]
+    mats, gl, _ = gpu_density(ctx, wl, 0.4)
+    assert_nk_parity(mats, wl.lattice, wl.sigma, 0.4, 2, klist=[0, 1, 2, 3, 7, 8, 15, 299, 300, 597, 598, 599])
+    assert_gloc_parity(gl, wl.lattice, wl.sigma, 0.4)
+
+
+def test_batched_pass(ctx):
+    """The low-rank plan on iterates of 5 and 14 orbitals with dependent rows."""
+    import torch
+
+    from paper_1111_2157_amd.dyson import FORM_LOWRANK, Context, Lattice, SelfEnergy, split_nk
+
+    wls = [with_rows("equal", nk=6, nb=24, nc=5), with_rows(1e-5, nk=6, nb=24, nc=14)]
+    c = Context(0)
+    try:
+        c.batched_set_form(FORM_LOWRANK)
+        lats = [Lattice.from_host(w.lattice) for w in wls]
+        sigs = [SelfEnergy.from_host(w.sigma) for w in wls]
+        print("dependent rows, batched", flush=True)
+        c.batched_plan(lats, sigs, 2)
+        nks, gls = c.batched_outputs()
+        c.batched_pass(torch.tensor([0.1, -0.2], dtype=torch.float64, device="cuda"), nks, gls)
+        c.batched_sync_status()
+        for s, mu in ((0, 0.1), (1, -0.2)):
+            mats = [m.cpu().numpy() for m in split_nk(nks[s], lats[s])]
+            assert_nk_parity(mats, wls[s].lattice, wls[s].sigma, mu, 2)
+            assert_gloc_parity(gls[s].cpu().numpy(), wls[s].lattice, wls[s].sigma, mu)
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("nb,nc", [(12, 4), (40, 9)])
+def test_non_finite_rows_stay_visible(ctx, nb, nc):
+    """A NaN or an infinity among oblique rows is reported, not dropped as a dependent row."""
+    from paper_1111_2157_amd._lib import DmftError
+    from paper_1111_2157_amd.dyson import Lattice, SelfEnergy
+
+    for value in (np.nan, np.inf):
+        wl = with_rows("equal", nb=nb, nc=nc)
+        wl.lattice.proj.reshape(4, nc, nb)[0, 1, 3] = value
+        print("non-finite among dependent rows", nb, nc, value, flush=True)
+        ctx.density_matrix(Lattice.from_host(wl.lattice), SelfEnergy.from_host(wl.sigma), 0.0)
+        with pytest.raises(DmftError) as e:
+            ctx.sync_status()
+        assert e.value.name == "DMFT_ENONFINITE"
+    check(ctx, with_rows("equal", nb=nb, nc=nc))
