@@ -59,7 +59,9 @@ struct SpecAdjShared {
   double ntd[NBP];  // Nt_vv in the energy order (general product)
   double red[3 * 4];
   unsigned long long key[NBP];
+  double2 lf[WHAT == SPEC_TRACE ? NC * NC : 1];  // L of S = L Q where the rows of S are oblique
   int rank[NBP];
+  int oblique;
 };
 
 // c += x b, row layout: c, x hold this lane's row, b the row that lanes broadcast.
@@ -183,6 +185,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
     // ---- bands sorted by energy, projector columns in that order (staged over xr)
     __syncthreads();
     if (tid < NBP) sh.key[tid] = tid < nb ? spec_key(eps[tid]) : ~0ull;
+    if (tid == 0) sh.oblique = 0;
     __syncthreads();
     if (tid < NBP) {
       const int r = tid < nb ? spec_rank(sh.key, tid, nb) : tid;
@@ -202,6 +205,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
       }
     }
     __syncthreads();
+    if constexpr (WHAT == SPEC_TRACE) spec_rows_check<NBP, NC>(sh, nc, tid);
     double p[Dm::PREG ? TPW : 1][Dm::PREG ? NBP / 4 : 1];
     int pab[TPW];
 #pragma unroll
@@ -377,6 +381,10 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
 
+    // (two copies, see spec_tile; the traces are the same in the rows of Q, with
+    // Sigma' there: tr G = tr D + tr(R_Q X_Q2), ...)
+    auto frequencies = [&](auto obl) __attribute__((always_inline)) {
+    constexpr bool oblique = decltype(obl)::value;
     for (int ng = n0; ng < n1; ng += 16) {
       __syncthreads();  // the last group's matrix area and resolvent table are free
       {
@@ -434,8 +442,19 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
         spec_sweep<NC>(gr, gi, i, pmin);
         if (t == 0) {
 #pragma unroll
+          for (int j = 0; j < NC; ++j) sr[j] -= i == j ? edc : 0.0;
+          if constexpr (oblique) {  // by way of the matrix area
+            spec_put_row<NC>(xb, i, sr, si);
+            spec_inner<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              const v2d x = xb[ic * NC + j];
+              sr[j] = x.x;
+              si[j] = x.y;
+            }
+          }
+#pragma unroll
           for (int j = 0; j < NC; ++j) {
-            sr[j] -= i == j ? edc : 0.0;
             gr[j] -= sr[j];
             gi[j] -= si[j];
           }
@@ -702,6 +721,15 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
           if (mine) mub -= x2;
         }
       }
+    }
+    };
+    if constexpr (WHAT == SPEC_TRACE) {
+      if (uniform_i(sh.oblique))
+        frequencies(std::true_type());
+      else
+        frequencies(std::false_type());
+    } else {
+      frequencies(std::false_type());
     }
     // ---- this k-point's traces: lanes, then wavefronts in order
 #pragma unroll

@@ -1,5 +1,5 @@
 """Projector rows that are nearly or exactly dependent, or of very different norms: the
-default density passes against the FP64 oracle, which inverts the band-window matrix and
+default density and trace passes against the FP64 oracle, which inverts the band-window matrix and
 never X = S D S^dag.
 
 1e-10 relative, as for every other input: an FP64 emulation of the passes, over the same
@@ -7,6 +7,7 @@ rows, stays within 1e-12 of 80-bit values, and the oracle within the same."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_1111_2157_amd import synth
 from gpu_util import assert_gloc_parity, assert_nk_parity, gpu_density
 
@@ -138,3 +139,32 @@ def test_non_finite_rows_stay_visible(ctx, nb, nc):
             ctx.sync_status()
         assert e.value.name == "DMFT_ENONFINITE"
     check(ctx, with_rows("equal", nb=nb, nc=nc))
+
+
+def check_trace(c, wl, mu):
+    """N and dN/dmu of dmft_ntot, and of find_mu's search, whose passes are the same kernel's."""
+    from paper_1111_2157_amd.dyson import Lattice, SelfEnergy
+
+    dl, ds = Lattice.from_host(wl.lattice), SelfEnergy.from_host(wl.sigma)
+    got = c.dmft_ntot(dl, ds, mu).cpu().numpy()
+    c.sync_status()
+    n, d = oracle.trace(wl.lattice, wl.sigma, mu)
+    assert abs(got[0] - n) <= 1e-10 * abs(n) and abs(got[1] - d) <= 1e-10 * max(abs(d), 1.0), (got, n, d)
+    m, _, n_at = c.find_mu(dl, ds, n)
+    c.sync_status()
+    n2, d2 = oracle.trace(wl.lattice, wl.sigma, m)
+    assert abs(n_at - n2) <= 1e-10 * abs(n2) and abs(n2 - n) <= 1e-7  # the search's own tolerance is 1e-8
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("nb,nc", [(9, 3), (40, 5), (18, 7), (50, 14)])
+def test_trace(ctx, kind, nb, nc):
+    print("dependent rows, trace", nb, nc, kind, flush=True)
+    check_trace(ctx, with_rows(kind, nb=nb, nc=nc), 0.2)
+
+
+@pytest.mark.parametrize("kind", [1e-4, "equal"])
+@pytest.mark.parametrize("nb,nc", [(16, 6), (64, 10), (12, 12), (33, 13), (60, 2)])
+def test_trace_sizes(ctx, kind, nb, nc):
+    print("dependent rows, trace", nb, nc, kind, flush=True)
+    check_trace(ctx, with_rows(kind, nb=nb, nc=nc, nw=35), -0.1)
