@@ -330,7 +330,7 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
  * without a report unless a pivot vanishes; 136 takes zero rows for every kind.
  * Where rows may be dependent, select a dense code (bit 3 clear) for kinds 2
  * and 3.
- * With code 136 selected, kinds 1 to 3 of a lattice of more than 14 orbitals run
+ * With code 136 selected, kinds 2 and 3 of a lattice of more than 14 orbitals run
  * the next variant of the list, and so does the density kind, unless the code was
  * set or tuned, for more than 14 orbitals in windows of up to 16 bands. */
 int dmft_variants(int kind, int nbp, int* out, int max);

@@ -298,7 +298,7 @@ int density_var(const dmft_handle h, int nbp, int nc, bool spec) {
 // has no class for nc orbitals the first other.
 int kind_var(const dmft_handle h, int kind, int nbp, int nc) {
   const int var = choose_var(h, kind, nbp);
-  if (var != kSpectralVariant || spec_adj_fits(nc)) return var;
+  if (var != kSpectralVariant || spec_adj_fits(nc, kind == KIND_TRACE)) return var;
   int v[16];
   const int n = dyson_variants(nbp, kind, v, 16);
   for (int i = 0; i < n; ++i)
@@ -381,7 +381,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       L.t_total += b.wtiles * b.t_stride;
       sall += (size + b.tile.kt - 1) / b.tile.kt;
     }
-    if (kind == KIND_ADJOINT) {  // table of the general product
+    if (kind == KIND_ADJOINT && spec_adj_fits(lat->nc, false)) {  // table of the general product
       b.t_base = L.t_total;
       L.t_total += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
     }
@@ -1229,7 +1229,7 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
     int dense = -1;
     for (int vi = nv - 1; vi >= 0; --vi)
       if (!(vars[vi] & 8)) dense = vars[vi];
-    const bool spec0 = vars[0] == kSpectralVariant && (kind == KIND_DENSITY || spec_adj_fits(nc));
+    const bool spec0 = vars[0] == kSpectralVariant && (kind == KIND_DENSITY || spec_adj_fits(nc, kind == KIND_TRACE));
     Tile best_tile = spec0 ? sbase : base;
     int best_var = vars[0];
     char key[32];
@@ -1286,7 +1286,7 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
       }
     for (int vi = 0; vi < nv; ++vi) {
       if (vars[vi] == kLowrankP3Variant && !lowrank_p3_fits(nbp, nc)) continue;
-      if (vars[vi] == kSpectralVariant && kind != KIND_DENSITY && !spec_adj_fits(nc)) continue;
+      if (vars[vi] == kSpectralVariant && kind != KIND_DENSITY && !spec_adj_fits(nc, kind == KIND_TRACE)) continue;
       for (const Tile& t : vars[vi] == kSpectralVariant ? stiles : tiles) {
         r = measure(vars[vi], t, 2, have_ref ? got : ref, ms, err, fits);
         if (r) return r;

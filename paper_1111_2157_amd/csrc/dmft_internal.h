@@ -39,12 +39,12 @@ constexpr int spec_wgs_per_cu(int nbp, int ncls) {
 }
 
 // Trace and adjoint kernels (spectral_adj_impl.h): orbital classes (fewer than above:
-// five kernels per class and size), whether there is one, the table of the general
+// five kernels per class and size; past 14 the traces only), whether there is one, the table of the general
 // product (chunks of four of the 2 nb - 1 rows in lane order, then the diagonal), and
 // work-groups per CU, by the row matrices they hold (up to seven of 4 ncls registers;
 // 5 orbitals at three work-groups: 0.238 against 0.191 ms, spilling).
-constexpr int spec_adj_ncls(int nc) { return nc <= 5 ? 5 : nc <= 8 ? 8 : nc <= 10 ? 10 : 14; }
-constexpr bool spec_adj_fits(int nc) { return nc <= 14; }
+constexpr int spec_adj_ncls(int nc) { return nc <= 5 ? 5 : nc <= 8 ? 8 : nc <= 10 ? 10 : nc <= 14 ? 14 : 16; }
+constexpr bool spec_adj_fits(int nc, bool trace) { return trace || nc <= 14; }
 constexpr int64_t spec_adj_slot_doubles(int nbp, int ncls) {
   return (int64_t)(nbp / 2) * spec_col_tiles(ncls) * 64 + nbp;
 }

@@ -41,8 +41,7 @@ static int band_variants(int nbp, int kind, int* out, int max) {
 }
 
 // The first variant is the default: the spectral kernel.  Kinds 0 and 1: then the dense
-// variants and the low-rank ones (kind 1: the low-rank one that serves more than 14
-// orbitals comes second).  Kinds 2 (fused scalar adjoint) and 3 (general vector-Jacobian
+// variants and the low-rank ones.  Kinds 2 (fused scalar adjoint) and 3 (general vector-Jacobian
 // product): the low-rank variants, then code 0 for the dense adjoint kernel, which
 // exists up to 48 bands.  Spectral against the best other variant, measured over 6 to
 // 64 bands and 1 to 16 orbitals: 1.2 to 5 times the speed for every kind up to 14 orbitals,
@@ -57,16 +56,7 @@ int dyson_variants(int nbp, int kind, int* out, int max) {
     if (nbp <= 48 && n < max) out[n++] = 0;
     return n;
   }
-  n += band_variants(nbp, kind, out + n, max - n);
-  if (kind == 1)  // the low-rank one that serves where the spectral one does not
-    for (int i = 2; i < n; ++i)
-      if (out[i] == (nbp <= 32 ? 14 : 10)) {
-        const int v = out[i];
-        for (int j = i; j > 1; --j) out[j] = out[j - 1];
-        out[1] = v;
-        break;
-      }
-  return n;
+  return n + band_variants(nbp, kind, out + n, max - n);
 }
 
 bool dyson_supported(int nbp) { return nbp == 16 || nbp == 32 || nbp == 48 || nbp == 64; }

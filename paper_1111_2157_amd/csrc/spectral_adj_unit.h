@@ -23,6 +23,10 @@ hipError_t SPEC_NAME(int ncls, int what, const DysonArgs& a, int grid, hipStream
     SPEC_CASE(8)
     SPEC_CASE(10)
     SPEC_CASE(14)
+    case 16:
+      if (what != SPEC_TRACE) return hipErrorInvalidValue;
+      SPEC_WHAT(16, SPEC_TRACE);
+      break;
     default: return hipErrorInvalidValue;
   }
 #undef SPEC_CASE
