@@ -33,6 +33,11 @@ int nbp_of(int nb) {
 struct Tile {
   int kt = 1, wt = 1;
 };
+// A measured one and the kernel variant it was measured on.
+struct TunedTile {
+  Tile tile;
+  int var = -1;
+};
 
 enum { KIND_DENSITY = 0, KIND_TRACE = 1, KIND_ADJOINT = 2, KIND_GENERAL = 3 };
 
@@ -64,7 +69,7 @@ struct Layout {
   // spectral form: k-tiles of all buckets (density kind), doubles of the sums
   int s_ktiles_total = 0;
   int64_t t_total = 0;
-  bool tuned = false;  // the tile was measured or forced
+  bool tuned = false;  // the spectral form's tile was measured or forced (density kind)
   size_t tsum = 0, xs = 0;
   std::vector<Bucket> buckets;
   std::vector<int32_t> nb, nbp;
@@ -86,7 +91,7 @@ struct dmft_handle_s {
   size_t pinned_bytes = 0;
   void* readback = nullptr;         // pinned 64 B: error word and scalars of a mu-search pass
   hipEvent_t staged = nullptr;      // recorded after the last upload from `pinned`
-  std::map<std::string, Tile> tune;  // autotuned tiles keyed by kind/size/nk/nw
+  std::map<std::string, TunedTile> tune;  // autotuned tiles keyed by kind/size/nk/nw/orbital class
   std::map<std::string, int> tvar;   // autotuned kernel variant keyed by kind/size
   // batched plan
   struct Iter {
@@ -193,9 +198,11 @@ int check_shapes(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig) 
   return DMFT_OK;
 }
 
-std::string tile_key(int kind, int nbp, int nk, int nw) {
+// (The orbital class is part of it because the spectral form's groups, items and partials
+// go by it.)
+std::string tile_key(int kind, int nbp, int nk, int nw, int nc) {
   char key[96];
-  snprintf(key, sizeof key, "%d/%d/%d/%d", kind, nbp, nk, nw);
+  snprintf(key, sizeof key, "%d/%d/%d/%d/%d", kind, nbp, nk, nw, kind == KIND_DENSITY ? spec_ncls(nc) : spec_adj_ncls(nc));
   return key;
 }
 
@@ -254,9 +261,10 @@ Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc, bool adj = false) {
   return best;
 }
 
-Tile choose_tile(const dmft_handle h, int kind, int nk, int nw, int nbp) {
-  auto it = h->tune.find(tile_key(kind, nbp, nk, nw));
-  return it != h->tune.end() ? it->second : heuristic_tile(nk, nw);
+// The measured tile of a shape, where variant var is the one it was measured on; else null.
+const Tile* tuned_tile(const dmft_handle h, int kind, int nbp, int nk, int nw, int nc, int var) {
+  auto it = h->tune.find(tile_key(kind, nbp, nk, nw, nc));
+  return it != h->tune.end() && it->second.var == var ? &it->second.tile : nullptr;
 }
 
 const char* kind_name(int kind) {
@@ -331,7 +339,13 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   }
   L.nbp_max = *std::max_element(L.nbp.begin(), L.nbp.end());
   L.kind = kind;
-  L.tile = force ? *force : choose_tile(h, kind, nk, nw, L.nbp_max);
+  const int var = kind != KIND_DENSITY    ? kind_var(h, kind, L.nbp_max, lat->nc)
+                  : form == LAYOUT_SPEC ? kSpectralVariant
+                                        : density_var(h, L.nbp_max, lat->nc, form != LAYOUT_NO_SPEC);
+  const Tile* tuned = force ? force : tuned_tile(h, kind, L.nbp_max, nk, nw, lat->nc, var);
+  // density kind: of the buckets that are not in the spectral form (those have their own)
+  L.tile = tuned && (force || kind != KIND_DENSITY || var != kSpectralVariant) ? *tuned : heuristic_tile(nk, nw);
+  L.tuned = force || (tuned && var == kSpectralVariant);
   const int ncls = spec_ncls(lat->nc);
   // trace and adjoint kinds: the spectral kernels take their own default tile and
   // whole groups of 16 frequencies; the partials are sized for either default, so
@@ -347,7 +361,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       const Tile legacy = heuristic_tile(nk, nw);
       kt_min = std::min(kt_min, std::min(legacy.kt, other.kt));
       wtiles_max = (nw + std::min(legacy.wt, other.wt) - 1) / std::min(legacy.wt, other.wt);
-      if (spec && !h->tune.count(tile_key(kind, L.nbp_max, nk, nw))) L.tile = other;
+      if (spec && !tuned) L.tile = other;
     }
     if (spec) L.tile.wt = (L.tile.wt + 15) / 16 * 16;
   }
@@ -356,7 +370,6 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   kt_min = std::max(1, std::min(kt_min, L.tile.kt));
   L.n_wtiles = (nw + L.tile.wt - 1) / L.tile.wt;
   wtiles_max = std::max(wtiles_max, L.n_wtiles);
-  const bool tuned = L.tuned = force || h->tune.count(tile_key(kind, L.nbp_max, nk, nw));
   L.buckets.clear();
   int base = 0, sbase = 0, all = 0, sall = 0;
   bool any = false, sany = false;
@@ -370,7 +383,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
     if (kind == KIND_DENSITY) {
       b.var = form == LAYOUT_SPEC ? kSpectralVariant : density_var(h, s, lat->nc, form != LAYOUT_NO_SPEC);
       b.spec = b.var == kSpectralVariant;
-      b.tile = tuned ? L.tile : spec_heuristic_tile(size, nw, s, lat->nc);
+      b.tile = L.tuned ? *tuned : spec_heuristic_tile(size, nw, s, lat->nc);
       // whole groups of frequencies
       const int unit = spec_wt_unit(ncls);
       b.tile.wt = std::min((b.tile.wt + unit - 1) / unit * unit, (nw + unit - 1) / unit * unit);
@@ -1316,7 +1329,7 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
       }
     }
     h->tvar[key] = best_var;
-    h->tune[tile_key(kind, nbp, nk, nw)] = best_tile;
+    h->tune[tile_key(kind, nbp, nk, nw, nc)] = {best_tile, best_var};
     char line[160];
     snprintf(line, sizeof line, "best %s: var=%d kt=%d wt=%d %.3f ms\n", kind_name(kind), best_var, best_tile.kt,
              best_tile.wt, best_ms);
