@@ -225,10 +225,11 @@ Tile heuristic_tile(int nk, int nw) {
 // costs a CU its matrix products at 64 cycles and its row operations at 4 cycles a
 // wavefront, however many work-groups share the CU (5 orbitals, 64 bands: 4.0 us alone,
 // 4.3 with three; up to 40% more is charged where too few share it, which 8 orbitals, 32
-// bands show), a k-point its set-up and
-// write-out, shared among those work-groups, and items are dealt to 256 CUs.  Smaller k-tiles mean more G_loc partials and smaller
-// frequency tiles more partial sums, each written and read once at about 4 TB/s, and
-// both are kept to about 2 GB.
+// bands show), a k-point its set-up and write-out, shared among those work-groups, and
+// items are dealt to 256 CUs.  Smaller k-tiles mean more G_loc partials and smaller
+// frequency tiles more partial sums, each written and read once at about 4 TB/s.  Where
+// larger tiles can keep them to 2 GB each they do; one frequency tile's sums are what
+// they are (160 KB a k-point at 48 bands and 14 orbitals).
 Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc, bool adj = false) {
   const int ncls = adj ? spec_adj_ncls(nc) : spec_ncls(nc), nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
   const bool lane = !adj && spec_lane(ncls);
@@ -315,9 +316,9 @@ int kind_var(const dmft_handle h, int kind, int nbp, int nc) {
 }
 
 // Build the workspace layout for one lattice.  form (density kind): by the
-// chosen variants with room for every other one too (so that one workspace size
-// holds whatever is chosen later), the same without that room, without the
-// spectral form, or only the spectral form.
+// chosen variants, with the partials' part as large as for any other choice of them
+// (so that one workspace size holds whatever is chosen later), the same without that
+// room, without the spectral form, or only the spectral form.
 int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, Layout& L, int kind,
                 const Tile* force = nullptr, int form = LAYOUT_AUTO) {
   int nk = lat->nk, nw = sig->nw;
@@ -335,7 +336,6 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
     L.nbp[k] = nbp_of(L.nb[k]);
     if (!dyson_supported(L.nbp[k]))
       return fail(h, DMFT_EUNSUPPORTED, "no kernel variant for nb = %d", L.nb[k]);
-    L.off_s[k + 1] = L.off_s[k] + (int64_t)L.nbp[k] * L.nbp[k];
   }
   L.nbp_max = *std::max_element(L.nbp.begin(), L.nbp.end());
   L.kind = kind;
@@ -371,8 +371,12 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.n_wtiles = (nw + L.tile.wt - 1) / L.tile.wt;
   wtiles_max = std::max(wtiles_max, L.n_wtiles);
   L.buckets.clear();
-  int base = 0, sbase = 0, all = 0, sall = 0;
-  bool any = false, sany = false;
+  int base = 0, sbase = 0, all = 0;
+  // density kind, per bucket: k-tiles of the G_loc partials outside the spectral form,
+  // bytes of sums and partials in it
+  std::vector<int> tiles;
+  std::vector<size_t> sums, parts;
+  int spec_sizes = 0;  // bit nbp / 16: in the spectral form
   for (int s : kNbpSizes) {
     Bucket b;
     b.nbp = s;
@@ -391,15 +395,17 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       b.wtiles = (nw + b.tile.wt - 1) / b.tile.wt;
       b.t_base = L.t_total;
       b.t_stride = size * spec_slot_doubles(s, ncls);
-      L.t_total += b.wtiles * b.t_stride;
-      sall += (size + b.tile.kt - 1) / b.tile.kt;
+      if (b.spec) L.t_total += b.wtiles * b.t_stride;
+      spec_sizes |= (int)b.spec << (s / 16);
+      tiles.push_back((size + L.tile.kt - 1) / L.tile.kt);
+      sums.push_back(b.wtiles * b.t_stride * sizeof(double));
+      parts.push_back((size_t)((size + b.tile.kt - 1) / b.tile.kt) * ((nw + 3) / 4) * 4 * ncls * ncls * 16);
     }
     if (kind == KIND_ADJOINT && spec_adj_fits(lat->nc, false)) {  // table of the general product
       b.t_base = L.t_total;
       L.t_total += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
     }
     all += (size + kt_min - 1) / kt_min;
-    (b.spec ? sany : any) = true;
     const int kt = b.spec ? b.tile.kt : L.tile.kt;
     int& at = b.spec ? sbase : base;
     b.n_ktiles = (size + kt - 1) / kt;
@@ -409,7 +415,6 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   }
   L.n_ktiles_total = base;
   L.s_ktiles_total = sbase;
-  if (form == LAYOUT_AUTO && kind == KIND_DENSITY) any = sany = true;
   // the kernels are compiled for one padded size each and take nb_k within
   // (NBP - 16, NBP] as given (they skip the chunk tests of all but the last
   // 16 bands); every k of a bucket must satisfy that
@@ -418,6 +423,9 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       if (!(L.nb[k] > b.nbp - 16 && L.nb[k] <= b.nbp))
         return fail(h, DMFT_EUNSUPPORTED, "internal: nb[%d] = %d outside the bucket of padded size %d", k, L.nb[k],
                     b.nbp);
+  // sum_n G of the k-points outside the spectral form
+  for (int k = 0; k < nk; ++k)
+    L.off_s[k + 1] = L.off_s[k] + (spec_sizes >> (L.nbp[k] / 16) & 1 ? 0 : (int64_t)L.nbp[k] * L.nbp[k]);
   L.s_stride = L.off_s[nk];
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -436,11 +444,39 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.meta_nbp = take(sizeof(int32_t) * nk);
   L.meta_klist = take(sizeof(int32_t) * nk);
   L.meta_offs = take(sizeof(int64_t) * (nk + 1));
-  L.spart = take(any ? (size_t)L.n_wtiles * L.s_stride * 16 : 0);
-  L.xpart = take(any ? (size_t)all * nw * 256 * 16 : 0);
+  const size_t part0 = o;
+  if (kind == KIND_DENSITY) {
+    // the partials with bucket i in the spectral form where bit i of `spec` is set
+    auto partials = [&](unsigned spec) {
+      o = part0;
+      int kts = 0;
+      size_t g = 0, t = 0, x = 0;
+      for (size_t i = 0; i < L.buckets.size(); ++i) {
+        const bool in = spec >> i & 1;
+        const Bucket& b = L.buckets[i];
+        kts += in ? 0 : tiles[i];
+        g += in ? 0 : b.klist.size() * b.nbp * b.nbp;
+        t += in ? sums[i] : 0;
+        x += in ? parts[i] : 0;
+      }
+      L.spart = take(L.n_wtiles * g * 16);
+      L.xpart = take((size_t)kts * nw * 256 * 16);
+      L.tsum = take(t);
+      L.xs = take(x);
+      return o;
+    };
+    size_t end = 0;
+    unsigned chosen = 0;
+    for (size_t i = 0; i < L.buckets.size(); ++i) chosen |= (unsigned)L.buckets[i].spec << i;
+    if (form == LAYOUT_AUTO)
+      for (unsigned spec = 0; spec < 1u << L.buckets.size(); ++spec) end = std::max(end, partials(spec));
+    o = std::max(end, partials(chosen));
+  } else {
+    L.spart = take((size_t)L.n_wtiles * L.s_stride * 16);
+    L.xpart = take((size_t)all * nw * 256 * 16);
+    L.tsum = take((size_t)L.t_total * sizeof(double));
+  }
   L.tpart = take((size_t)wtiles_max * nk * 3 * sizeof(double));
-  L.tsum = take(kind == KIND_ADJOINT || sany ? (size_t)L.t_total * sizeof(double) : 0);
-  L.xs = take(sany ? (size_t)sall * ((nw + 3) / 4) * 4 * ncls * ncls * 16 : 0);
   L.kscal = take((size_t)nk * 3 * sizeof(double));
   L.ktrace = take((size_t)nk * 2 * sizeof(double));
   L.tune_a = take((size_t)nw * lat->nc * lat->nc * 16 + 64);
