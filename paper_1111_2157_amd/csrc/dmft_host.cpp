@@ -342,7 +342,9 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   const int var = kind != KIND_DENSITY    ? kind_var(h, kind, L.nbp_max, lat->nc)
                   : form == LAYOUT_SPEC ? kSpectralVariant
                                         : density_var(h, L.nbp_max, lat->nc, form != LAYOUT_NO_SPEC);
-  const Tile* tuned = force ? force : tuned_tile(h, kind, L.nbp_max, nk, nw, lat->nc, var);
+  // (the general product has the tile of the scalar adjoint, which the autotuner measures)
+  const Tile* tuned = force ? force : tuned_tile(h, kind == KIND_GENERAL ? (int)KIND_ADJOINT : kind, L.nbp_max, nk, nw,
+                                                 lat->nc, var);
   // density kind: of the buckets that are not in the spectral form (those have their own)
   L.tile = tuned && (force || kind != KIND_DENSITY || var != kSpectralVariant) ? *tuned : heuristic_tile(nk, nw);
   L.tuned = force || (tuned && var == kSpectralVariant);
@@ -354,9 +356,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   if (kind != KIND_DENSITY) {
     const Tile other = spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc, true);
     bool spec = false;
-    for (int n : L.nbp)
-      spec = spec || kind_var(h, kind, n, lat->nc) == kSpectralVariant ||
-             (kind == KIND_ADJOINT && kind_var(h, KIND_GENERAL, n, lat->nc) == kSpectralVariant);
+    for (int n : L.nbp) spec = spec || kind_var(h, kind, n, lat->nc) == kSpectralVariant;
     if (!force) {
       const Tile legacy = heuristic_tile(nk, nw);
       kt_min = std::min(kt_min, std::min(legacy.kt, other.kt));
@@ -401,7 +401,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       sums.push_back(b.wtiles * b.t_stride * sizeof(double));
       parts.push_back((size_t)((size + b.tile.kt - 1) / b.tile.kt) * ((nw + 3) / 4) * 4 * ncls * ncls * 16);
     }
-    if (kind == KIND_ADJOINT && spec_adj_fits(lat->nc, false)) {  // table of the general product
+    if (kind == KIND_GENERAL && spec_adj_fits(lat->nc, false)) {  // its table
       b.t_base = L.t_total;
       L.t_total += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
     }
@@ -916,10 +916,12 @@ int dmft_workspace_size(dmft_handle h, const dmft_lattice* lat, const dmft_sigma
   if (r) return r;
   r = make_layout(h, lat, sig, L2, KIND_TRACE);
   if (r) return r;
-  Layout L3;
+  Layout L3, L4;
   r = make_layout(h, lat, sig, L3, KIND_ADJOINT);
   if (r) return r;
-  *bytes = std::max(std::max(L.total, L2.total), L3.total);
+  r = make_layout(h, lat, sig, L4, KIND_GENERAL);
+  if (r) return r;
+  *bytes = std::max(std::max(L.total, L2.total), std::max(L3.total, L4.total));
   return DMFT_OK;
 }
 
@@ -1085,7 +1087,7 @@ int density_matrix_vjp(dmft_handle h, const dmft_lattice* lat, const dmft_sigma*
   if (!sigma_bar) return fail(h, DMFT_EINVAL, "sigma_bar is NULL");
   if (!std::isfinite(mu)) return fail(h, DMFT_EINVAL, "mu is not finite");
   Layout L;
-  int r = prepare(h, lat, sig, ws, ws_bytes, L, KIND_ADJOINT, stream);
+  int r = prepare(h, lat, sig, ws, ws_bytes, L, KIND_GENERAL, stream);
   if (r) return r;
   char* w = (char*)ws;
   AdjReq adj;
