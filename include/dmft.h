@@ -327,9 +327,9 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
  * works on orthonormal rows Q, P = L Q, at up to twice the time for that
  * k-point.  The other low-rank codes, and 136 of kinds 2 and 3, lose about the
  * square of the ratio of the largest to the smallest singular value of P(k),
- * without a report unless a pivot vanishes; 136 takes zero rows for every kind.
- * Where rows may be dependent, select a dense code (bit 3 clear) for kinds 2
- * and 3.
+ * without a report unless a pivot vanishes; kinds 2 and 3 take zero rows
+ * with every code.  Where rows may be dependent, select a dense code (bit 3
+ * clear) for kinds 2 and 3.
  * With code 136 selected, kinds 2 and 3 of a lattice of more than 14 orbitals run
  * the next variant of the list, and so does the density kind, unless the code was
  * set or tuned, for more than 14 orbitals in windows of up to 16 bands. */

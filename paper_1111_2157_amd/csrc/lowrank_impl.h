@@ -272,6 +272,25 @@ __device__ __forceinline__ void rsweep(double (&rr)[NC], double (&ri)[NC], int i
   }
 }
 
+// Orbitals without weight in a k-point's window (a zero projector row: X has a zero row
+// and column) are left out of the inversions: their rows and columns are set to `diag`
+// times the identity.  (x, y): this lane's diagonal element of X; the mask holds a bit per lane.
+__device__ __forceinline__ unsigned long long row_absent(double x, double y, int i, int nc) {
+  return __ballot(i < nc && x == 0.0 && y == 0.0);
+}
+template <int NC>
+__device__ __forceinline__ void row_leave_out(double (&rr)[NC], double (&ri)[NC], unsigned long long absent, int lane,
+                                               double diag) {
+  const unsigned row = (unsigned)(absent >> (lane & 48)) & 0xffffu;
+  const int i = lane & 15;
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const bool z = (row >> i | row >> j) & 1u;
+    rr[j] = z ? (i == j ? diag : 0.0) : rr[j];
+    ri[j] = z ? 0.0 : ri[j];
+  }
+}
+
 // S[c16 & 7][r] from the lane's S[c16][r] when nc <= 8: rows 8 .. 15 of S are
 // zero, so adding the value eight lanes away along the 16-lane row (row_ror:8)
 // moves S[c16 - 8][r] into lanes 8 .. 15 and leaves lanes 0 .. 7 unchanged.
@@ -549,6 +568,12 @@ __device__ __forceinline__ void lr_tile_part(const DysonArgs& a, int ktile, int 
             rr[j] = v.x;
             rim[j] = v.y;
           }
+          unsigned long long absent = 0;
+          if constexpr (KIND == KIND_ADJ || KIND == KIND_GEN) {
+            const double2 own = sh.buf[g][ri_ * 17 + ri_];
+            absent = row_absent(own.x, own.y, ri_, nc);
+            if (absent) row_leave_out<NC>(rr, rim, absent, lane, 1.0);
+          }
           rsweep<0, NC>(rr, rim, ri_, nc, bad);
   #pragma unroll
           for (int j = 0; j < NC; ++j) {
@@ -559,7 +584,9 @@ __device__ __forceinline__ void lr_tile_part(const DysonArgs& a, int ktile, int 
               rim[j] -= rin ? v.y : 0.0;
             }
           }
+          if (absent) row_leave_out<NC>(rr, rim, absent, lane, 1.0);
           rsweep<0, NC>(rr, rim, ri_, nc, bad);
+          if (absent) row_leave_out<NC>(rr, rim, absent, lane, 0.0);
   #pragma unroll
           for (int j = 0; j < NC; ++j) sh.buf[g][ri_ * 17 + j] = make_double2(rr[j], rim[j]);
           // the packed X of nc <= 8 leaves rows 8 .. 15 unwritten: complete the

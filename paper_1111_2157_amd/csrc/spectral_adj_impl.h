@@ -429,8 +429,9 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
       lv2d* xb = spec_lds(&sh.xr[nl * NP]);
       double gr[NC], gi[NC];
       spec_pair_row<NC, false>(gr, gi, xb, ic);
-      const unsigned long long absent = spec_absent(xb[ic * NC + ic], i, nc);
-      if (absent) spec_leave_out<NC>(gr, gi, absent, l, 1.0);
+      const v2d own = xb[ic * NC + ic];
+      const unsigned long long absent = row_absent(own.x, own.y, i, nc);
+      if (absent) row_leave_out<NC>(gr, gi, absent, l, 1.0);
       if (nc < NC) {
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
@@ -460,7 +461,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
             gr[j] -= sr[j];
             gi[j] -= si[j];
           }
-          if (absent) spec_leave_out<NC>(gr, gi, absent, l, 1.0);
+          if (absent) row_leave_out<NC>(gr, gi, absent, l, 1.0);
         }
       };
       if constexpr (ROLL) {
@@ -470,7 +471,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
         invert(0);
         invert(1);
       }
-      if (absent) spec_leave_out<NC>(gr, gi, absent, l, 0.0);
+      if (absent) row_leave_out<NC>(gr, gi, absent, l, 0.0);
       if (nc < NC) {  // the identity of rows past nc must not count as part of Gl
 #pragma unroll
         for (int j = 0; j < NC; ++j) {

@@ -171,7 +171,7 @@ __device__ __forceinline__ int spec_here(int i) {
 // squared norms, or (same) one row by its own: past |z| = |x| |y| / (3 nc) (below it the
 // Gram matrix of the normalised rows has its eigenvalues in 1/2 .. 3/2), or at a norm far
 // from 1 (a pivot p leaves its row about max(1, |p|) roundings, see SpecStep).  Zero rows
-// do not (spec_absent), nor do NaN (they reach the error word).
+// do not (row_absent), nor do NaN (they reach the error word).
 __device__ __forceinline__ bool spec_oblique(double xx, double yy, double z, bool same, int nc) {
   return same ? xx > 0.0 && !(xx >= 1e-4 && xx <= 1e4) : z * z * (9.0 * nc * nc) > xx * yy;
 }
@@ -378,25 +378,6 @@ struct SpecStep {
 template <int NC>
 __device__ __forceinline__ void spec_sweep(double (&rr)[NC], double (&ri)[NC], int i, double& pmin) {
   SpecStep<0, NC>::run(rr, ri, i, pmin);
-}
-
-// Orbitals without weight in a k-point's window (a zero projector row: X has a zero row
-// and column) are left out of the inversions: their rows and columns are set to `diag`
-// times the identity.  own: this lane's diagonal element of X; the mask holds a bit per lane.
-__device__ __forceinline__ unsigned long long spec_absent(v2d own, int i, int nc) {
-  return __ballot(i < nc && own.x == 0.0 && own.y == 0.0);
-}
-template <int NC>
-__device__ __forceinline__ void spec_leave_out(double (&rr)[NC], double (&ri)[NC], unsigned long long absent, int lane,
-                                               double diag) {
-  const unsigned row = (unsigned)(absent >> (lane & 48)) & 0xffffu;
-  const int i = lane & 15;
-#pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    const bool z = (row >> i | row >> j) & 1u;
-    rr[j] = z ? (i == j ? diag : 0.0) : rr[j];
-    ri[j] = z ? 0.0 : ri[j];
-  }
 }
 
 // c_j += (row K's b_j) x + (row K + 1's b_j) y for JB columns (complex), and the
@@ -769,8 +750,8 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
             ri[j] = i < nc ? ri[j] : 0.0;
           }
         }
-        const unsigned long long absent = spec_absent(own, i, nc);
-        if (absent) spec_leave_out<NC>(rr, ri, absent, l, 1.0);
+        const unsigned long long absent = row_absent(own.x, own.y, i, nc);
+        if (absent) row_leave_out<NC>(rr, ri, absent, l, 1.0);
         spec_sweep<NC>(rr, ri, i, pmin);
         if (nc < NC) {
 #pragma unroll
@@ -798,9 +779,9 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
             ri[j] -= si[j];
           }
         }
-        if (absent) spec_leave_out<NC>(rr, ri, absent, l, 1.0);
+        if (absent) row_leave_out<NC>(rr, ri, absent, l, 1.0);
         spec_sweep<NC>(rr, ri, i, pmin);
-        if (absent) spec_leave_out<NC>(rr, ri, absent, l, 0.0);
+        if (absent) row_leave_out<NC>(rr, ri, absent, l, 0.0);
         if constexpr (oblique) {  // Gl of the rows of S
           spec_put_row<NC>(xb, i, rr, ri);
           spec_outer<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));

@@ -235,7 +235,7 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
               gi[j][i] = re.y - im.x;
             }
           }
-        // orbitals without weight in this window (see spec_absent; the same in every lane)
+        // orbitals without weight in this window (see row_absent; the same in every lane)
         int absent = 0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) absent |= i < nc && gr[i][i] == 0.0 && gi[i][i] == 0.0 ? 1 << i : 0;
