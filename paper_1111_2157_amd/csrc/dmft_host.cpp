@@ -303,11 +303,26 @@ int density_var(const dmft_handle h, int nbp, int nc, bool spec) {
   return var;
 }
 
-// Trace and adjoint kinds: the chosen variant, or where that is the spectral one and
-// has no class for nc orbitals the first other.
-int kind_var(const dmft_handle h, int kind, int nbp, int nc) {
+// Trace and adjoint kinds: the chosen variant, or the first other where that is the
+// spectral one and has no class for nc orbitals, or by default runs slower: in windows of
+// 16 bands with more than 10 orbitals (its class is then 14, or 16) a work-group of 16
+// frequencies has a CU to itself, and there is little to save on so few bands.
+// 256 k-points x 512 frequencies, against the next variant: traces of 11, 12, 14 and 16
+// orbitals 0.65, 0.65, 0.63 and 0.92 ms against 0.51, 0.51, 0.54 and 0.54 (10 orbitals 0.36
+// against 0.51); general product of 12 and 14 orbitals 1.68 and 1.67 ms against 1.72 and
+// 1.99, but at fewer groups of 16 frequencies over all k-points: 3200 0.74 and 0.74 ms
+// against 0.72 and 0.85, 1600 0.46 and 0.46 against 0.41 and 0.48, 700 0.27 and 0.27
+// against 0.21 and 0.24, 280 0.15 and 0.15 against 0.09 and 0.10.
+int kind_var(const dmft_handle h, int kind, int nbp, int nc, int nk, int nw) {
   const int var = choose_var(h, kind, nbp);
-  if (var != kSpectralVariant || spec_adj_fits(nc, kind == KIND_TRACE)) return var;
+  if (var != kSpectralVariant) return var;
+  bool other = !spec_adj_fits(nc, kind == KIND_TRACE);
+  char key[32];
+  snprintf(key, sizeof key, "%d/%d", kind, nbp);
+  if (nbp == 16 && nc > 10 && !h->tvar.count(key))
+    other = other || kind == KIND_TRACE ||
+            (kind == KIND_GENERAL && (nc <= 12 || (int64_t)nk * ((nw + 15) / 16) <= 700));
+  if (!other) return var;
   int v[16];
   const int n = dyson_variants(nbp, kind, v, 16);
   for (int i = 0; i < n; ++i)
@@ -339,7 +354,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   }
   L.nbp_max = *std::max_element(L.nbp.begin(), L.nbp.end());
   L.kind = kind;
-  const int var = kind != KIND_DENSITY    ? kind_var(h, kind, L.nbp_max, lat->nc)
+  const int var = kind != KIND_DENSITY    ? kind_var(h, kind, L.nbp_max, lat->nc, nk, nw)
                   : form == LAYOUT_SPEC ? kSpectralVariant
                                         : density_var(h, L.nbp_max, lat->nc, form != LAYOUT_NO_SPEC);
   // (the general product has the tile of the scalar adjoint, which the autotuner measures)
@@ -356,7 +371,7 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   if (kind != KIND_DENSITY) {
     const Tile other = spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc, true);
     bool spec = false;
-    for (int n : L.nbp) spec = spec || kind_var(h, kind, n, lat->nc) == kSpectralVariant;
+    for (int n : L.nbp) spec = spec || kind_var(h, kind, n, lat->nc, nk, nw) == kSpectralVariant;
     if (!force) {
       const Tile legacy = heuristic_tile(nk, nw);
       kt_min = std::min(kt_min, std::min(legacy.kt, other.kt));
@@ -592,12 +607,12 @@ int run_dyson(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, con
       }
       HIPCHK(h, hipEventRecord(ev.first, s));
     }
-    if (adj.gen == 0 && (kind_var(h, KIND_ADJOINT, b.nbp, lat->nc) & 8)) {
+    if (adj.gen == 0 && (kind_var(h, KIND_ADJOINT, b.nbp, lat->nc, lat->nk, sig->nw) & 8)) {
       // fused scalar adjoint in the low-rank form (same partials as the dense kernel)
       DysonArgs aa = a;
       aa.mode = MODE_ADJ;
-      HIPCHK(h, launch_dyson(b.nbp, kind_var(h, KIND_ADJOINT, b.nbp, lat->nc), aa, b.n_ktiles, s));
-    } else if (adj.gen == 1 && (kind_var(h, KIND_GENERAL, b.nbp, lat->nc) & 8)) {
+      HIPCHK(h, launch_dyson(b.nbp, kind_var(h, KIND_ADJOINT, b.nbp, lat->nc, lat->nk, sig->nw), aa, b.n_ktiles, s));
+    } else if (adj.gen == 1 && (kind_var(h, KIND_GENERAL, b.nbp, lat->nc, lat->nk, sig->nw) & 8)) {
       // general vector-Jacobian product in the low-rank form (same partials as the dense kernel)
       DysonArgs aa = a;
       aa.mode = MODE_GEN;
@@ -606,7 +621,7 @@ int run_dyson(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, con
       aa.gbar = adj.gbar;
       aa.tsum = (double*)(ws + L.tsum);
       aa.t_base = b.t_base;
-      HIPCHK(h, launch_dyson(b.nbp, kind_var(h, KIND_GENERAL, b.nbp, lat->nc), aa, b.n_ktiles, s));
+      HIPCHK(h, launch_dyson(b.nbp, kind_var(h, KIND_GENERAL, b.nbp, lat->nc, lat->nk, sig->nw), aa, b.n_ktiles, s));
     } else if (adj.gen >= 0) {
       if (b.nbp > 48) return fail(h, DMFT_EUNSUPPORTED, "the dense adjoint supports band windows up to 48");
       HIPCHK(h, launch_adjoint(b.nbp, adj.gen, a, adj.nbar, L.ragged ? (const int64_t*)(ws + L.meta_offn) : nullptr,
@@ -614,7 +629,7 @@ int run_dyson(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, con
     } else {
       DysonArgs aa = a;
       if (b.spec) spec_args(L, b, ws, aa);
-      const int var = (mode & MODE_TRACE) ? kind_var(h, KIND_TRACE, b.nbp, lat->nc) : b.var;
+      const int var = (mode & MODE_TRACE) ? kind_var(h, KIND_TRACE, b.nbp, lat->nc, lat->nk, sig->nw) : b.var;
       HIPCHK(h, launch_dyson(b.nbp, var, aa, b.n_ktiles, s));
     }
     if (h->timing) {

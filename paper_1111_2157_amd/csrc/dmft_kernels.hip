@@ -44,9 +44,10 @@ static int band_variants(int nbp, int kind, int* out, int max) {
 // variants and the low-rank ones.  Kinds 2 (fused scalar adjoint) and 3 (general vector-Jacobian
 // product): the low-rank variants, then code 0 for the dense adjoint kernel, which
 // exists up to 48 bands.  Spectral against the best other variant, measured over 6 to
-// 64 bands and 1 to 16 orbitals: 1.2 to 5 times the speed for every kind up to 14 orbitals,
-// 1.2 to 1.5 times for the density kind at 15 and 16, except in windows of 16 bands
-// (density_var in dmft_host.cpp).
+// 64 bands and 1 to 16 orbitals: 1.1 to 5 times the speed for every kind up to 14 orbitals
+// (least for the traces of 14: 1.51 against 1.80 ms for 256 k-points of 40 bands, 1024
+// frequencies), 1.2 to 1.5 times for the density kind at 15 and 16, except in windows of 16
+// bands (density_var and kind_var in dmft_host.cpp).
 int dyson_variants(int nbp, int kind, int* out, int max) {
   if (!dyson_supported(nbp) || max <= 0) return 0;
   out[0] = kSpectralVariant;

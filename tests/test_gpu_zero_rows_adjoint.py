@@ -1,5 +1,6 @@
 """Correlated orbitals without weight in a k-point's window (zero projector rows) in the
-adjoint passes and the batched pass, up to 16 orbitals, against the FP64 oracle: 1e-10 relative, as for every other input."""
+adjoint passes and the batched pass, up to 16 orbitals and on either side of the default's
+change of kernel, against the FP64 oracle: 1e-10 relative, as for every other input."""
 import numpy as np
 import pytest
 
@@ -68,6 +69,13 @@ def test_low_rank_codes(nb, nc):
     c.close()
     for i in range(max(len(x) for x in lists)):
         check_vjp(zero_rows(nb, nc), {2: lists[0][i % len(lists[0])], 3: lists[1][i % len(lists[1])]})
+
+
+@pytest.mark.parametrize("nc,nk,nw", [(14, 700, 16), (14, 701, 5), (11, 30, 40)])
+def test_either_side_of_the_small_call_rule(nc, nk, nw):
+    """16-band windows with 11 to 14 orbitals: the general product's kernel goes by the number
+    of groups of 16 frequencies over all k-points (700; up to 12 orbitals it is one)."""
+    check_vjp(zero_rows(16, nc, nk, nw))
 
 
 def test_batched_pass():
