@@ -46,7 +46,7 @@ namespace {
 // in the order of the band energies.  A pair v < v' whose indices first differ
 // in bit l has a multiple m of 2^l in (v, v']; with L[v] = sum of e_j H(j, j+1)
 // over the steps between v and m (and likewise for v'), H(v, v') is
-// (L[v] + L[v']) / (E_v' - E_v): positive terms only, so nothing cancels, and
+// (L[v] + L[v']) / (E_v' - E_v): a mean with positive weights (see spectral_impl.h), and
 // W = S_v^dag L[v] is formed once per band and level instead of per pair.  A
 // thread takes one column of L from m outwards, one band per step, so a level
 // reads the sums once: 6 nb nc^2 additions and complex products per k-point,

@@ -19,7 +19,7 @@ namespace {
 // of the highest bit in which its indices differ, split at the multiple m of 2^l in
 // (v, v']: with A_u = S_u y_u^dag + h.c., y_u = sum over the other side of
 // conj(Nt_uu' / gap) S_u', Q_j takes e_j times the sum of A_u over the bands of its
-// side that lie outside it; partial sums only, no differences, so nothing cancels.
+// side that lie outside it; partial sums, and no differences of them.
 // Written as B operands: chunk of four rows, column tile, lane; then Nt_vv.
 // Bound by the latency of the chains over the bands of a side (128 k-points of 40
 // bands, 14 orbitals: 61 us, against 2.4 ms of the product's kernel).
