@@ -396,8 +396,9 @@ template <int NC>
 hipError_t epilogue_case(const EpilogueArgs& a, double* nk_out, hipStream_t s) {
   const int nbm = a.nb_uniform > 0 ? a.nb_uniform : a.spec_nbp;
   const size_t small = sizeof(double2) * 3 * NC * nbm, sums = sizeof(double) * (size_t)(nbm - 1) * NC * NC;
-  if (small + sums <= 156 * 1024) return epilogue_launch<NC, true>(a, small + sums, nk_out, s);
-  return epilogue_launch<NC, false>(a, small, nk_out, s);
+  if constexpr (NC == 16)  // 15 and 16 orbitals from 58 bands on
+    if (small + sums > 156 * 1024) return epilogue_launch<NC, false>(a, small, nk_out, s);
+  return epilogue_launch<NC, true>(a, small + sums, nk_out, s);
 }
 
 }  // namespace
