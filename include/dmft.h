@@ -321,20 +321,20 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
  * density kind) runs the low-rank step on two-wavefront work-groups that
  * share the nc x nc part of the step.  Code 136, the default of every kind and
  * size, is the low-rank step with its sums over bands as real matrix products
- * shared by many frequencies.  For kinds 0 and 1 it takes any P(k): zero rows (an orbital without weight in the
- * window) are left out of its inversions, and where the rows of a k-point are
- * oblique (|cos| of two past 1 / (3 nc)) or of norms outside 1e-2 .. 1e2 it
- * works on orthonormal rows Q, P = L Q, at up to twice the time for that
+ * shared by many frequencies.  For kinds 0 and 1 it takes any P(k): zero rows
+ * (an orbital without weight in the window) are left out of its inversions,
+ * and where the rows of a k-point are dependent or nearly so (the trace of
+ * (P P^dag)^-1 of its normalised rows above 64) or of norms outside 1e-2 .. 1e2
+ * it works on orthonormal rows Q, P = L Q, at up to 2.5 times the time for that
  * k-point.  The other low-rank codes, and 136 of kinds 2 and 3, lose about the
  * square of the ratio of the largest to the smallest singular value of P(k),
- * without a report unless a pivot vanishes; kinds 2 and 3 take zero rows
- * with every code.  Where rows may be dependent, select a dense code (bit 3
- * clear) for kinds 2 and 3.
- * With code 136 selected, kinds 2 and 3 of a lattice of more than 14 orbitals run
- * the next variant of the list.  Unless the code was set or tuned, so do in
- * windows of up to 16 bands the density kind from 15 orbitals, the trace kind
- * from 11, and kind 3 with 11 or 12, or with 13 or 14 on few k-points and
- * frequencies. */
+ * without a report unless a pivot vanishes; kinds 2 and 3 take zero rows with
+ * every code.  Where rows may be dependent, select a dense code (bit 3 clear)
+ * for kinds 2 and 3.  With code 136 selected, kinds 2 and 3 of a lattice of
+ * more than 14 orbitals run the next variant of the list.  Unless the code was
+ * set or tuned, so do in windows of up to 16 bands the density kind from 15
+ * orbitals, the trace kind from 11, and kind 3 with 11 or 12, or with 13 or 14
+ * on few k-points and frequencies. */
 int dmft_variants(int kind, int nbp, int* out, int max);
 int dmft_set_variant(dmft_handle h, int kind, int nbp, int var);
 int dmft_get_variant(dmft_handle h, int kind, int nbp);

@@ -61,9 +61,10 @@ struct SpecAdjShared {
   double ntd[NBP];  // Nt_vv in the energy order (general product)
   double red[3 * 4];
   unsigned long long key[NBP];
-  double2 lf[WHAT == SPEC_TRACE ? NC * NC : 1];  // L of S = L Q where the rows of S are oblique
+  double2 lf[WHAT == SPEC_TRACE ? NC * NC : 1];  // L of S = L Q where Q is used
   int rank[NBP];
-  int oblique;
+  int oblique, use_q;
+  static __device__ __forceinline__ double2* scratch(SpecAdjShared& sh) { return sh.dt; }  // filled later
 };
 
 // c += x b, row layout: c, x hold this lane's row, b the row that lanes broadcast.
@@ -187,7 +188,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
     // ---- bands sorted by energy, projector columns in that order (staged over xr)
     __syncthreads();
     if (tid < NBP) sh.key[tid] = tid < nb ? spec_key(eps[tid]) : ~0ull;
-    if (tid == 0) sh.oblique = 0;
+    if (tid == 0) sh.oblique = sh.use_q = 0;
     __syncthreads();
     if (tid < NBP) {
       const int r = tid < nb ? spec_rank(sh.key, tid, nb) : tid;
@@ -727,7 +728,7 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
     }
     };
     if constexpr (WHAT == SPEC_TRACE) {
-      if (uniform_i(sh.oblique))
+      if (uniform_i(sh.use_q))
         frequencies(std::true_type());
       else
         frequencies(std::false_type());

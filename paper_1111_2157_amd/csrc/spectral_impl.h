@@ -44,8 +44,8 @@
 // full 16x16x4 products and B on uniform row operations.
 //
 // Measured (512 k-points, 2048 frequencies, per k-point and frequency; in brackets
-// the frequency-at-a-time low-rank kernels, tuned): 32 bands and 10 orbitals 2.46 ns
-// (5.3), 48 and 14 5.33 (10.2), 64 and 14 5.85.  At 48 and 14 the matrix products with
+// the frequency-at-a-time low-rank kernels, tuned): 32 bands and 10 orbitals 2.37 ns
+// (5.3), 48 and 14 5.28 (10.2), 64 and 14 5.97.  At 48 and 14 the matrix products with
 // their padding would take 2.0 ns at full rate and the row operations of B 2.1; what
 // bounds the rest is that the two units do not run FP64 together and a SIMD holds one
 // wavefront (its row matrices, sums and operands fill the registers), so the LDS round
@@ -123,10 +123,11 @@ struct SpecShared {
   double sd[NBP * 17];            // running sum of Re d_v per (band, frequency of the group)
   double eps[NBP];                // sorted band energies
   unsigned long long key[NBP];
-  double2 lf[NC * NC];            // L of S = L Q where the rows of S are oblique
+  double2 lf[NC * NC];            // L of S = L Q where Q is used
   int rank[NBP];
-  int oblique;
+  int oblique, use_q;             // the rows of S are looked at closer; Q stands in their place
   int next;
+  static __device__ __forceinline__ double2* scratch(SpecShared& sh) { return sh.dt[0]; }  // filled later
 };
 
 // Smallest energy step the weighted mean of adjacent sums resolves: steps below
@@ -162,21 +163,23 @@ __device__ __forceinline__ int spec_here(int i) {
 // orthonormal (or zero) rows of Q and lower triangular L takes that number out of the
 // inversions, X = Q D Q^dag then being as well conditioned as for orthonormal projectors:
 //   Gl = L (X^-1 - L^dag Sigma' L)^-1 L^dag,
-// four more row products per evaluation, so only a k-point whose rows ask for it is
+// four more row products per evaluation, so only a k-point whose rows call for it is
 // taken this way.  (6 to 48 bands, one singular value of S from 1 down to 1e-13, or equal
 // rows, beta 40 and 1000: G_loc within 2e-12 of 80-bit values and N(k) within 5e-13, as the
 // band-window inversion (2e-13, 8e-14); with S itself 1e-8 at a singular value of 1e-4.
-// All k-points oblique against none: density passes of 64 k-points, 12 bands, 5 orbitals,
-// 256 frequencies 76 us against 50, of 256, 48, 14, 512 1.72 ms against 0.86; the band-window
-// kernels 158 us and 7.9 ms.)
+// All k-points in Q against none: density passes of 64 k-points, 12 bands, 5 orbitals, 256
+// frequencies 78 us against 49, of 256, 48, 14, 512 1.73 ms against 0.86; the band-window
+// kernels 158 us and 7.9 ms.  Rows that are looked at closer and keep their basis: 58 us and
+// 0.97 ms.)
 
-// Whether two rows ask for it, by the real or imaginary part z of their product and their
-// squared norms, or (same) one row by its own: past |z| = |x| |y| / (3 nc) (below it the
-// Gram matrix of the normalised rows has its eigenvalues in 1/2 .. 3/2), or at a norm far
-// from 1 (a pivot p leaves its row about max(1, |p|) roundings, see SpecStep).  Zero rows
-// do not (row_absent), nor do NaN (they reach the error word).
+// Whether two rows may ask for it, by the real or imaginary part z of their product and
+// their squared norms, or (same) one row by its own: past |z| = |x| |y| / (3 nc) (below it
+// the Gram matrix of the normalised rows has its eigenvalues in 1/2 .. 3/2), or at a norm
+// far from 1 (a pivot p leaves its row about max(1, |p|) roundings, see SpecStep).  Zero
+// rows do not (row_absent), nor do NaN (they reach the error word).
+__device__ __forceinline__ bool spec_far(double xx) { return xx > 0.0 && !(xx >= 1e-4 && xx <= 1e4); }
 __device__ __forceinline__ bool spec_oblique(double xx, double yy, double z, bool same, int nc) {
-  return same ? xx > 0.0 && !(xx >= 1e-4 && xx <= 1e4) : z * z * (9.0 * nc * nc) > xx * yy;
+  return same ? spec_far(xx) : z * z * (9.0 * nc * nc) > xx * yy;
 }
 
 // Sums over the four lanes of a quad, and over a wavefront.
@@ -192,10 +195,15 @@ __device__ __forceinline__ double spec_wave_sum(double v) {
 
 // S = L Q by one wavefront, a band per lane: Gram-Schmidt, every row twice against all
 // before it.  s: the rows in LDS (stride ss, zeros past the window), replaced by Q; a row
-// within 3.6e-15 of the span of those before it gets a zero row of Q.
+// within 3.6e-15 of the span of those before it gets a zero row of Q.  Returns whether Q is
+// to be used: a row dropped or of a far norm, or tr (S S^dag)^-1 of the normalised rows, the
+// factor by which roundings in X^-1 grow, over 64 (nc for orthonormal rows).  y: scratch of
+// NC * NC.
 template <int NBP, int NC>
-__device__ __forceinline__ void spec_orthonormal(double2* s, int ss, double2* lf, int nc, int lane) {
+__device__ __forceinline__ bool spec_orthonormal(double2* s, int ss, double2* lf, double2* y, int nc, int lane) {
   const int j = lane & 15, h = lane >> 4;
+  double norm = 1.0, f = 0.0;  // |row j|; this lane's share of the trace
+  bool use = false;
 #pragma clang loop unroll(disable)
   for (int i = 0; i < NC; ++i) {
     double2 r = lane < NBP && i < nc ? s[i * ss + lane] : make_double2(0.0, 0.0);
@@ -231,10 +239,30 @@ __device__ __forceinline__ void spec_orthonormal(double2* s, int ss, double2* lf
     const double n = spec_wave_sum(lane < NBP ? r.x * r.x + r.y * r.y : 0.0);
     const bool drop = n <= 1.3e-29 * n0 && __builtin_isfinite(n0);  // not for NaN or infinity: they stay visible
     const double len = drop ? 0.0 : __builtin_sqrt(n), inv = drop ? 0.0 : 1.0 / len;
+    use |= spec_far(n0) || (drop && n0 > 0.0);
+    if (j == i) norm = __builtin_sqrt(n0);
     if (lane < NBP && i < nc) s[i * ss + lane] = make_double2(r.x * inv, r.y * inv);
     if (lane < NC) lf[i * NC + lane] = i < nc && j < i ? l : make_double2(i < nc && j == i ? len : 0.0, 0.0);
     wave_sync();
   }
+  // column j of L^-1 times |row j| (zero rows: of the identity)
+  if (lane < nc)
+#pragma clang loop unroll(disable)
+    for (int i = j; i < nc; ++i) {
+      double2 z = make_double2(i == j ? norm : 0.0, 0.0);
+#pragma clang loop unroll(disable)
+      for (int m = j; m < i; ++m) {
+        const double2 a = lf[i * NC + m], b = y[j * NC + m];
+        z.x -= a.x * b.x - a.y * b.y;
+        z.y -= a.x * b.y + a.y * b.x;
+      }
+      const double d = lf[i * NC + i].x, inv = d == 0.0 ? 1.0 : 1.0 / d;
+      z.x *= inv;
+      z.y *= inv;
+      y[j * NC + i] = z;
+      f += z.x * z.x + z.y * z.y;
+    }
+  return use || !(spec_wave_sum(f) <= 64.0);
 }
 
 // m = L^dag m L and m = L m L^dag in place, m in LDS: this lane's rows i0 .. i1 - 1, then
@@ -493,7 +521,7 @@ struct SpecGl {
 };
 
 // Looks the staged rows of S over (four lanes to an unordered pair of them) and where they
-// are oblique puts Q in their place: sh.oblique.
+// are oblique enough puts Q in their place: sh.use_q.
 template <int NBP, int NC, class Sh>
 __device__ __forceinline__ void spec_rows_check(Sh& sh, int nc, int tid) {
   using Dm = typename Sh::Dm;
@@ -519,17 +547,29 @@ __device__ __forceinline__ void spec_rows_check(Sh& sh, int nc, int tid) {
   }
   __syncthreads();
   if (!uniform_i(sh.oblique)) return;
-  if (tid < 64) spec_orthonormal<NBP, NC>(s, SS, sh.lf, nc, tid);
-  __syncthreads();
-  if constexpr (!Dm::PREG) {
-#pragma clang loop unroll(disable)
-    for (int idx = tid; idx < NC * NBP; idx += 256) {
-      const int al = idx / NBP, v = idx - al * NBP;
-      const double2 x = sh.sp[al * SS + v];
-      sh.sp[(NC + al) * SS + v] = make_double2(x.y, -x.x);
-    }
+  // S is kept meanwhile: in its other form, or past the scratch
+  double2* const y = Sh::scratch(sh);
+  double2* const back = Dm::PREG ? y + NC * NC : s + NC * SS;
+  if constexpr (Dm::PREG) {
+    for (int idx = tid; idx < NC * NBP; idx += 256) back[idx] = s[idx];
     __syncthreads();
   }
+  if (tid < 64) {
+    const bool use = spec_orthonormal<NBP, NC>(s, SS, sh.lf, y, nc, tid);
+    if (tid == 0) sh.use_q = use;
+  }
+  __syncthreads();
+  const bool use = uniform_i(sh.use_q);
+#pragma clang loop unroll(disable)
+  for (int idx = tid; idx < NC * NBP; idx += 256) {
+    const int at = idx / NBP * SS + idx % NBP;
+    const double2 x = s[at], b = back[at];
+    if (!use)
+      s[at] = Dm::PREG ? b : make_double2(-b.y, b.x);
+    else if (!Dm::PREG)
+      back[at] = make_double2(x.y, -x.x);
+  }
+  __syncthreads();
 }
 
 // WS: the sums are wanted (N(k)); else G_loc only.
@@ -565,7 +605,7 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
     // ---- bands sorted by energy, projector columns in that order (staged over xr)
     __syncthreads();
     if (tid < NBP) sh.key[tid] = tid < nb ? spec_key(eps[tid]) : ~0ull;
-    if (tid == 0) sh.oblique = 0;
+    if (tid == 0) sh.oblique = sh.use_q = 0;
     __syncthreads();
     if (tid < NBP) {
       const int r = tid < nb ? spec_rank(sh.key, tid, nb) : tid;
@@ -894,7 +934,7 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
       }
     }
     };
-    if (uniform_i(sh.oblique))
+    if (uniform_i(sh.use_q))
       frequencies(std::true_type());
     else
       frequencies(std::false_type());

@@ -19,7 +19,7 @@
 // Bound by the matrix cores (A and C: 4 nb nc^2 and 8 nb nc^2 with nc^2 padded to 32)
 // and, at small windows, by B.  Measured per k-point and frequency, 512 k-points, 2048
 // frequencies, row layout in brackets: 64 bands 0.72 ns (1.04), 48 0.57 (0.98), 32
-// 0.43 (0.82), 16 0.33 (0.7).  Six orbitals do not fit the registers at 64 bands.
+// 0.44 (0.82), 16 0.33 (0.7).  Six orbitals do not fit the registers at 64 bands.
 #pragma once
 
 #include "spectral_impl.h"
@@ -33,7 +33,7 @@ struct SpecLaneShared {
   double2 d[2][4 * DS];    // d_v of four frequencies, two turns
   double eps[NBP];         // sorted band energies
   unsigned long long key[NBP];
-  double2 lf[NC * NC];     // L of S = L Q where the rows of S are oblique
+  double2 lf[NC * NC];     // L of S = L Q where Q is used
   double g[NC * NC];       // S S^dag
 };
 
@@ -129,7 +129,7 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
     load_p();
     // oblique rows, from S S^dag = sum_v P_v (summed over the quarters of the lanes by a
     // product with ones): Q in their place
-    bool any_oblique;
+    bool use_q = false;
     {
       double g[NT];
 #pragma unroll
@@ -151,10 +151,9 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
         const int ab = min(16 * t + (lane & 15), NN - 1), al = ab / NC, be = ab - al * NC;
         bad |= al < nc && be < nc && spec_oblique(sh.g[al * (NC + 1)], sh.g[be * (NC + 1)], g[t], al == be, nc);
       }
-      any_oblique = __ballot(bad) != 0;
-      if (any_oblique) {
-        spec_orthonormal<NBP, NC>(sh.x, NBP, sh.lf, nc, lane);
-        load_p();
+      if (__ballot(bad)) {
+        use_q = __ballot(spec_orthonormal<NBP, NC>(sh.x, NBP, sh.lf, sh.d[0], nc, lane)) != 0;
+        if (use_q) load_p();  // else p stays as it is
       }
     }
     wave_sync();
@@ -441,7 +440,7 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
       }
     }
     };
-    if (any_oblique)
+    if (use_q)
       frequencies(std::true_type());
     else
       frequencies(std::false_type());

@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 def with_rows(kind, nk=4, nb=20, nc=5, nw=21):
     """The f-shell workload with the rows of all k-points but the last changed: a singular
     value of S (a number), a row equal to another or the sum of two, all rows equal, norms
-    from 1 down to 10^(1 - nc), a row of norm 1e-120, two rows 20 degrees apart."""
+    from 1 down to 10^(1 - nc), a row of norm 1e-120, two rows 20 degrees apart, every row
+    15 degrees from the mean of those before it, rows mixed by a matrix near 1."""
     wl = synth.f_shell(nk=nk, nb=nb, nc=nc, nw=nw, n_narrow=nc)
     p = wl.lattice.proj.reshape(nk, nc, nb)
     rng = np.random.default_rng(nb + nc)
@@ -38,6 +39,12 @@ def with_rows(kind, nk=4, nb=20, nc=5, nw=21):
             s[1] *= 1e-120
         elif kind == "angle":
             s[1] = np.cos(0.35) * s[0] + np.sin(0.35) * s[1]
+        elif kind == "stair":
+            for i in range(1, nc):
+                m = s[:i].sum(0)
+                s[i] = np.cos(0.26) * m / np.linalg.norm(m) + np.sin(0.26) * s[i]
+        elif kind == "mixed":
+            s[:] = (np.eye(nc) + 0.1 * (rng.standard_normal((nc, nc)) + 1j * rng.standard_normal((nc, nc)))) @ s
     return wl
 
 
@@ -168,3 +175,13 @@ def test_trace(ctx, kind, nb, nc):
 def test_trace_sizes(ctx, kind, nb, nc):
     print("dependent rows, trace", nb, nc, kind, flush=True)
     check_trace(ctx, with_rows(kind, nb=nb, nc=nc, nw=35), -0.1)
+
+
+@pytest.mark.parametrize("kind", [0.5, 0.2, 0.12, "stair", "mixed"])
+@pytest.mark.parametrize("nb,nc", [(10, 4), (40, 5), (18, 6), (50, 14), (60, 8)])
+def test_on_either_side_of_the_rule(ctx, kind, nb, nc):
+    """Oblique rows that keep their own basis, and ones that are just past that."""
+    wl = with_rows(kind, nb=nb, nc=nc)
+    print("oblique rows", nb, nc, kind, flush=True)
+    check(ctx, wl)
+    check_trace(ctx, wl, 0.2)
