@@ -230,7 +230,9 @@ Tile heuristic_tile(int nk, int nw) {
 // frequency tiles more partial sums, each written and read once at about 4 TB/s.  Where
 // larger tiles can keep them to 2 GB each they do; one frequency tile's sums are what
 // they are (160 KB a k-point at 48 bands and 14 orbitals).
-Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc, bool adj = false) {
+// kt0: the smallest k-tile (adjoint kinds, whose partials have 4 KB per k-tile and
+// frequency as those of the other kernels: theirs).
+Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc, bool adj = false, int kt0 = 1) {
   const int ncls = adj ? spec_adj_ncls(nc) : spec_ncls(nc), nt = spec_col_tiles(ncls), nr = spec_row_tiles(nbp);
   const bool lane = !adj && spec_lane(ncls);
   const double per_cu = adj ? spec_adj_wgs_per_cu(ncls, 0) : spec_wgs_per_cu(nbp, ncls);
@@ -242,7 +244,7 @@ Tile spec_heuristic_tile(int nk, int nw, int nbp, int nc, bool adj = false) {
   const int unit = lane ? 64 : 16, nwr = (nw + unit - 1) / unit * unit;
   Tile best;
   double best_t = 1e300;
-  for (int kt = 1; kt <= std::min(nk, 64); kt *= 2)
+  for (int kt = kt0; kt <= std::max(kt0, std::min(nk, 64)); kt *= 2)
     for (int f = 1; f <= nwr / unit; f = f < 8 ? f + 1 : f * 2) {
       const int wt = (nwr / unit + f - 1) / f * unit;
       const double ktiles = (nk + kt - 1) / kt, wtiles = (nw + wt - 1) / wt;
@@ -345,12 +347,14 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.off_n.assign(nk + 1, 0);
   L.off_s.assign(nk + 1, 0);
   L.nbp.assign(nk, 0);
+  int sizes = 0;  // padded sizes in use (bit nbp / 16)
   for (int k = 0; k < nk; ++k) {
     L.off_b[k + 1] = L.off_b[k] + L.nb[k];
     L.off_n[k + 1] = L.off_n[k] + (int64_t)L.nb[k] * L.nb[k];
     L.nbp[k] = nbp_of(L.nb[k]);
     if (!dyson_supported(L.nbp[k]))
       return fail(h, DMFT_EUNSUPPORTED, "no kernel variant for nb = %d", L.nb[k]);
+    sizes |= 1 << (L.nbp[k] / 16);
   }
   L.nbp_max = *std::max_element(L.nbp.begin(), L.nbp.end());
   L.kind = kind;
@@ -361,32 +365,48 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   const Tile* tuned = force ? force : tuned_tile(h, kind == KIND_GENERAL ? (int)KIND_ADJOINT : kind, L.nbp_max, nk, nw,
                                                  lat->nc, var);
   // density kind: of the buckets that are not in the spectral form (those have their own)
-  L.tile = tuned && (force || kind != KIND_DENSITY || var != kSpectralVariant) ? *tuned : heuristic_tile(nk, nw);
+  const Tile legacy = heuristic_tile(nk, nw);
+  L.tile = tuned && (force || kind != KIND_DENSITY || var != kSpectralVariant) ? *tuned : legacy;
   L.tuned = force || (tuned && var == kSpectralVariant);
   const int ncls = spec_ncls(lat->nc);
   // trace and adjoint kinds: the spectral kernels take their own default tile and
-  // whole groups of 16 frequencies; the partials are sized for either default, so
-  // that a workspace holds the pass whichever variant is chosen later
+  // whole groups of 16 frequencies; the partials are sized for either default and the
+  // tuned tiles, so that a workspace holds the pass whichever variant is chosen later.
+  // (The adjoint default's k-tiles are no smaller than the others', and its frequency
+  // tiles matter for the traces' partials only.)
+  auto other_tile = [&](bool trace) {
+    return spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc, true, trace ? 1 : legacy.kt);
+  };
   int kt_min = L.tile.kt, wtiles_max = 0;
+  if (!force) {
+    int wt = legacy.wt;
+    kt_min = legacy.kt;
+    if (wt > 16) wt = std::min(wt, std::min(other_tile(true).wt, other_tile(false).wt));
+    if (!h->tune.empty())
+      for (int k : {KIND_TRACE, KIND_ADJOINT}) {
+        auto it = h->tune.find(tile_key(k, L.nbp_max, nk, nw, lat->nc));
+        if (it == h->tune.end()) continue;
+        wt = std::min(wt, it->second.tile.wt);
+        if (k == KIND_ADJOINT) kt_min = std::min(kt_min, it->second.tile.kt);
+      }
+    kt_min = std::max(1, std::min(kt_min, nk));
+    wtiles_max = (nw + wt - 1) / wt;
+  }
   if (kind != KIND_DENSITY) {
-    const Tile other = spec_heuristic_tile(nk, nw, L.nbp_max, lat->nc, true);
     bool spec = false;
-    for (int n : L.nbp) spec = spec || kind_var(h, kind, n, lat->nc, nk, nw) == kSpectralVariant;
-    if (!force) {
-      const Tile legacy = heuristic_tile(nk, nw);
-      kt_min = std::min(kt_min, std::min(legacy.kt, other.kt));
-      wtiles_max = (nw + std::min(legacy.wt, other.wt) - 1) / std::min(legacy.wt, other.wt);
-      if (spec && !tuned) L.tile = other;
-    }
+    for (int s : kNbpSizes)
+      spec = spec || (sizes >> (s / 16) & 1 && kind_var(h, kind, s, lat->nc, nk, nw) == kSpectralVariant);
+    if (spec && !tuned) L.tile = other_tile(kind == KIND_TRACE);
     if (spec) L.tile.wt = (L.tile.wt + 15) / 16 * 16;
   }
   L.tile.wt = std::max(1, std::min(L.tile.wt, kind == KIND_DENSITY ? nw : (nw + 15) / 16 * 16));
   L.tile.kt = std::max(1, std::min(L.tile.kt, nk));
-  kt_min = std::max(1, std::min(kt_min, L.tile.kt));
+  if (force) kt_min = L.tile.kt;
   L.n_wtiles = (nw + L.tile.wt - 1) / L.tile.wt;
   wtiles_max = std::max(wtiles_max, L.n_wtiles);
   L.buckets.clear();
   int base = 0, sbase = 0, all = 0;
+  size_t table = 0;  // doubles of the general product's table
   // density kind, per bucket: k-tiles of the G_loc partials outside the spectral form,
   // bytes of sums and partials in it
   std::vector<int> tiles;
@@ -416,10 +436,8 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       sums.push_back(b.wtiles * b.t_stride * sizeof(double));
       parts.push_back((size_t)((size + b.tile.kt - 1) / b.tile.kt) * ((nw + 3) / 4) * 4 * ncls * ncls * 16);
     }
-    if (kind == KIND_GENERAL && spec_adj_fits(lat->nc, false)) {  // its table
-      b.t_base = L.t_total;
-      L.t_total += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
-    }
+    if (kind != KIND_DENSITY) b.t_base = table;
+    if (spec_adj_fits(lat->nc, false)) table += size * spec_adj_slot_doubles(s, spec_adj_ncls(lat->nc));
     all += (size + kt_min - 1) / kt_min;
     const int kt = b.spec ? b.tile.kt : L.tile.kt;
     int& at = b.spec ? sbase : base;
@@ -460,6 +478,12 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
   L.meta_klist = take(sizeof(int32_t) * nk);
   L.meta_offs = take(sizeof(int64_t) * (nk + 1));
   const size_t part0 = o;
+  auto adjoint_partials = [&](bool general) {
+    o = part0;
+    L.xpart = take((size_t)all * nw * 256 * 16);
+    L.tsum = take(general ? table * sizeof(double) : 0);
+    return o;
+  };
   if (kind == KIND_DENSITY) {
     // the partials with bucket i in the spectral form where bit i of `spec` is set
     auto partials = [&](unsigned spec) {
@@ -480,16 +504,16 @@ int make_layout(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig, L
       L.xs = take(x);
       return o;
     };
-    size_t end = 0;
+    // (and as much as the adjoint kinds take: a size that is too small for one of them is
+    // refused here too)
+    size_t end = form == LAYOUT_AUTO && !force ? adjoint_partials(true) : 0;
     unsigned chosen = 0;
     for (size_t i = 0; i < L.buckets.size(); ++i) chosen |= (unsigned)L.buckets[i].spec << i;
     if (form == LAYOUT_AUTO)
       for (unsigned spec = 0; spec < 1u << L.buckets.size(); ++spec) end = std::max(end, partials(spec));
     o = std::max(end, partials(chosen));
-  } else {
-    L.spart = take((size_t)L.n_wtiles * L.s_stride * 16);
-    L.xpart = take((size_t)all * nw * 256 * 16);
-    L.tsum = take((size_t)L.t_total * sizeof(double));
+  } else if (kind != KIND_TRACE) {
+    adjoint_partials(kind == KIND_GENERAL);
   }
   L.tpart = take((size_t)wtiles_max * nk * 3 * sizeof(double));
   L.kscal = take((size_t)nk * 3 * sizeof(double));
@@ -1267,7 +1291,8 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
     int nbp = L0.nbp_max, nk = lat->nk, nw = sig->nw, nc = lat->nc;
     int vars[16];
     int nv = dyson_variants(nbp, kind, vars, 16);
-    const Tile base = heuristic_tile(nk, nw), sbase = spec_heuristic_tile(nk, nw, nbp, nc, kind != KIND_DENSITY);
+    const Tile base = heuristic_tile(nk, nw), sbase = spec_heuristic_tile(nk, nw, nbp, nc, kind != KIND_DENSITY,
+                                                                             kind == KIND_ADJOINT ? heuristic_tile(nk, nw).kt : 1);
     // frequency tiles around the default, then the k-tile halved and doubled
     // with the frequency tile scaled the other way (the same number of items;
     // fewer G_loc partial read-backs against fewer partials of the running sum).

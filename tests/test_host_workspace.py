@@ -30,6 +30,39 @@ def test_one_form_at_a_time(lib, h, nk, nb, nc, nw, size):  # noqa: F811
     assert n <= size * (1.0 if np.isscalar(nb) else 1.1)
 
 
+# the adjoint kinds' partials: 2.4 to 3 times these with k-tiles of their own choice; the
+# sums of the spectral density pass are what remains
+@pytest.mark.parametrize("nk,nb,nc,nw,size,more", [
+    (8542, (13, 34), 1, 513, 2293073152, 1.0), (4111, 11, 10, 851, 1266592768, 1.3), (2294, 12, 7, 1252, 1263759616, 1.1)])
+def test_adjoint_partials(lib, h, nk, nb, nc, nw, size, more):  # noqa: F811
+    r, n = ws_size(lib, h, lattice(nk, nc, windows(nk, nb)), sigma(nw))
+    assert r == 0 and n <= more * size, n / size
+
+
+def test_one_size_serves_every_call(lib, h):  # noqa: F811
+    """Over random shapes: with the size as asked for every kind of call reaches the device
+    (which a planning handle does not have), with one byte less density_matrix does not."""
+    rng = np.random.default_rng(5)
+    out, ws = fake(200), fake(100)
+    for i in range(60):
+        nc = int(rng.integers(1, 17))
+        nb = rng.integers(nc, rng.integers(nc, 65) + 1, int(2 ** rng.uniform(0, 12)))
+        lat, sig = lattice(len(nb), nc, nb), sigma(int(2 ** rng.uniform(0, 11)))
+        r, need = ws_size(lib, h, lat, sig)
+        assert r == 0
+        n = C.c_size_t(need)
+        mu, passes, nv = C.c_double(), C.c_int(), C.c_double()
+        assert lib.density_matrix(h, ref(lat), ref(sig), C.c_double(0.0), 2, out, None, None, ws, C.c_size_t(need - 1),
+                                  None) == -6, (i, nc, len(nb), sig.nw)
+        for r in (lib.density_matrix(h, ref(lat), ref(sig), C.c_double(0.0), 2, out, None, None, ws, n, None),
+                  lib.dmft_ntot(h, ref(lat), ref(sig), C.c_double(0.0), 2, out, ws, n, None),
+                  lib.dmft_ntot_vjp(h, ref(lat), ref(sig), C.c_double(0.0), 2, out, out, ws, n, None),
+                  lib.density_matrix_vjp(h, ref(lat), ref(sig), C.c_double(0.0), 2, out, out, out, None, ws, n, None),
+                  lib.find_mu(h, ref(lat), ref(sig), 2, C.c_double(1.0), C.c_double(1e-8), 0, C.c_double(-1.0),
+                              C.c_double(1.0), C.c_double(0.0), 9, ref(mu), ref(passes), ref(nv), ws, n, None)):
+            assert r == -1 and "planning handle" in last(lib, h), (i, nc, len(nb), sig.nw, last(lib, h))
+
+
 @pytest.mark.parametrize("nk,nb,nc,nw", [(64, 12, 5, 256), (40, (8, 64), 6, 100), (200, (14, 64), 14, 64), (3, 64, 16, 40)])
 def test_holds_any_choice_of_variants(lib, h, nk, nb, nc, nw):  # noqa: F811
     """density_matrix with the size as asked for at first reaches the device (which a planning
