@@ -333,8 +333,8 @@ int dmft_autotune(dmft_handle h, const dmft_lattice* lat, const dmft_sigma* sig,
  * for kinds 2 and 3.  With code 136 selected, kinds 2 and 3 of a lattice of
  * more than 14 orbitals run the next variant of the list.  Unless the code was
  * set or tuned, so do in windows of up to 16 bands the density kind from 15
- * orbitals, the trace kind from 11, and kind 3 with 11 or 12, or with 13 or 14
- * on few k-points and frequencies. */
+ * orbitals, the trace kind from 11 but for few k-points and frequencies, and
+ * kind 3 with 11 or 12, or with 13 or 14 on few k-points and frequencies. */
 int dmft_variants(int kind, int nbp, int* out, int max);
 int dmft_set_variant(dmft_handle h, int kind, int nbp, int var);
 int dmft_get_variant(dmft_handle h, int kind, int nbp);

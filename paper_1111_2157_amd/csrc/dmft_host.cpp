@@ -311,9 +311,11 @@ int density_var(const dmft_handle h, int nbp, int nc, bool spec) {
 // frequencies has a CU to itself, and there is little to save on so few bands.
 // 256 k-points x 512 frequencies, against the next variant: traces of 11, 12, 14 and 16
 // orbitals 0.65, 0.65, 0.63 and 0.92 ms against 0.51, 0.51, 0.54 and 0.54 (10 orbitals 0.36
-// against 0.51); general product of 12 and 14 orbitals 1.68 and 1.67 ms against 1.72 and
-// 1.99, but at fewer groups of 16 frequencies over all k-points: 3200 0.74 and 0.74 ms
-// against 0.72 and 0.85, 1600 0.46 and 0.46 against 0.41 and 0.48, 700 0.27 and 0.27
+// against 0.51).  The traces go either way up to two rounds of 256 CUs with groups of 16
+// frequencies (over all k-points: 160 groups 44 us against 50, 280 61 against 55, 448 63
+// against 67) and are slower past them (520 82 against 75).  General product of 12 and 14
+// orbitals 1.68 and 1.67 ms against 1.72 and 1.99, but at fewer groups: 3200 0.74 and 0.74
+// ms against 0.72 and 0.85, 1600 0.46 and 0.46 against 0.41 and 0.48, 700 0.27 and 0.27
 // against 0.21 and 0.24, 280 0.15 and 0.15 against 0.09 and 0.10.
 int kind_var(const dmft_handle h, int kind, int nbp, int nc, int nk, int nw) {
   const int var = choose_var(h, kind, nbp);
@@ -321,9 +323,11 @@ int kind_var(const dmft_handle h, int kind, int nbp, int nc, int nk, int nw) {
   bool other = !spec_adj_fits(nc, kind == KIND_TRACE);
   char key[32];
   snprintf(key, sizeof key, "%d/%d", kind, nbp);
-  if (nbp == 16 && nc > 10 && !h->tvar.count(key))
-    other = other || kind == KIND_TRACE ||
-            (kind == KIND_GENERAL && (nc <= 12 || (int64_t)nk * ((nw + 15) / 16) <= 700));
+  if (nbp == 16 && nc > 10 && !h->tvar.count(key)) {
+    const int64_t groups = (int64_t)nk * ((nw + 15) / 16);
+    other = other || (kind == KIND_TRACE && groups > 512) ||
+            (kind == KIND_GENERAL && (nc <= 12 || groups <= 700));
+  }
   if (!other) return var;
   int v[16];
   const int n = dyson_variants(nbp, kind, v, 16);
