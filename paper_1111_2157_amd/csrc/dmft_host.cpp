@@ -954,17 +954,10 @@ int dmft_workspace_size(dmft_handle h, const dmft_lattice* lat, const dmft_sigma
   if (!bytes) return fail(h, DMFT_EINVAL, "bytes is NULL");
   int r = check_shapes(h, lat, sig);
   if (r) return r;
-  Layout L, L2;
-  r = make_layout(h, lat, sig, L, KIND_DENSITY);
+  Layout L;
+  r = make_layout(h, lat, sig, L, KIND_DENSITY);  // no smaller than those of the other kinds
   if (r) return r;
-  r = make_layout(h, lat, sig, L2, KIND_TRACE);
-  if (r) return r;
-  Layout L3, L4;
-  r = make_layout(h, lat, sig, L3, KIND_ADJOINT);
-  if (r) return r;
-  r = make_layout(h, lat, sig, L4, KIND_GENERAL);
-  if (r) return r;
-  *bytes = std::max(std::max(L.total, L2.total), std::max(L3.total, L4.total));
+  *bytes = L.total;
   return DMFT_OK;
 }
 
