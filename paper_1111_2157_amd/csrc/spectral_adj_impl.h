@@ -28,7 +28,7 @@
 // Measured, per k-point and frequency, with the frequency-at-a-time low-rank kernels in
 // brackets (256 k-points, 512 or 1024 frequencies): trace, 64 bands and 5 orbitals 1.4 ns
 // (6.1), 30 and 10 3.3 (4.8), 40 and 14 5.8 (6.8); scalar adjoint 2.1 (8.4), 4.4 (7.3)
-// and 8.1 (10); general product, 40 and 14, 17.0 (28.3).  At 40 bands and 14 orbitals the
+// and 8.0 (10); general product, 40 and 14, 16.5 (28.3).  At 40 bands and 14 orbitals the
 // products and inversions would take 4.7, 5.8 and 9.9 ns at full rate: the scalar
 // adjoint and the traces lose the rest to stage changes, and the general product to
 // fetching its 132 KB of straight-line code through the 64 KB instruction cache.  For
@@ -387,345 +387,345 @@ __device__ __forceinline__ void spec_adj_tile(const DysonArgs& a, int ktile, int
     // (two copies, see spec_tile; the traces are the same in the rows of Q, with
     // Sigma' there: tr G = tr D + tr(R_Q X_Q2), ...)
     auto frequencies = [&](auto obl) __attribute__((always_inline)) {
-    constexpr bool oblique = decltype(obl)::value;
-    for (int ng = n0; ng < n1; ng += 16) {
-      __syncthreads();  // the last group's matrix area and resolvent table are free
-      {
-        const int t = spec_here(tid), nl = t & 15, v0 = t >> 4;
-        const double wn = (double)(2 * min(ng + nl, n1 - 1) + 1) * pib;
-        lv2d* dt = spec_lds(&sh.dt[nl * DS + v0]);
-        const lds_double* es = (const lds_double*)&sh.eps[v0];
-        const lds_double* nt = (const lds_double*)&sh.ntd[v0];
-        const bool on = ng + nl < n1;
+      constexpr bool oblique = decltype(obl)::value;
+      for (int ng = n0; ng < n1; ng += 16) {
+        __syncthreads();  // the last group's matrix area and resolvent table are free
+        {
+          const int t = spec_here(tid), nl = t & 15, v0 = t >> 4;
+          const double wn = (double)(2 * min(ng + nl, n1 - 1) + 1) * pib;
+          lv2d* dt = spec_lds(&sh.dt[nl * DS + v0]);
+          const lds_double* es = (const lds_double*)&sh.eps[v0];
+          const lds_double* nt = (const lds_double*)&sh.ntd[v0];
+          const bool on = ng + nl < n1;
 #pragma unroll
-        for (int m = 0; m < T; ++m) {
-          const double2 d = inv_z_minus(mu, wn, es[16 * m]);
-          dt[16 * m] = (v2d){d.x, d.y};
-          const double d2 = __builtin_fma(d.x, d.x, -d.y * d.y);
-          if (on && v0 + 16 * m < nb) {
-            t1 += d.x;
-            t2 += d2;
-            if (GEN) mub -= ibeta * nt[16 * m] * d2;
-          }
-        }
-        if (v0 == 0) sh.dt[nl * DS + NBP] = make_double2(0.0, 0.0);
-      }
-      const int l = spec_here(tid & 63), i = l & 15, nl = 4 * w + (l >> 4), ic = min(i, NC - 1);
-      const bool valid = ng + nl < n1, mine = valid && i < NC;
-      const int n = min(ng + nl, n1 - 1);
-      double sr[NC], si[NC];  // row i of Sigma', in flight until it is needed
-      {
-        const gv2d* sgp = (const gv2d*)a.sigma + ((int64_t)n * nc + min(i, nc - 1)) * nc;
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          const v2d v = sgp[min(j, nc - 1)];
-          sr[j] = v.x;
-          si[j] = v.y;
-        }
-      }
-      __syncthreads();
-      Acc xa;
-      moments(I1{}, I1{}, xa);
-      publish(xa[0]);
-      lv2d* xb = spec_lds(&sh.xr[nl * NP]);
-      double gr[NC], gi[NC];
-      spec_pair_row<NC, false>(gr, gi, xb, ic);
-      const v2d own = xb[ic * NC + ic];
-      const unsigned long long absent = row_absent(own.x, own.y, i, nc);
-      if (absent) row_leave_out<NC>(gr, gi, absent, l, 1.0);
-      if (nc < NC) {
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          gr[j] = i < nc ? gr[j] : (i == j ? 1.0 : 0.0);
-          gi[j] = i < nc ? gi[j] : 0.0;
-          sr[j] = i < nc && j < nc ? sr[j] : 0.0;
-          si[j] = i < nc && j < nc ? si[j] : 0.0;
-        }
-      }
-      auto invert = [&](int t) {
-        spec_sweep<NC>(gr, gi, i, pmin);
-        if (t == 0) {
-#pragma unroll
-          for (int j = 0; j < NC; ++j) sr[j] -= i == j ? edc : 0.0;
-          if constexpr (oblique) {  // by way of the matrix area
-            spec_put_row<NC>(xb, i, sr, si);
-            spec_inner<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              const v2d x = xb[ic * NC + j];
-              sr[j] = x.x;
-              si[j] = x.y;
+          for (int m = 0; m < T; ++m) {
+            const double2 d = inv_z_minus(mu, wn, es[16 * m]);
+            dt[16 * m] = (v2d){d.x, d.y};
+            const double d2 = __builtin_fma(d.x, d.x, -d.y * d.y);
+            if (on && v0 + 16 * m < nb) {
+              t1 += d.x;
+              t2 += d2;
+              if (GEN) mub -= ibeta * nt[16 * m] * d2;
             }
           }
+          if (v0 == 0) sh.dt[nl * DS + NBP] = make_double2(0.0, 0.0);
+        }
+        const int l = spec_here(tid & 63), i = l & 15, nl = 4 * w + (l >> 4), ic = min(i, NC - 1);
+        const bool valid = ng + nl < n1, mine = valid && i < NC;
+        const int n = min(ng + nl, n1 - 1);
+        double sr[NC], si[NC];  // row i of Sigma', in flight until it is needed
+        {
+          const gv2d* sgp = (const gv2d*)a.sigma + ((int64_t)n * nc + min(i, nc - 1)) * nc;
 #pragma unroll
           for (int j = 0; j < NC; ++j) {
-            gr[j] -= sr[j];
-            gi[j] -= si[j];
+            const v2d v = sgp[min(j, nc - 1)];
+            sr[j] = v.x;
+            si[j] = v.y;
           }
-          if (absent) row_leave_out<NC>(gr, gi, absent, l, 1.0);
         }
-      };
-      if constexpr (ROLL) {
-#pragma clang loop unroll(disable)
-        for (int t = 0; t < 2; ++t) invert(t);
-      } else {
-        invert(0);
-        invert(1);
-      }
-      if (absent) row_leave_out<NC>(gr, gi, absent, l, 0.0);
-      if (nc < NC) {  // the identity of rows past nc must not count as part of Gl
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          gr[j] = i < nc && j < nc ? gr[j] : 0.0;
-          gi[j] = i < nc && j < nc ? gi[j] : 0.0;
-        }
-      }
-      if constexpr (GEN) {
-        double chk = 0.0;
-#pragma unroll
-        for (int j = 0; j < NC; ++j) chk += gr[j] + gi[j];
-        if (mine && !__builtin_isfinite(chk)) nonfinite = 1;
-      }
-      // The order below keeps few row matrices alive at a time (4 registers per
-      // column): the moment that is only traced against R goes first.
-      const gv2d* gbp = (const gv2d*)a.gbar + (int64_t)n * nc * nc + min(i, nc - 1);
-      auto load_gbar = [&](double (&ar)[NC], double (&ai)[NC]) {  // row i of w_k Gbar^dag
-        if (WHAT == SPEC_GEN_G && !a.gbar) return spec_zero<NC>(ar, ai);
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          const v2d v = gbp[min(j, nc - 1) * nc];
-          ar[j] = wk * v.x;
-          ai[j] = -wk * v.y;
-        }
+        __syncthreads();
+        Acc xa;
+        moments(I1{}, I1{}, xa);
+        publish(xa[0]);
+        lv2d* xb = spec_lds(&sh.xr[nl * NP]);
+        double gr[NC], gi[NC];
+        spec_pair_row<NC, false>(gr, gi, xb, ic);
+        const v2d own = xb[ic * NC + ic];
+        const unsigned long long absent = row_absent(own.x, own.y, i, nc);
+        if (absent) row_leave_out<NC>(gr, gi, absent, l, 1.0);
         if (nc < NC) {
 #pragma unroll
           for (int j = 0; j < NC; ++j) {
-            ar[j] = i < nc && j < nc ? ar[j] : 0.0;
-            ai[j] = i < nc && j < nc ? ai[j] : 0.0;
+            gr[j] = i < nc ? gr[j] : (i == j ? 1.0 : 0.0);
+            gi[j] = i < nc ? gi[j] : 0.0;
+            sr[j] = i < nc && j < nc ? sr[j] : 0.0;
+            si[j] = i < nc && j < nc ? si[j] : 0.0;
           }
         }
-      };
-      double xr[NC], xi[NC], br[NC], bi[NC], cr[NC], ci[NC];  // c += x b at every step
-      double nr[GEN ? NC : 1], ni[GEN ? NC : 1];              // Sigmabar^dag, then K
-      if constexpr (GEN) {
-        spec_zero<NC>(nr, ni);
-        if constexpr (has_g) {  // w_k Gl Gbar^dag Gl
-          spec_set<NC>(xr, xi, gr, gi);
-          load_gbar(br, bi);
-          spec_zero<NC>(cr, ci);
-          spec_steps<2>(0, [&](int t) {
-            spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
-            if (t == 0) {
-              spec_set<NC>(xr, xi, cr, ci);
-              spec_set<NC>(br, bi, gr, gi);
-              spec_zero<NC>(cr, ci);
+        auto invert = [&](int t) {
+          spec_sweep<NC>(gr, gi, i, pmin);
+          if (t == 0) {
+#pragma unroll
+            for (int j = 0; j < NC; ++j) sr[j] -= i == j ? edc : 0.0;
+            if constexpr (oblique) {  // by way of the matrix area
+              spec_put_row<NC>(xb, i, sr, si);
+              spec_inner<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                const v2d x = xb[ic * NC + j];
+                sr[j] = x.x;
+                si[j] = x.y;
+              }
             }
-            return true;
-          });
-          if constexpr (STASH)
-            stash(cr, ci);
-          else
-            spec_set<NC>(nr, ni, cr, ci);
-        }
-      }
-      // V = Gl Sigma', V' = Sigma' Gl (not for the traces), R = Sigma' + Sigma' V (in c; x = Sigma')
-      double vr[NC], vi[NC], ur[WHAT == SPEC_TRACE ? 1 : NC], ui[WHAT == SPEC_TRACE ? 1 : NC];
-      spec_set<NC>(xr, xi, gr, gi);
-      spec_set<NC>(br, bi, sr, si);
-      spec_zero<NC>(cr, ci);
-      spec_steps<3>(0, [&](int t) {
-        spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
-        if (t == 0) {
-          spec_set<NC>(vr, vi, cr, ci);
-          if constexpr (WHAT == SPEC_TRACE) {
-            spec_set<NC>(xr, xi, br, bi);
-            spec_set<NC>(cr, ci, br, bi);
-            spec_set<NC>(br, bi, vr, vi);
-          } else {
-            double tr[NC], ti[NC];
-            spec_set<NC>(tr, ti, xr, xi);
-            spec_set<NC>(xr, xi, br, bi);
-            spec_set<NC>(br, bi, tr, ti);
-            spec_zero<NC>(cr, ci);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              gr[j] -= sr[j];
+              gi[j] -= si[j];
+            }
+            if (absent) row_leave_out<NC>(gr, gi, absent, l, 1.0);
           }
-          return true;
-        }
-        if (WHAT == SPEC_TRACE || t == 2) return false;
-        if constexpr (WHAT != SPEC_TRACE) {
-          if constexpr (STASH && WHAT == SPEC_ADJ)
-            stash(cr, ci);
-          else
-            spec_set<NC>(ur, ui, cr, ci);
-          spec_set<NC>(cr, ci, xr, xi);
-          spec_set<NC>(br, bi, vr, vi);
-        }
-        return true;
-      });
-      double rr[NC], ri[NC];
-      spec_set<NC>(rr, ri, cr, ci);
-      if constexpr (!GEN) {
-        if constexpr (WHAT == SPEC_ADJ) spec_set<NC>(sr, si, xr, xi);
-        moments(I2{}, I2{}, xa);
-        publish(xa[1]);
-        spec_pair_row<NC, true>(cr, ci, xb, ic);  // X_3
-        const double r3 = spec_row_dot<NC>(rr, ri, cr, ci);
-        publish(xa[0]);
-        if (mine) t2 += 2.0 * r3;
-        spec_pair_row<NC, false>(br, bi, xb, ic);
-        if constexpr (WHAT == SPEC_TRACE) {
-          spec_zero<NC>(cr, ci);
-          spec_mat_mac<NC>(cr, ci, rr, ri, br, bi);  // R X_2
+        };
+        if constexpr (ROLL) {
+#pragma clang loop unroll(disable)
+          for (int t = 0; t < 2; ++t) invert(t);
         } else {
-          // T = L X_2, M = T L', R X_2 = Sigma' T
-          double tr[NC], ti[NC];
-          spec_set<NC>(xr, xi, vr, vi);
-          spec_set<NC>(cr, ci, br, bi);
-          spec_steps<3>(0, [&](int t) {
-            spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
-            if (t == 0) {
-              spec_set<NC>(tr, ti, cr, ci);
-              spec_set<NC>(xr, xi, cr, ci);
-              if constexpr (STASH)
-                unstash(br, bi);
-              else
-                spec_set<NC>(br, bi, ur, ui);
-            } else if (t == 1) {
-              // M by columns (through this matrix's own part of the matrix area), so that
-              // the partial is read and written 16 lanes to a row
-              wave_sync();
-              if (i < NC) {
+          invert(0);
+          invert(1);
+        }
+        if (absent) row_leave_out<NC>(gr, gi, absent, l, 0.0);
+        if (nc < NC) {  // the identity of rows past nc must not count as part of Gl
 #pragma unroll
-                for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){cr[j], ci[j]};
+          for (int j = 0; j < NC; ++j) {
+            gr[j] = i < nc && j < nc ? gr[j] : 0.0;
+            gi[j] = i < nc && j < nc ? gi[j] : 0.0;
+          }
+        }
+        if constexpr (GEN) {
+          double chk = 0.0;
+#pragma unroll
+          for (int j = 0; j < NC; ++j) chk += gr[j] + gi[j];
+          if (mine && !__builtin_isfinite(chk)) nonfinite = 1;
+        }
+        // The order below keeps few row matrices alive at a time (4 registers per
+        // column): the moment that is only traced against R goes first.
+        const gv2d* gbp = (const gv2d*)a.gbar + (int64_t)n * nc * nc + min(i, nc - 1);
+        auto load_gbar = [&](double (&ar)[NC], double (&ai)[NC]) {  // row i of w_k Gbar^dag
+          if (WHAT == SPEC_GEN_G && !a.gbar) return spec_zero<NC>(ar, ai);
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            const v2d v = gbp[min(j, nc - 1) * nc];
+            ar[j] = wk * v.x;
+            ai[j] = -wk * v.y;
+          }
+          if (nc < NC) {
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              ar[j] = i < nc && j < nc ? ar[j] : 0.0;
+              ai[j] = i < nc && j < nc ? ai[j] : 0.0;
+            }
+          }
+        };
+        double xr[NC], xi[NC], br[NC], bi[NC], cr[NC], ci[NC];  // c += x b at every step
+        double nr[GEN ? NC : 1], ni[GEN ? NC : 1];              // Sigmabar^dag, then K
+        if constexpr (GEN) {
+          spec_zero<NC>(nr, ni);
+          if constexpr (has_g) {  // w_k Gl Gbar^dag Gl
+            spec_set<NC>(xr, xi, gr, gi);
+            load_gbar(br, bi);
+            spec_zero<NC>(cr, ci);
+            spec_steps<2>(0, [&](int t) {
+              spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
+              if (t == 0) {
+                spec_set<NC>(xr, xi, cr, ci);
+                spec_set<NC>(br, bi, gr, gi);
+                spec_zero<NC>(cr, ci);
               }
-              wave_sync();
-              if (mine) {
-                gv2d* mp = (gv2d*)a.xpart + ((int64_t)(a.ktile_base + ktile) * a.nw + n) * 256 + i;
-                v2d o[NC], z[NC];
-#pragma unroll
-                for (int j = 0; j < NC; ++j) {
-                  o[j] = (v2d){0.0, 0.0};
-                  z[j] = xb[j * NC + i];
-                }
-                if (kk != kk0) {
-#pragma unroll
-                  for (int j = 0; j < NC; ++j) o[j] = mp[j * 16];
-                }
-#pragma unroll
-                for (int j = 0; j < NC; ++j)
-                  mp[j * 16] = (v2d){__builtin_fma(wk, z[j].x, o[j].x), __builtin_fma(wk, z[j].y, o[j].y)};
-              }
-              spec_set<NC>(xr, xi, sr, si);
+              return true;
+            });
+            if constexpr (STASH)
+              stash(cr, ci);
+            else
+              spec_set<NC>(nr, ni, cr, ci);
+          }
+        }
+        // V = Gl Sigma', V' = Sigma' Gl (not for the traces), R = Sigma' + Sigma' V (in c; x = Sigma')
+        double vr[NC], vi[NC], ur[WHAT == SPEC_TRACE ? 1 : NC], ui[WHAT == SPEC_TRACE ? 1 : NC];
+        spec_set<NC>(xr, xi, gr, gi);
+        spec_set<NC>(br, bi, sr, si);
+        spec_zero<NC>(cr, ci);
+        spec_steps<3>(0, [&](int t) {
+          spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
+          if (t == 0) {
+            spec_set<NC>(vr, vi, cr, ci);
+            if constexpr (WHAT == SPEC_TRACE) {
+              spec_set<NC>(xr, xi, br, bi);
+              spec_set<NC>(cr, ci, br, bi);
+              spec_set<NC>(br, bi, vr, vi);
+            } else {
+              double tr[NC], ti[NC];
+              spec_set<NC>(tr, ti, xr, xi);
+              spec_set<NC>(xr, xi, br, bi);
               spec_set<NC>(br, bi, tr, ti);
               spec_zero<NC>(cr, ci);
             }
             return true;
-          });
-        }
-        // tr((R X_2)^2): the transpose the same way
-        wave_sync();
-        if (i < NC) {
-#pragma unroll
-          for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){cr[j], ci[j]};
-        }
-        wave_sync();
-        double q1 = 0.0, q2 = 0.0;
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          const v2d z = xb[j * NC + ic];
-          q1 = i == j ? cr[j] : q1;
-          q2 = __builtin_fma(cr[j], z.x, __builtin_fma(-ci[j], z.y, q2));
-        }
-        if (mine) {
-          t1 += q1;
-          t2 += q2;
-        }
-      } else {
-        auto store = [&](const double (&ar)[NC], const double (&ai)[NC]) {
-          if (!mine) return;  // Sigmabar = (..)^dag: this lane's row is a column of it
-          gv2d* mp = (gv2d*)a.xpart + ((int64_t)(a.ktile_base + ktile) * a.nw + n) * 256 + i;
-          v2d o[NC];
-#pragma unroll
-          for (int j = 0; j < NC; ++j) o[j] = (v2d){0.0, 0.0};
-          if (kk != kk0) {
-#pragma unroll
-            for (int j = 0; j < NC; ++j) o[j] = mp[j * 16];
           }
-#pragma unroll
-          for (int j = 0; j < NC; ++j) mp[j * 16] = (v2d){o[j].x + ar[j], o[j].y - ai[j]};
-        };
-        auto load_q = [&]() {  // Q / beta
+          if (WHAT == SPEC_TRACE || t == 2) return false;
+          if constexpr (WHAT != SPEC_TRACE) {
+            if constexpr (STASH && WHAT == SPEC_ADJ)
+              stash(cr, ci);
+            else
+              spec_set<NC>(ur, ui, cr, ci);
+            spec_set<NC>(cr, ci, xr, xi);
+            spec_set<NC>(br, bi, vr, vi);
+          }
+          return true;
+        });
+        double rr[NC], ri[NC];
+        spec_set<NC>(rr, ri, cr, ci);
+        if constexpr (!GEN) {
+          if constexpr (WHAT == SPEC_ADJ) spec_set<NC>(sr, si, xr, xi);
+          moments(I2{}, I2{}, xa);
+          publish(xa[1]);
+          spec_pair_row<NC, true>(cr, ci, xb, ic);  // X_3
+          const double r3 = spec_row_dot<NC>(rr, ri, cr, ci);
+          publish(xa[0]);
+          if (mine) t2 += 2.0 * r3;
           spec_pair_row<NC, false>(br, bi, xb, ic);
+          if constexpr (WHAT == SPEC_TRACE) {
+            spec_zero<NC>(cr, ci);
+            spec_mat_mac<NC>(cr, ci, rr, ri, br, bi);  // R X_2
+          } else {
+            // T = L X_2, M = T L', R X_2 = Sigma' T
+            double tr[NC], ti[NC];
+            spec_set<NC>(xr, xi, vr, vi);
+            spec_set<NC>(cr, ci, br, bi);
+            spec_steps<3>(0, [&](int t) {
+              spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
+              if (t == 0) {
+                spec_set<NC>(tr, ti, cr, ci);
+                spec_set<NC>(xr, xi, cr, ci);
+                if constexpr (STASH)
+                  unstash(br, bi);
+                else
+                  spec_set<NC>(br, bi, ur, ui);
+              } else if (t == 1) {
+                // M by columns (through this matrix's own part of the matrix area), so that
+                // the partial is read and written 16 lanes to a row
+                wave_sync();
+                if (i < NC) {
+#pragma unroll
+                  for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){cr[j], ci[j]};
+                }
+                wave_sync();
+                if (mine) {
+                  gv2d* mp = (gv2d*)a.xpart + ((int64_t)(a.ktile_base + ktile) * a.nw + n) * 256 + i;
+                  v2d o[NC], z[NC];
+#pragma unroll
+                  for (int j = 0; j < NC; ++j) {
+                    o[j] = (v2d){0.0, 0.0};
+                    z[j] = xb[j * NC + i];
+                  }
+                  if (kk != kk0) {
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) o[j] = mp[j * 16];
+                  }
+#pragma unroll
+                  for (int j = 0; j < NC; ++j)
+                    mp[j * 16] = (v2d){__builtin_fma(wk, z[j].x, o[j].x), __builtin_fma(wk, z[j].y, o[j].y)};
+                }
+                spec_set<NC>(xr, xi, sr, si);
+                spec_set<NC>(br, bi, tr, ti);
+                spec_zero<NC>(cr, ci);
+              }
+              return true;
+            });
+          }
+          // tr((R X_2)^2): the transpose the same way
+          wave_sync();
+          if (i < NC) {
+#pragma unroll
+            for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){cr[j], ci[j]};
+          }
+          wave_sync();
+          double q1 = 0.0, q2 = 0.0;
 #pragma unroll
           for (int j = 0; j < NC; ++j) {
-            br[j] *= ibeta;
-            bi[j] *= ibeta;
+            const v2d z = xb[j * NC + ic];
+            q1 = i == j ? cr[j] : q1;
+            q2 = __builtin_fma(cr[j], z.x, __builtin_fma(-ci[j], z.y, q2));
           }
-        };
-        auto start_g = [&]() {  // L' Gbar^dag next
-          spec_set<NC>(xr, xi, ur, ui);
-          load_gbar(br, bi);
-          spec_set<NC>(cr, ci, br, bi);
-        };
-        if constexpr (has_n) {
-          rows(xa);
-          publish(xa[1]);
-          spec_pair_row<NC, true>(cr, ci, xb, ic);  // Q_3
-          const double r3 = spec_row_dot<NC>(rr, ri, cr, ci);
-          if (mine) mub -= ibeta * r3;
-          publish(xa[0]);
-          spec_set<NC>(xr, xi, vr, vi);
-          load_q();
-          spec_set<NC>(cr, ci, br, bi);
+          if (mine) {
+            t1 += q1;
+            t2 += q2;
+          }
         } else {
-          store(nr, ni);
-          spec_zero<NC>(nr, ni);
-          start_g();
-        }
-        {
-          spec_steps<6>(has_n ? 0 : 4, [&](int t) {
-            spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
-            if (t == 0) {  // L Q; L Q L' next, on top of the Gbar part
-              spec_set<NC>(xr, xi, cr, ci);
-              spec_set<NC>(br, bi, ur, ui);
-              if constexpr (STASH) unstash(nr, ni);
+          auto store = [&](const double (&ar)[NC], const double (&ai)[NC]) {
+            if (!mine) return;  // Sigmabar = (..)^dag: this lane's row is a column of it
+            gv2d* mp = (gv2d*)a.xpart + ((int64_t)(a.ktile_base + ktile) * a.nw + n) * 256 + i;
+            v2d o[NC];
 #pragma unroll
-              for (int j = 0; j < NC; ++j) {
-                cr[j] += nr[j];
-                ci[j] += ni[j];
-              }
-            } else if (t == 1) {  // R Q next
-              store(cr, ci);
-              spec_set<NC>(xr, xi, rr, ri);
-              load_q();
-              spec_zero<NC>(cr, ci);
-            } else if (t == 2) {  // R Q R next
-              spec_set<NC>(xr, xi, cr, ci);
-              spec_set<NC>(br, bi, rr, ri);
-              spec_zero<NC>(cr, ci);
-            } else if (t == 3) {
-              if (!has_g) return false;
-              spec_set<NC>(nr, ni, cr, ci);
-              start_g();
-            } else if (t == 4) {  // L' Gbar^dag L next
-              spec_set<NC>(xr, xi, cr, ci);
-              spec_set<NC>(br, bi, vr, vi);
+            for (int j = 0; j < NC; ++j) o[j] = (v2d){0.0, 0.0};
+            if (kk != kk0) {
 #pragma unroll
-              for (int j = 0; j < NC; ++j) {
-                cr[j] += nr[j];
-                ci[j] += ni[j];
-              }
+              for (int j = 0; j < NC; ++j) o[j] = mp[j * 16];
             }
-            return true;
-          });
-          spec_set<NC>(nr, ni, cr, ci);  // K
-          moments(I2{}, I1{}, xa);
-          publish(xa[0]);
-          spec_pair_row<NC, true>(cr, ci, xb, ic);  // X_2
-          const double x2 = spec_row_dot<NC>(nr, ni, cr, ci);
-          if (mine) mub -= x2;
+#pragma unroll
+            for (int j = 0; j < NC; ++j) mp[j * 16] = (v2d){o[j].x + ar[j], o[j].y - ai[j]};
+          };
+          auto load_q = [&]() {  // Q / beta
+            spec_pair_row<NC, false>(br, bi, xb, ic);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              br[j] *= ibeta;
+              bi[j] *= ibeta;
+            }
+          };
+          auto start_g = [&]() {  // L' Gbar^dag next
+            spec_set<NC>(xr, xi, ur, ui);
+            load_gbar(br, bi);
+            spec_set<NC>(cr, ci, br, bi);
+          };
+          if constexpr (has_n) {
+            rows(xa);
+            publish(xa[1]);
+            spec_pair_row<NC, true>(cr, ci, xb, ic);  // Q_3
+            const double r3 = spec_row_dot<NC>(rr, ri, cr, ci);
+            if (mine) mub -= ibeta * r3;
+            publish(xa[0]);
+            spec_set<NC>(xr, xi, vr, vi);
+            load_q();
+            spec_set<NC>(cr, ci, br, bi);
+          } else {
+            store(nr, ni);
+            spec_zero<NC>(nr, ni);
+            start_g();
+          }
+          {
+            spec_steps<6>(has_n ? 0 : 4, [&](int t) {
+              spec_mat_mac<NC>(cr, ci, xr, xi, br, bi);
+              if (t == 0) {  // L Q; L Q L' next, on top of the Gbar part
+                spec_set<NC>(xr, xi, cr, ci);
+                spec_set<NC>(br, bi, ur, ui);
+                if constexpr (STASH) unstash(nr, ni);
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
+                  cr[j] += nr[j];
+                  ci[j] += ni[j];
+                }
+              } else if (t == 1) {  // R Q next
+                store(cr, ci);
+                spec_set<NC>(xr, xi, rr, ri);
+                load_q();
+                spec_zero<NC>(cr, ci);
+              } else if (t == 2) {  // R Q R next
+                spec_set<NC>(xr, xi, cr, ci);
+                spec_set<NC>(br, bi, rr, ri);
+                spec_zero<NC>(cr, ci);
+              } else if (t == 3) {
+                if (!has_g) return false;
+                spec_set<NC>(nr, ni, cr, ci);
+                start_g();
+              } else if (t == 4) {  // L' Gbar^dag L next
+                spec_set<NC>(xr, xi, cr, ci);
+                spec_set<NC>(br, bi, vr, vi);
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
+                  cr[j] += nr[j];
+                  ci[j] += ni[j];
+                }
+              }
+              return true;
+            });
+            spec_set<NC>(nr, ni, cr, ci);  // K
+            moments(I2{}, I1{}, xa);
+            publish(xa[0]);
+            spec_pair_row<NC, true>(cr, ci, xb, ic);  // X_2
+            const double x2 = spec_row_dot<NC>(nr, ni, cr, ci);
+            if (mine) mub -= x2;
+          }
         }
       }
-    }
     };
     if constexpr (WHAT == SPEC_TRACE) {
       if (uniform_i(sh.use_q))

@@ -23,9 +23,9 @@
 // H(j, j+1) themselves change sign across mu, and between distant bands on either
 // side H(v, v') is smaller than its terms: single elements of N(k) lose that ratio
 // (48 bands, beta 4000: 3e-12 of an element against 8e-14 of the band-window inversion),
-// the matrix does not (2e-14 against 1e-15, against 80-bit values).  The frequency loop therefore accumulates only the 2 nb - 1 matrices
-// H(v, v) and H(j, j+1) (rows 2v and 2j+1 of one real matrix product over the
-// frequencies), and the epilogue (spec_epilogue_kernel) forms N(k) from them
+// the matrix does not (2e-14 against 1e-15, against 80-bit values).  The frequency
+// loop therefore accumulates only the 2 nb - 1 matrices H(v, v) and H(j, j+1) (rows
+// 2v and 2j+1 of one real matrix product over the frequencies), and the epilogue (spec_epilogue_kernel) forms N(k) from them
 // once per k-point.  Per evaluation the matrix cores run 4 nb nc^2 (X) and
 // 8 nb nc^2 (sums) real flops, without the nb x nb or nb x nc complex products
 // of the other low-rank kernels.
@@ -44,8 +44,8 @@
 // full 16x16x4 products and B on uniform row operations.
 //
 // Measured (512 k-points, 2048 frequencies, per k-point and frequency; in brackets
-// the frequency-at-a-time low-rank kernels, tuned): 32 bands and 10 orbitals 2.37 ns
-// (5.3), 48 and 14 5.28 (10.2), 64 and 14 5.97.  At 48 and 14 the matrix products with
+// the frequency-at-a-time low-rank kernels, tuned): 32 bands and 10 orbitals 2.41 ns
+// (5.3), 48 and 14 5.35 (10.2), 64 and 14 6.01.  At 48 and 14 the matrix products with
 // their padding would take 2.0 ns at full rate and the row operations of B 2.1; what
 // bounds the rest is that the two units do not run FP64 together and a SIMD holds one
 // wavefront (its row matrices, sums and operands fill the registers), so the LDS round
@@ -670,269 +670,270 @@ __device__ __forceinline__ void spec_tile(const DysonArgs& a, int ktile, int wti
       for (int t = 0; t < CT; ++t) acc[r][t] = (v4d){0.0, 0.0, 0.0, 0.0};
 
     int cur = 0;
-    // the frequencies, for oblique rows or others: two copies of the loop, because the
+    // the frequencies, for rows in Q or as they are: two copies of the loop, because the
     // former's extra work costs the latter registers where they share one (48 bands, 14
-    // orbitals 1.3%, 5 orbitals up to 10%)
+    // orbitals 1.3%, 5 orbitals up to 8% more time; now 1% and 3% with the look at the rows)
     auto frequencies = [&](auto obl) __attribute__((always_inline)) {
-    constexpr bool oblique = decltype(obl)::value;
-    for (int ng = n0; ng < n1; ng += 16, cur ^= 1) {
-      // row c16 of Sigma of this lane's stage-B frequency, in flight during stage A
-      // (rows and columns past nc repeat the last one and are cleared below)
-      double sr[NC], si[NC];
-      {
-        const int l = spec_here(tid & 63), i = min(l & 15, nc - 1), n = min(ng + 4 * w + (l >> 4), n1 - 1);
-        const gv2d* sgp = (const gv2d*)a.sigma + ((int64_t)n * nc + i) * nc;
+      constexpr bool oblique = decltype(obl)::value;
+      for (int ng = n0; ng < n1; ng += 16, cur ^= 1) {
+        // row c16 of Sigma of this lane's stage-B frequency, in flight during stage A
+        // (rows and columns past nc repeat the last one and are cleared below)
+        double sr[NC], si[NC];
+        {
+          const int l = spec_here(tid & 63), i = min(l & 15, nc - 1), n = min(ng + 4 * w + (l >> 4), n1 - 1);
+          const gv2d* sgp = (const gv2d*)a.sigma + ((int64_t)n * nc + i) * nc;
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          const v2d v = sgp[min(j, nc - 1)];
-          sr[j] = v.x;
-          si[j] = v.y;
-        }
-      }
-      // ---- stage A (a wavefront with fewer jobs repeats its last column: the others set the time)
-      {
-        const int l = spec_here(tid & 63), q = l >> 4, c16 = l & 15;
-        const lv2d* dt = spec_lds(&sh.dt[cur][c16 * DS + q]);
-        v4d xa[TPW][SPLIT ? 1 : 2];
-        const lv2d *sa[TPW], *sb[TPW];
-#pragma unroll
-        for (int m = 0; m < TPW; ++m) {
-          if constexpr (!Dm::PREG) {
-            const int ab = spec_here(pab[m]);
-            sa[m] = spec_lds(&sh.sp[ab & 0xffff]);
-            sb[m] = spec_lds(&sh.sp[ab >> 16]);
+          for (int j = 0; j < NC; ++j) {
+            const v2d v = sgp[min(j, nc - 1)];
+            sr[j] = v.x;
+            si[j] = v.y;
           }
-#pragma unroll
-          for (int h = 0; h < (SPLIT ? 1 : 2); ++h) xa[m][h] = (v4d){0.0, 0.0, 0.0, 0.0};
         }
-        // operands one band chunk ahead: two products take 128 cycles, about an LDS
-        // round trip, so loads issued at their use would be waited for every time
-        v2d d[2], x[2][Dm::PREG ? 1 : TPW], y[2][Dm::PREG ? 1 : TPW];
-        auto fetch = [&](int c, int s) {
-          d[s] = dt[4 * c];
-          if constexpr (!Dm::PREG) {
+        // ---- stage A (a wavefront with fewer jobs repeats its last column: the others set the time)
+        {
+          const int l = spec_here(tid & 63), q = l >> 4, c16 = l & 15;
+          const lv2d* dt = spec_lds(&sh.dt[cur][c16 * DS + q]);
+          v4d xa[TPW][SPLIT ? 1 : 2];
+          const lv2d *sa[TPW], *sb[TPW];
+#pragma unroll
+          for (int m = 0; m < TPW; ++m) {
+            if constexpr (!Dm::PREG) {
+              const int ab = spec_here(pab[m]);
+              sa[m] = spec_lds(&sh.sp[ab & 0xffff]);
+              sb[m] = spec_lds(&sh.sp[ab >> 16]);
+            }
+#pragma unroll
+            for (int h = 0; h < (SPLIT ? 1 : 2); ++h) xa[m][h] = (v4d){0.0, 0.0, 0.0, 0.0};
+          }
+          // operands one band chunk ahead: two products take 128 cycles, about an LDS
+          // round trip, so loads issued at their use would be waited for every time
+          v2d d[2], x[2][Dm::PREG ? 1 : TPW], y[2][Dm::PREG ? 1 : TPW];
+          auto fetch = [&](int c, int s) {
+            d[s] = dt[4 * c];
+            if constexpr (!Dm::PREG) {
+#pragma unroll
+              for (int m = 0; m < TPW; ++m) {
+                x[s][m] = sa[m][4 * c];
+                y[s][m] = sb[m][4 * c];
+              }
+            }
+          };
+          fetch(0, 0);
+          spec_for<0, NBP / 4>([&](auto ci) {
+            constexpr int c = decltype(ci)::value;
+            if (4 * c >= nb) return;
+            if constexpr (c + 1 < NBP / 4) fetch(c + 1, (c + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            // all vector work of the chunk before its products: the vector and matrix
+            // units do not run FP64 together, and each change from one to the other
+            // drains the pipe (70 cycles measured)
+            double pv[TPW];
 #pragma unroll
             for (int m = 0; m < TPW; ++m) {
-              x[s][m] = sa[m][4 * c];
-              y[s][m] = sb[m][4 * c];
+              if constexpr (Dm::PREG)
+                pv[m] = p[m][c];
+              else
+                pv[m] = __builtin_fma(x[c & 1][m].x, y[c & 1][m].x, x[c & 1][m].y * y[c & 1][m].y);
+            }
+            const double dx = SPLIT && (w & 1) ? d[c & 1].y : d[c & 1].x;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < TPW; ++m) {
+              xa[m][0] = mma(dx, pv[m], xa[m][0]);
+              if constexpr (!SPLIT) xa[m][1] = mma(d[c & 1].y, pv[m], xa[m][1]);
+            }
+          });
+          __syncthreads();  // the previous group's stage C has read xr
+          lv2d* xw = spec_lds(&sh.xr[q * NP + c16]);
+#pragma unroll
+          for (int m = 0; m < TPW; ++m) {
+            const int job = w + 4 * m;
+            if (job >= (SPLIT ? 2 * NT : NT)) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              if constexpr (SPLIT)
+                ((__attribute__((address_space(3))) double*)(xw + 4 * i * NP + 16 * (job >> 1)))[job & 1] = xa[m][0][i];
+              else
+                xw[4 * i * NP + 16 * job] = (v2d){xa[m][0][i], xa[m][1][i]};
             }
           }
-        };
-        fetch(0, 0);
-        spec_for<0, NBP / 4>([&](auto ci) {
-          constexpr int c = decltype(ci)::value;
-          if (4 * c >= nb) return;
-          if constexpr (c + 1 < NBP / 4) fetch(c + 1, (c + 1) & 1);
-          __builtin_amdgcn_sched_barrier(0);
-          // all vector work of the chunk before its products: the vector and matrix
-          // units do not run FP64 together, and each change from one to the other
-          // drains the pipe (70 cycles measured)
-          double pv[TPW];
-#pragma unroll
-          for (int m = 0; m < TPW; ++m) {
-            if constexpr (Dm::PREG)
-              pv[m] = p[m][c];
-            else
-              pv[m] = __builtin_fma(x[c & 1][m].x, y[c & 1][m].x, x[c & 1][m].y * y[c & 1][m].y);
-          }
-          const double dx = SPLIT && (w & 1) ? d[c & 1].y : d[c & 1].x;
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int m = 0; m < TPW; ++m) {
-            xa[m][0] = mma(dx, pv[m], xa[m][0]);
-            if constexpr (!SPLIT) xa[m][1] = mma(d[c & 1].y, pv[m], xa[m][1]);
-          }
-        });
-        __syncthreads();  // the previous group's stage C has read xr
-        lv2d* xw = spec_lds(&sh.xr[q * NP + c16]);
-#pragma unroll
-        for (int m = 0; m < TPW; ++m) {
-          const int job = w + 4 * m;
-          if (job >= (SPLIT ? 2 * NT : NT)) break;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if constexpr (SPLIT)
-              ((__attribute__((address_space(3))) double*)(xw + 4 * i * NP + 16 * (job >> 1)))[job & 1] = xa[m][0][i];
-            else
-              xw[4 * i * NP + 16 * job] = (v2d){xa[m][0][i], xa[m][1][i]};
-          }
         }
-      }
-      __syncthreads();
-      // ---- stage B: four matrices per wavefront in the row layout
-      {
-        const int l = spec_here(tid & 63), i = l & 15, nl = 4 * w + (l >> 4);
-        const bool valid = ng + nl < n1;
-        const int ic = min(i, NC - 1);
-        lv2d* xb = spec_lds(&sh.xr[nl * NP]);
-        double rr[NC], ri[NC];
-        v2d own;  // X_ii
-        // row i of X from its Hermitian pairs (lanes past the NC rows repeat the last
-        // one; nothing of theirs is read by another lane or kept)
+        __syncthreads();
+        // ---- stage B: four matrices per wavefront in the row layout
         {
-          v2d re[NC], im[NC];
+          const int l = spec_here(tid & 63), i = l & 15, nl = 4 * w + (l >> 4);
+          const bool valid = ng + nl < n1;
+          const int ic = min(i, NC - 1);
+          lv2d* xb = spec_lds(&sh.xr[nl * NP]);
+          double rr[NC], ri[NC];
+          v2d own;  // X_ii
+          // row i of X from its Hermitian pairs (lanes past the NC rows repeat the last
+          // one; nothing of theirs is read by another lane or kept)
+          {
+            v2d re[NC], im[NC];
 #pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            const int lo = min(ic, j), hi = max(ic, j);
-            re[j] = xb[lo * NC + hi];
-            im[j] = xb[hi * NC + lo];
+            for (int j = 0; j < NC; ++j) {
+              const int lo = min(ic, j), hi = max(ic, j);
+              re[j] = xb[lo * NC + hi];
+              im[j] = xb[hi * NC + lo];
+            }
+            own = xb[ic * NC + ic];
+            __builtin_amdgcn_sched_barrier(0);  // every read issued before the first is waited for
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              const double s = ic < j ? 1.0 : (ic > j ? -1.0 : 0.0);
+              rr[j] = __builtin_fma(-s, im[j].y, re[j].x);
+              ri[j] = __builtin_fma(s, im[j].x, re[j].y);
+            }
           }
-          own = xb[ic * NC + ic];
-          __builtin_amdgcn_sched_barrier(0);  // every read issued before the first is waited for
+          if (nc < NC) {
 #pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            const double s = ic < j ? 1.0 : (ic > j ? -1.0 : 0.0);
-            rr[j] = __builtin_fma(-s, im[j].y, re[j].x);
-            ri[j] = __builtin_fma(s, im[j].x, re[j].y);
+            for (int j = 0; j < NC; ++j) {
+              rr[j] = i < nc ? rr[j] : (i == j ? 1.0 : 0.0);
+              ri[j] = i < nc ? ri[j] : 0.0;
+            }
           }
-        }
-        if (nc < NC) {
+          const unsigned long long absent = row_absent(own.x, own.y, i, nc);
+          if (absent) row_leave_out<NC>(rr, ri, absent, l, 1.0);
+          spec_sweep<NC>(rr, ri, i, pmin);
+          if (nc < NC) {
 #pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            rr[j] = i < nc ? rr[j] : (i == j ? 1.0 : 0.0);
-            ri[j] = i < nc ? ri[j] : 0.0;
+            for (int j = 0; j < NC; ++j) {
+              sr[j] = i < nc && j < nc ? sr[j] : 0.0;
+              si[j] = i < nc && j < nc ? si[j] : 0.0;
+            }
           }
-        }
-        const unsigned long long absent = row_absent(own.x, own.y, i, nc);
-        if (absent) row_leave_out<NC>(rr, ri, absent, l, 1.0);
-        spec_sweep<NC>(rr, ri, i, pmin);
-        if (nc < NC) {
 #pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            sr[j] = i < nc && j < nc ? sr[j] : 0.0;
-            si[j] = i < nc && j < nc ? si[j] : 0.0;
+          for (int j = 0; j < NC; ++j) sr[j] -= i == j ? edc : 0.0;
+          if constexpr (oblique) {  // Sigma' of the rows of Q, by way of the matrix area
+            spec_put_row<NC>(xb, i, sr, si);
+            spec_inner<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // a few at a time: few registers
+              const v2d x = xb[ic * NC + j];
+              rr[j] -= x.x;
+              ri[j] -= x.y;
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+              rr[j] -= sr[j];
+              ri[j] -= si[j];
+            }
           }
-        }
+          if (absent) row_leave_out<NC>(rr, ri, absent, l, 1.0);
+          spec_sweep<NC>(rr, ri, i, pmin);
+          if (absent) row_leave_out<NC>(rr, ri, absent, l, 0.0);
+          if constexpr (oblique) {  // Gl of the rows of S
+            spec_put_row<NC>(xb, i, rr, ri);
+            spec_outer<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
 #pragma unroll
-        for (int j = 0; j < NC; ++j) sr[j] -= i == j ? edc : 0.0;
-        if constexpr (oblique) {  // Sigma' of the rows of Q, by way of the matrix area
-          spec_put_row<NC>(xb, i, sr, si);
-          spec_inner<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
-#pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // a few at a time: few registers
-            const v2d x = xb[ic * NC + j];
-            rr[j] -= x.x;
-            ri[j] -= x.y;
+            for (int j = 0; j < NC; ++j) {
+              if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // a few at a time: few registers
+              const v2d x = xb[ic * NC + j];
+              rr[j] = x.x;
+              ri[j] = x.y;
+            }
           }
-        } else {
+          SpecGl<NC> gl;
+          gl.p = (gv2d*)a.xs +
+                 ((int64_t)(a.ktile_base + ktile) * n4_all + min((ng >> 2) + w, n4_all - 1)) * (4 * NC * NC) +
+                 (nl & 3) * NC + ic;
+          gl.wk = wk;
+          gl.put = want_x && valid && i < NC;
+          gl.more = want_x && kk != kk0;
+          v2d part[spec_jb<NC>()];
+          gl.template load<0>(part);
+          double chk = 0.0;
 #pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            rr[j] -= sr[j];
-            ri[j] -= si[j];
-          }
-        }
-        if (absent) row_leave_out<NC>(rr, ri, absent, l, 1.0);
-        spec_sweep<NC>(rr, ri, i, pmin);
-        if (absent) row_leave_out<NC>(rr, ri, absent, l, 0.0);
-        if constexpr (oblique) {  // Gl of the rows of S
-          spec_put_row<NC>(xb, i, rr, ri);
-          spec_outer<NC>(xb, spec_lds(sh.lf), i, min(i + 1, NC));
-#pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            if (j % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // a few at a time: few registers
-            const v2d x = xb[ic * NC + j];
-            rr[j] = x.x;
-            ri[j] = x.y;
-          }
-        }
-        SpecGl<NC> gl;
-        gl.p = (gv2d*)a.xs + ((int64_t)(a.ktile_base + ktile) * n4_all + min((ng >> 2) + w, n4_all - 1)) * (4 * NC * NC) +
-               (nl & 3) * NC + ic;
-        gl.wk = wk;
-        gl.put = want_x && valid && i < NC;
-        gl.more = want_x && kk != kk0;
-        v2d part[spec_jb<NC>()];
-        gl.template load<0>(part);
-        double chk = 0.0;
-#pragma unroll
-        for (int j = 0; j < NC; ++j) chk += rr[j] + ri[j];
-        if (i < NC && !__builtin_isfinite(chk)) nonfinite = 1;
-        wave_sync();
-        spec_r_blocks<0, NC, WS>(rr, ri, sr, si, valid, i, xb, gl, part);
-        wave_sync();
-        if constexpr (WS) {
-          // R -> (R + R^dag, i (R - R^dag)) as Hermitian pairs, in place: lane i takes the
-          // unordered pairs (i, i + r mod NC); all are read before any is written (and the
-          // two lanes that share a pair at r = NC / 2 write the same values)
-          v2d u[NC / 2 + 1], v[NC / 2 + 1];
-#pragma unroll
-          for (int r = 0; r <= NC / 2; ++r) {
-            const int j = ic + r >= NC ? ic + r - NC : ic + r;
-            u[r] = xb[min(ic, j) * NC + max(ic, j)];
-            v[r] = xb[max(ic, j) * NC + min(ic, j)];
-          }
+          for (int j = 0; j < NC; ++j) chk += rr[j] + ri[j];
+          if (i < NC && !__builtin_isfinite(chk)) nonfinite = 1;
           wave_sync();
-          if (ng + 16 < n1) fill_d(ng + 16, sh.dt[cur ^ 1], false);  // while the pairs arrive
-          if (i < NC) {
+          spec_r_blocks<0, NC, WS>(rr, ri, sr, si, valid, i, xb, gl, part);
+          wave_sync();
+          if constexpr (WS) {
+            // R -> (R + R^dag, i (R - R^dag)) as Hermitian pairs, in place: lane i takes the
+            // unordered pairs (i, i + r mod NC); all are read before any is written (and the
+            // two lanes that share a pair at r = NC / 2 write the same values)
+            v2d u[NC / 2 + 1], v[NC / 2 + 1];
 #pragma unroll
             for (int r = 0; r <= NC / 2; ++r) {
-              const int j = i + r >= NC ? i + r - NC : i + r;
-              if (r) xb[max(i, j) * NC + min(i, j)] = (v2d){u[r].y - v[r].y, u[r].x - v[r].x};
-              xb[min(i, j) * NC + max(i, j)] = (v2d){u[r].x + v[r].x, -(u[r].y + v[r].y)};
+              const int j = ic + r >= NC ? ic + r - NC : ic + r;
+              u[r] = xb[min(ic, j) * NC + max(ic, j)];
+              v[r] = xb[max(ic, j) * NC + min(ic, j)];
             }
-            if (!valid) {  // frequencies past the tile add nothing
+            wave_sync();
+            if (ng + 16 < n1) fill_d(ng + 16, sh.dt[cur ^ 1], false);  // while the pairs arrive
+            if (i < NC) {
 #pragma unroll
-              for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){0.0, 0.0};
+              for (int r = 0; r <= NC / 2; ++r) {
+                const int j = i + r >= NC ? i + r - NC : i + r;
+                if (r) xb[max(i, j) * NC + min(i, j)] = (v2d){u[r].y - v[r].y, u[r].x - v[r].x};
+                xb[min(i, j) * NC + max(i, j)] = (v2d){u[r].x + v[r].x, -(u[r].y + v[r].y)};
+              }
+              if (!valid) {  // frequencies past the tile add nothing
+#pragma unroll
+                for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){0.0, 0.0};
+              }
             }
+          } else {
+            if (ng + 16 < n1) fill_d(ng + 16, sh.dt[cur ^ 1], false);
           }
-        } else {
-          if (ng + 16 < n1) fill_d(ng + 16, sh.dt[cur ^ 1], false);
+        }
+        __syncthreads();
+        // ---- stage C: rows 2v: d_v^2, rows 2v + 1: d_v d_{v+1}
+        if constexpr (WS) {
+          const int l = spec_here(tid & 63), q = l >> 4, c16 = l & 15;
+          const lv2d* xc = spec_lds(&sh.xr[q * NP + c16 + 16 * wc]);
+          const lv2d *d1[RT], *d2[RT];
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            const int row = 16 * (wr + WR * r) + c16;  // rows past 2 nb - 2 are never read
+            d1[r] = spec_lds(&sh.dt[cur][q * DS + min(row >> 1, NBP - 1)]);
+            d2[r] = spec_lds(&sh.dt[cur][q * DS + min((row + 1) >> 1, NBP - 1)]);
+          }
+          // row factors of all 16 frequencies first, then products only; operands one
+          // chunk of four frequencies ahead
+          v2d h[2][CT];
+          auto fetch = [&](int c, int s) {
+#pragma unroll
+            for (int t = 0; t < CT; ++t) h[s][t] = xc[4 * c * NP + 16 * WC * t];
+          };
+          double fr[4][RT], fi[4][RT];
+          {
+            v2d x[4][RT], y[4][RT];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+              for (int r = 0; r < RT; ++r) {
+                x[c][r] = d1[r][4 * c * DS];
+                y[c][r] = d2[r][4 * c * DS];
+              }
+            fetch(0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+              for (int r = 0; r < RT; ++r) {
+                fr[c][r] = x[c][r].x * y[c][r].x - x[c][r].y * y[c][r].y;
+                fi[c][r] = x[c][r].x * y[c][r].y + x[c][r].y * y[c][r].x;
+              }
+          }
+          spec_for<0, 4>([&](auto ci) {
+            constexpr int c = decltype(ci)::value;
+            if constexpr (c < 3) fetch(c + 1, (c + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < CT; ++t) {
+#pragma unroll
+              for (int r = 0; r < RT; ++r) acc[r][t] = mma(fr[c][r], h[c & 1][t].x, acc[r][t]);
+#pragma unroll
+              for (int r = 0; r < RT; ++r) acc[r][t] = mma(fi[c][r], h[c & 1][t].y, acc[r][t]);
+            }
+          });
         }
       }
-      __syncthreads();
-      // ---- stage C: rows 2v: d_v^2, rows 2v + 1: d_v d_{v+1}
-      if constexpr (WS) {
-        const int l = spec_here(tid & 63), q = l >> 4, c16 = l & 15;
-        const lv2d* xc = spec_lds(&sh.xr[q * NP + c16 + 16 * wc]);
-        const lv2d *d1[RT], *d2[RT];
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-          const int row = 16 * (wr + WR * r) + c16;  // rows past 2 nb - 2 are never read
-          d1[r] = spec_lds(&sh.dt[cur][q * DS + min(row >> 1, NBP - 1)]);
-          d2[r] = spec_lds(&sh.dt[cur][q * DS + min((row + 1) >> 1, NBP - 1)]);
-        }
-        // row factors of all 16 frequencies first, then products only; operands one
-        // chunk of four frequencies ahead
-        v2d h[2][CT];
-        auto fetch = [&](int c, int s) {
-#pragma unroll
-          for (int t = 0; t < CT; ++t) h[s][t] = xc[4 * c * NP + 16 * WC * t];
-        };
-        double fr[4][RT], fi[4][RT];
-        {
-          v2d x[4][RT], y[4][RT];
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-              x[c][r] = d1[r][4 * c * DS];
-              y[c][r] = d2[r][4 * c * DS];
-            }
-          fetch(0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-              fr[c][r] = x[c][r].x * y[c][r].x - x[c][r].y * y[c][r].y;
-              fi[c][r] = x[c][r].x * y[c][r].y + x[c][r].y * y[c][r].x;
-            }
-        }
-        spec_for<0, 4>([&](auto ci) {
-          constexpr int c = decltype(ci)::value;
-          if constexpr (c < 3) fetch(c + 1, (c + 1) & 1);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int t = 0; t < CT; ++t) {
-#pragma unroll
-            for (int r = 0; r < RT; ++r) acc[r][t] = mma(fr[c][r], h[c & 1][t].x, acc[r][t]);
-#pragma unroll
-            for (int r = 0; r < RT; ++r) acc[r][t] = mma(fi[c][r], h[c & 1][t].y, acc[r][t]);
-          }
-        });
-      }
-    }
     };
     if (uniform_i(sh.use_q))
       frequencies(std::true_type());

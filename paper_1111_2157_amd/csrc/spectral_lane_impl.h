@@ -18,7 +18,7 @@
 //
 // Bound by the matrix cores (A and C: 4 nb nc^2 and 8 nb nc^2 with nc^2 padded to 32)
 // and, at small windows, by B.  Measured per k-point and frequency, 512 k-points, 2048
-// frequencies, row layout in brackets: 64 bands 0.72 ns (1.04), 48 0.57 (0.98), 32
+// frequencies, row layout in brackets: 64 bands 0.72 ns (1.04), 48 0.58 (0.98), 32
 // 0.44 (0.82), 16 0.33 (0.7).  Six orbitals do not fit the registers at 64 bands.
 #pragma once
 
@@ -168,277 +168,277 @@ __device__ __forceinline__ void spec_lane_tile(const DysonArgs& a, int ktile, in
     for (int m = 0; m < NBP / 16; ++m) sd[m] = 0.0;
 
     auto frequencies = [&](auto obl) __attribute__((always_inline)) {  // two copies, see spec_tile
-    constexpr bool oblique = decltype(obl)::value;
-    for (int ng = n0; ng < n1; ng += 64) {
-      // ---- stage A
-      {
-        const int l = spec_here(lane), q = l >> 4, c16 = l & 15;
-        const lds_double* es = (const lds_double*)&sh.eps[q];
-#pragma clang loop unroll(disable)
-        for (int f = 0; f < 64 && ng + f < n1; f += 16) {
-          const double wn = (double)(2 * min(ng + f + c16, n1 - 1) + 1) * pib;
-          v4d xa[NT][2];
-#pragma unroll
-          for (int t = 0; t < NT; ++t) xa[t][0] = xa[t][1] = (v4d){0.0, 0.0, 0.0, 0.0};
-          spec_for<0, NBP / 4>([&](auto ci) {
-            constexpr int c = decltype(ci)::value;
-            if (4 * c >= nb) return;
-            const double2 d = inv_z_minus(mu, wn, es[4 * c]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-              xa[t][0] = mma(d.x, p[t][c], xa[t][0]);
-              xa[t][1] = mma(d.y, p[t][c], xa[t][1]);
-            }
-          });
-          lv2d* xw = spec_lds(&sh.x[(f + q) * LDX + c16]);
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-            if (16 * t + c16 < NN) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) xw[4 * i * LDX + 16 * t] = (v2d){xa[t][0][i], xa[t][1][i]};
-            }
-        }
-      }
-      wave_sync();
-      // ---- stage B: this lane's frequency
-      {
-        const int l = spec_here(lane), n = min(ng + l, n1 - 1);
-        const bool valid = ng + l < n1;
-        const bool whole = nc == NC && ng + 64 <= n1;  // no orbital or frequency to mask
-        lv2d* xb = spec_lds(&sh.x[l * LDX]);
-        double sr[NC][NC], si[NC][NC];  // Sigma', in flight during the first inversion
+      constexpr bool oblique = decltype(obl)::value;
+      for (int ng = n0; ng < n1; ng += 64) {
+        // ---- stage A
         {
-          const gv2d* sg = (const gv2d*)a.sigma + (int64_t)n * nc * nc;
+          const int l = spec_here(lane), q = l >> 4, c16 = l & 15;
+          const lds_double* es = (const lds_double*)&sh.eps[q];
+#pragma clang loop unroll(disable)
+          for (int f = 0; f < 64 && ng + f < n1; f += 16) {
+            const double wn = (double)(2 * min(ng + f + c16, n1 - 1) + 1) * pib;
+            v4d xa[NT][2];
 #pragma unroll
-          for (int i = 0; i < NC; ++i)
+            for (int t = 0; t < NT; ++t) xa[t][0] = xa[t][1] = (v4d){0.0, 0.0, 0.0, 0.0};
+            spec_for<0, NBP / 4>([&](auto ci) {
+              constexpr int c = decltype(ci)::value;
+              if (4 * c >= nb) return;
+              const double2 d = inv_z_minus(mu, wn, es[4 * c]);
+              __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              const v2d v = sg[min(i, nc - 1) * nc + min(j, nc - 1)];
-              sr[i][j] = v.x;
-              si[i][j] = v.y;
-            }
-        }
-        double gr[NC][NC], gi[NC][NC];
-#pragma unroll
-        for (int i = 0; i < NC; ++i)
-#pragma unroll
-          for (int j = i; j < NC; ++j) {
-            const v2d re = xb[i * NC + j];
-            v2d im = (v2d){0.0, 0.0};
-            if (i != j) im = xb[j * NC + i];
-            gr[i][j] = re.x - im.y;
-            gi[i][j] = re.y + im.x;
-            if (i != j) {
-              gr[j][i] = re.x + im.y;
-              gi[j][i] = re.y - im.x;
-            }
-          }
-        // orbitals without weight in this window (see row_absent; the same in every lane)
-        int absent = 0;
-#pragma unroll
-        for (int i = 0; i < NC; ++i) absent |= i < nc && gr[i][i] == 0.0 && gi[i][i] == 0.0 ? 1 << i : 0;
-        absent = __builtin_amdgcn_readfirstlane(absent);
-        auto leave_out = [&](double diag) {
-#pragma unroll
-          for (int i = 0; i < NC; ++i)
-#pragma unroll
-            for (int j = 0; j < NC; ++j)
-              if ((absent >> i | absent >> j) & 1) {
-                gr[i][j] = i == j ? diag : 0.0;
-                gi[i][j] = 0.0;
+              for (int t = 0; t < NT; ++t) {
+                xa[t][0] = mma(d.x, p[t][c], xa[t][0]);
+                xa[t][1] = mma(d.y, p[t][c], xa[t][1]);
               }
-        };
-        if (absent) leave_out(1.0);
-        // orbitals past nc and frequencies past the tile: X = 1, Sigma' = 0
-        if (!whole) {
+            });
+            lv2d* xw = spec_lds(&sh.x[(f + q) * LDX + c16]);
 #pragma unroll
-          for (int i = 0; i < NC; ++i)
+            for (int t = 0; t < NT; ++t)
+              if (16 * t + c16 < NN) {
 #pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              const bool on = valid && i < nc && j < nc;
-              gr[i][j] = on ? gr[i][j] : (i == j ? 1.0 : 0.0);
-              gi[i][j] = on ? gi[i][j] : 0.0;
-            }
-        }
-        lane_inverse<NC>(gr, gi, pmin);
-#pragma unroll
-        for (int i = 0; i < NC; ++i) sr[i][i] -= ((const gdouble*)a.e_dc)[min(i, nc - 1)];
-        if (!whole) {
-#pragma unroll
-          for (int i = 0; i < NC; ++i)
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              const bool on = valid && i < nc && j < nc;
-              sr[i][j] = on ? sr[i][j] : 0.0;
-              si[i][j] = on ? si[i][j] : 0.0;
-            }
-        }
-        if constexpr (oblique) {  // Sigma' of the rows of Q, by way of this lane's part of the matrix area
-#pragma unroll
-          for (int i = 0; i < NC; ++i) {
-            __builtin_amdgcn_sched_barrier(0);  // a row at a time: few registers
-#pragma unroll
-            for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){sr[i][j], si[i][j]};
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          spec_inner<NC>(xb, spec_lds(sh.lf), 0, NC);
-#pragma unroll
-          for (int i = 0; i < NC; ++i) {
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              const v2d x = xb[i * NC + j];
-              gr[i][j] -= x.x;
-              gi[i][j] -= x.y;
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        } else {
-#pragma unroll
-          for (int i = 0; i < NC; ++i)
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              gr[i][j] -= sr[i][j];
-              gi[i][j] -= si[i][j];
-            }
-        }
-        if (absent) leave_out(1.0);
-        lane_inverse<NC>(gr, gi, pmin);
-        if (absent) leave_out(0.0);
-        if constexpr (oblique) {  // Gl of the rows of S
-#pragma unroll
-          for (int i = 0; i < NC; ++i) {
-            __builtin_amdgcn_sched_barrier(0);  // a row at a time: few registers
-#pragma unroll
-            for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){gr[i][j], gi[i][j]};
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          spec_outer<NC>(xb, spec_lds(sh.lf), 0, NC);
-#pragma unroll
-          for (int i = 0; i < NC; ++i) {
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              const v2d x = xb[i * NC + j];
-              gr[i][j] = x.x;
-              gi[i][j] = x.y;
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        double chk = 0.0;
-#pragma unroll
-        for (int i = 0; i < NC; ++i)
-#pragma unroll
-          for (int j = 0; j < NC; ++j) chk += gr[i][j] + gi[i][j];
-        if (!__builtin_isfinite(chk)) nonfinite = 1;
-        if (want_x && valid) {
-          gv2d* xp = (gv2d*)a.xs + (int64_t)(a.ktile_base + ktile) * NN * nw4 + n;
-#pragma unroll
-          for (int i = 0; i < NC; ++i) {
-            v2d o[NC];
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              o[j] = (v2d){0.0, 0.0};
-              if (kk != kk0) o[j] = xp[(int64_t)(i * NC + j) * nw4];
-            }
-#pragma unroll
-            for (int j = 0; j < NC; ++j)
-              xp[(int64_t)(i * NC + j) * nw4] =
-                  (v2d){__builtin_fma(wk, gr[i][j], o[j].x), __builtin_fma(wk, gi[i][j], o[j].y)};
-          }
-        }
-        if constexpr (WS) {
-          double vr[NC][NC], vi[NC][NC];  // Gl Sigma'
-#pragma unroll
-          for (int i = 0; i < NC; ++i)
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              double x = 0.0, y = 0.0;
-#pragma unroll
-              for (int m = 0; m < NC; ++m) {
-                x = __builtin_fma(gr[i][m], sr[m][j], __builtin_fma(-gi[i][m], si[m][j], x));
-                y = __builtin_fma(gr[i][m], si[m][j], __builtin_fma(gi[i][m], sr[m][j], y));
+                for (int i = 0; i < 4; ++i) xw[4 * i * LDX + 16 * t] = (v2d){xa[t][0][i], xa[t][1][i]};
               }
-              vr[i][j] = x;
-              vi[i][j] = y;
-            }
-          // R (0 past the tile, where Sigma' is), then its Hermitian pairs, in place
+          }
+        }
+        wave_sync();
+        // ---- stage B: this lane's frequency
+        {
+          const int l = spec_here(lane), n = min(ng + l, n1 - 1);
+          const bool valid = ng + l < n1;
+          const bool whole = nc == NC && ng + 64 <= n1;  // no orbital or frequency to mask
+          lv2d* xb = spec_lds(&sh.x[l * LDX]);
+          double sr[NC][NC], si[NC][NC];  // Sigma', in flight during the first inversion
+          {
+            const gv2d* sg = (const gv2d*)a.sigma + (int64_t)n * nc * nc;
 #pragma unroll
-          for (int i = 0; i < NC; ++i)
+            for (int i = 0; i < NC; ++i)
 #pragma unroll
-            for (int j = 0; j < NC; ++j) {
-              double x = sr[i][j], y = si[i][j];
-#pragma unroll
-              for (int m = 0; m < NC; ++m) {
-                x = __builtin_fma(sr[i][m], vr[m][j], __builtin_fma(-si[i][m], vi[m][j], x));
-                y = __builtin_fma(sr[i][m], vi[m][j], __builtin_fma(si[i][m], vr[m][j], y));
+              for (int j = 0; j < NC; ++j) {
+                const v2d v = sg[min(i, nc - 1) * nc + min(j, nc - 1)];
+                sr[i][j] = v.x;
+                si[i][j] = v.y;
               }
-              gr[i][j] = x;
-              gi[i][j] = y;
-            }
+          }
+          double gr[NC][NC], gi[NC][NC];
 #pragma unroll
           for (int i = 0; i < NC; ++i)
 #pragma unroll
             for (int j = i; j < NC; ++j) {
-              xb[i * NC + j] = (v2d){gr[i][j] + gr[j][i], -(gi[i][j] + gi[j][i])};
-              if (i != j) xb[j * NC + i] = (v2d){gi[i][j] - gi[j][i], gr[i][j] - gr[j][i]};
+              const v2d re = xb[i * NC + j];
+              v2d im = (v2d){0.0, 0.0};
+              if (i != j) im = xb[j * NC + i];
+              gr[i][j] = re.x - im.y;
+              gi[i][j] = re.y + im.x;
+              if (i != j) {
+                gr[j][i] = re.x + im.y;
+                gi[j][i] = re.y - im.x;
+              }
             }
-        }
-      }
-      wave_sync();
-      // ---- stage C: rows 2v: d_v^2, rows 2v + 1: d_v d_{v+1}; the next four frequencies'
-      // resolvents while this four's products run
-      if constexpr (WS) {
-        const int l = spec_here(lane), q = l >> 4, c16 = l & 15;
-        const lds_double* es = (const lds_double*)&sh.eps[c16];
-        const int turns = (min(64, n1 - ng) + 3) >> 2;
-        auto table = [&](int c) {
-          const int n = ng + 4 * c + q;
-          const double wn = (double)(2 * min(n, n1 - 1) + 1) * pib;
-          lv2d* dw = spec_lds(&sh.d[c & 1][q * DS + c16]);
+          // orbitals without weight in this window (see row_absent; the same in every lane)
+          int absent = 0;
 #pragma unroll
-          for (int m = 0; m < NBP / 16; ++m) {
-            const double2 d = inv_z_minus(mu, wn, es[16 * m]);
-            dw[16 * m] = (v2d){d.x, d.y};
-            sd[m] += n < n1 ? d.x : 0.0;
+          for (int i = 0; i < NC; ++i) absent |= i < nc && gr[i][i] == 0.0 && gi[i][i] == 0.0 ? 1 << i : 0;
+          absent = __builtin_amdgcn_readfirstlane(absent);
+          auto leave_out = [&](double diag) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+              for (int j = 0; j < NC; ++j)
+                if ((absent >> i | absent >> j) & 1) {
+                  gr[i][j] = i == j ? diag : 0.0;
+                  gi[i][j] = 0.0;
+                }
+          };
+          if (absent) leave_out(1.0);
+          // orbitals past nc and frequencies past the tile: X = 1, Sigma' = 0
+          if (!whole) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                const bool on = valid && i < nc && j < nc;
+                gr[i][j] = on ? gr[i][j] : (i == j ? 1.0 : 0.0);
+                gi[i][j] = on ? gi[i][j] : 0.0;
+              }
           }
-        };
-        table(0);
+          lane_inverse<NC>(gr, gi, pmin);
+#pragma unroll
+          for (int i = 0; i < NC; ++i) sr[i][i] -= ((const gdouble*)a.e_dc)[min(i, nc - 1)];
+          if (!whole) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                const bool on = valid && i < nc && j < nc;
+                sr[i][j] = on ? sr[i][j] : 0.0;
+                si[i][j] = on ? si[i][j] : 0.0;
+              }
+          }
+          if constexpr (oblique) {  // Sigma' of the rows of Q, by way of this lane's part of the matrix area
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+              __builtin_amdgcn_sched_barrier(0);  // a row at a time: few registers
+#pragma unroll
+              for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){sr[i][j], si[i][j]};
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            spec_inner<NC>(xb, spec_lds(sh.lf), 0, NC);
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                const v2d x = xb[i * NC + j];
+                gr[i][j] -= x.x;
+                gi[i][j] -= x.y;
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          } else {
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                gr[i][j] -= sr[i][j];
+                gi[i][j] -= si[i][j];
+              }
+          }
+          if (absent) leave_out(1.0);
+          lane_inverse<NC>(gr, gi, pmin);
+          if (absent) leave_out(0.0);
+          if constexpr (oblique) {  // Gl of the rows of S
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+              __builtin_amdgcn_sched_barrier(0);  // a row at a time: few registers
+#pragma unroll
+              for (int j = 0; j < NC; ++j) xb[i * NC + j] = (v2d){gr[i][j], gi[i][j]};
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            spec_outer<NC>(xb, spec_lds(sh.lf), 0, NC);
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                const v2d x = xb[i * NC + j];
+                gr[i][j] = x.x;
+                gi[i][j] = x.y;
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          double chk = 0.0;
+#pragma unroll
+          for (int i = 0; i < NC; ++i)
+#pragma unroll
+            for (int j = 0; j < NC; ++j) chk += gr[i][j] + gi[i][j];
+          if (!__builtin_isfinite(chk)) nonfinite = 1;
+          if (want_x && valid) {
+            gv2d* xp = (gv2d*)a.xs + (int64_t)(a.ktile_base + ktile) * NN * nw4 + n;
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+              v2d o[NC];
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                o[j] = (v2d){0.0, 0.0};
+                if (kk != kk0) o[j] = xp[(int64_t)(i * NC + j) * nw4];
+              }
+#pragma unroll
+              for (int j = 0; j < NC; ++j)
+                xp[(int64_t)(i * NC + j) * nw4] =
+                    (v2d){__builtin_fma(wk, gr[i][j], o[j].x), __builtin_fma(wk, gi[i][j], o[j].y)};
+            }
+          }
+          if constexpr (WS) {
+            double vr[NC][NC], vi[NC][NC];  // Gl Sigma'
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                double x = 0.0, y = 0.0;
+#pragma unroll
+                for (int m = 0; m < NC; ++m) {
+                  x = __builtin_fma(gr[i][m], sr[m][j], __builtin_fma(-gi[i][m], si[m][j], x));
+                  y = __builtin_fma(gr[i][m], si[m][j], __builtin_fma(gi[i][m], sr[m][j], y));
+                }
+                vr[i][j] = x;
+                vi[i][j] = y;
+              }
+            // R (0 past the tile, where Sigma' is), then its Hermitian pairs, in place
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+              for (int j = 0; j < NC; ++j) {
+                double x = sr[i][j], y = si[i][j];
+#pragma unroll
+                for (int m = 0; m < NC; ++m) {
+                  x = __builtin_fma(sr[i][m], vr[m][j], __builtin_fma(-si[i][m], vi[m][j], x));
+                  y = __builtin_fma(sr[i][m], vi[m][j], __builtin_fma(si[i][m], vr[m][j], y));
+                }
+                gr[i][j] = x;
+                gi[i][j] = y;
+              }
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+              for (int j = i; j < NC; ++j) {
+                xb[i * NC + j] = (v2d){gr[i][j] + gr[j][i], -(gi[i][j] + gi[j][i])};
+                if (i != j) xb[j * NC + i] = (v2d){gi[i][j] - gi[j][i], gr[i][j] - gr[j][i]};
+              }
+          }
+        }
         wave_sync();
-#pragma clang loop unroll(disable)
-        for (int c = 0; c < turns; ++c) {
-          const lv2d* dr = spec_lds(&sh.d[c & 1][q * DS]);
-          const lv2d* hr = spec_lds(&sh.x[(4 * c + q) * LDX]);
-          v2d u[NR], v[NR], h[NT];
+        // ---- stage C: rows 2v: d_v^2, rows 2v + 1: d_v d_{v+1}; the next four frequencies'
+        // resolvents while this four's products run
+        if constexpr (WS) {
+          const int l = spec_here(lane), q = l >> 4, c16 = l & 15;
+          const lds_double* es = (const lds_double*)&sh.eps[c16];
+          const int turns = (min(64, n1 - ng) + 3) >> 2;
+          auto table = [&](int c) {
+            const int n = ng + 4 * c + q;
+            const double wn = (double)(2 * min(n, n1 - 1) + 1) * pib;
+            lv2d* dw = spec_lds(&sh.d[c & 1][q * DS + c16]);
 #pragma unroll
-          for (int r = 0; r < NR; ++r) {
-            const int row = 16 * r + c16;
-            u[r] = dr[row >> 1];
-            v[r] = dr[min((row + 1) >> 1, NBP - 1)];
-          }
-#pragma unroll
-          for (int t = 0; t < NT; ++t) h[t] = hr[min(16 * t + c16, NN - 1)];
-          if (c + 1 < turns) table(c + 1);
-          double fr[NR], fi[NR];
-#pragma unroll
-          for (int r = 0; r < NR; ++r) {
-            fr[r] = u[r].x * v[r].x - u[r].y * v[r].y;
-            fi[r] = u[r].x * v[r].y + u[r].y * v[r].x;
-          }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int t = 0; t < NT; ++t) {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) acc[r][t] = mma(fr[r], h[t].x, acc[r][t]);
-#pragma unroll
-            for (int r = 0; r < NR; ++r) acc[r][t] = mma(fi[r], h[t].y, acc[r][t]);
-          }
+            for (int m = 0; m < NBP / 16; ++m) {
+              const double2 d = inv_z_minus(mu, wn, es[16 * m]);
+              dw[16 * m] = (v2d){d.x, d.y};
+              sd[m] += n < n1 ? d.x : 0.0;
+            }
+          };
+          table(0);
           wave_sync();
+#pragma clang loop unroll(disable)
+          for (int c = 0; c < turns; ++c) {
+            const lv2d* dr = spec_lds(&sh.d[c & 1][q * DS]);
+            const lv2d* hr = spec_lds(&sh.x[(4 * c + q) * LDX]);
+            v2d u[NR], v[NR], h[NT];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+              const int row = 16 * r + c16;
+              u[r] = dr[row >> 1];
+              v[r] = dr[min((row + 1) >> 1, NBP - 1)];
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) h[t] = hr[min(16 * t + c16, NN - 1)];
+            if (c + 1 < turns) table(c + 1);
+            double fr[NR], fi[NR];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+              fr[r] = u[r].x * v[r].x - u[r].y * v[r].y;
+              fi[r] = u[r].x * v[r].y + u[r].y * v[r].x;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+#pragma unroll
+              for (int r = 0; r < NR; ++r) acc[r][t] = mma(fr[r], h[t].x, acc[r][t]);
+#pragma unroll
+              for (int r = 0; r < NR; ++r) acc[r][t] = mma(fi[r], h[t].y, acc[r][t]);
+            }
+            wave_sync();
+          }
         }
       }
-    }
     };
     if (use_q)
       frequencies(std::true_type());
