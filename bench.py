@@ -54,16 +54,16 @@ TRAFFIC_SOURCES = ["paper_1111_2157_amd/csrc/spectral_impl.h", "paper_1111_2157_
 TRAFFIC = {
     ("batched-Nk4096-Nb20..64-x8-Nw2048", "low-rank",
      ((32, 5, 4664), (32, 14, 2336), (48, 5, 5820), (48, 14, 2912), (64, 5, 5900), (64, 14, 2952))): {
-        "bytes": 218.03e9,  # FETCH 92.9 GB + WRITE 125.1 GB
+        "bytes": 230.77e9,  # FETCH 99.5 GB + WRITE 131.2 GB
         "profile": "profiles/batched_cfg4.md",
-        "sources_sha256": "fd901cb1d1e17eab6bc1571e515eccb9fee97b20f5f3f36b3f3929ecf6203c73",
+        "sources_sha256": "7c41590fc68ab8fb6b1f5053470b75565c084fc552c83ed05a3528f2261363f3",
     },
     # the plan's quarter k-tile with the default frequency tile
     ("batched-Nk4096-Nb20..64-x8-Nw2048", "low-rank",
      ((32, 5, 4664), (32, 14, 1168), (48, 5, 5820), (48, 14, 1456), (64, 5, 5900), (64, 14, 1476))): {
-        "bytes": 213.81e9,  # FETCH 91.6 GB + WRITE 122.2 GB
+        "bytes": 226.56e9,  # FETCH 98.3 GB + WRITE 128.3 GB
         "profile": "profiles/batched_cfg4.md",
-        "sources_sha256": "fd901cb1d1e17eab6bc1571e515eccb9fee97b20f5f3f36b3f3929ecf6203c73",
+        "sources_sha256": "7c41590fc68ab8fb6b1f5053470b75565c084fc552c83ed05a3528f2261363f3",
     },
 }
 
