@@ -56,14 +56,14 @@ TRAFFIC = {
      ((32, 5, 4664), (32, 14, 2336), (48, 5, 5820), (48, 14, 2912), (64, 5, 5900), (64, 14, 2952))): {
         "bytes": 230.77e9,  # FETCH 99.5 GB + WRITE 131.2 GB
         "profile": "profiles/batched_cfg4.md",
-        "sources_sha256": "7c41590fc68ab8fb6b1f5053470b75565c084fc552c83ed05a3528f2261363f3",
+        "sources_sha256": "0a043e477501a253231f850c588613420f4598221c2de40bb7145990c077d2fc",
     },
     # the plan's quarter k-tile with the default frequency tile
     ("batched-Nk4096-Nb20..64-x8-Nw2048", "low-rank",
      ((32, 5, 4664), (32, 14, 1168), (48, 5, 5820), (48, 14, 1456), (64, 5, 5900), (64, 14, 1476))): {
         "bytes": 226.56e9,  # FETCH 98.3 GB + WRITE 128.3 GB
         "profile": "profiles/batched_cfg4.md",
-        "sources_sha256": "7c41590fc68ab8fb6b1f5053470b75565c084fc552c83ed05a3528f2261363f3",
+        "sources_sha256": "0a043e477501a253231f850c588613420f4598221c2de40bb7145990c077d2fc",
     },
 }
 

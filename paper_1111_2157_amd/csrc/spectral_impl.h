@@ -175,9 +175,12 @@ __device__ __forceinline__ int spec_here(int i) {
 // Whether two rows may ask for it, by the real or imaginary part z of their product and
 // their squared norms, or (same) one row by its own: past |z| = |x| |y| / (3 nc) (below it
 // the Gram matrix of the normalised rows has its eigenvalues in 1/2 .. 3/2), or at a norm
-// far from 1 (a pivot p leaves its row about max(1, |p|) roundings, see SpecStep).  Zero
-// rows do not (row_absent), nor do NaN (they reach the error word).
-__device__ __forceinline__ bool spec_far(double xx) { return xx > 0.0 && !(xx >= 1e-4 && xx <= 1e4); }
+// far from 1 (a pivot p leaves its row about max(1, |p|) roundings, see SpecStep, and the
+// second inversion's pivots go with one over the squared norm: G_loc, 24 bands, 8 orbitals,
+// beta 40, within 4e-15 at norm 1, 1e-14 at 0.3, 6e-14 at 0.1 and 3e-12 at 0.011 in their
+// own basis; the band-window kernels 1e-15).  Zero rows do not (row_absent), nor do NaN
+// (they reach the error word).
+__device__ __forceinline__ bool spec_far(double xx) { return xx > 0.0 && !(xx >= 0.0625 && xx <= 1e4); }
 __device__ __forceinline__ bool spec_oblique(double xx, double yy, double z, bool same, int nc) {
   return same ? spec_far(xx) : z * z * (9.0 * nc * nc) > xx * yy;
 }

@@ -185,3 +185,17 @@ def test_on_either_side_of_the_rule(ctx, kind, nb, nc):
     print("oblique rows", nb, nc, kind, flush=True)
     check(ctx, wl)
     check_trace(ctx, wl, 0.2)
+
+
+@pytest.mark.parametrize("scale", [0.26, 0.24, 0.1, 0.03, 0.011])
+@pytest.mark.parametrize("nb,nc", [(24, 8), (40, 14), (64, 10)])
+def test_small_rows(ctx, nb, nc, scale):
+    """Orthogonal rows of one small norm.  6e-14 relative: a pivot p leaves its row max(1, |p|)
+    times the roundings that rows of norm 1 leave (up to 4e-15 here), and the pivots grow with
+    one over the squared norm, 16 at the norm of 1/4 below which the rows are normalised."""
+    wl = synth.f_shell(nk=3, nb=nb, nc=nc, nw=64, n_narrow=nc)
+    wl.lattice.proj[:] *= scale
+    print("small rows", nb, nc, scale, flush=True)
+    gl = gpu_density(ctx, wl, 0.2)[1]
+    for n, ref in zip([0, 5, 63], oracle.gloc(wl.lattice, wl.sigma, 0.2, [0, 5, 63])):
+        assert np.linalg.norm(gl[n] - ref) <= 6e-14 * np.linalg.norm(ref), n
